@@ -54,8 +54,8 @@ int round_up(int v, int a) { return (v + a - 1) / a * a; }
 struct Layout {
     size_t F, SE, SG, A, Aexp, Y, Yprev, fresh, Yc, top, bottom, tie, cstar, improved, reinit, src;
     size_t best_x, best_y, best_f, best_gen, best_upd, ctrl, partial, Xp, Xb, Ypad, Lpad;
-    size_t Wpack, Xw, lo, hi, Pnet, H0, H1, Zero;
-    size_t Wstar, Ystar, Xp32, Wpack32, Xw32;   // FP32 re-check of BF16 selection winners
+    size_t Wpack, Xw, Xe, lo, hi, Pnet, H0, H1, Zero;
+    size_t Wstar, Ystar, Xp32, Wpack32, Xw32, Xe32;   // FP32 re-check of BF16 selection winners
     size_t desc;                                // the job's descriptor for grouped launches
     size_t total;
     int partial_rows;
@@ -230,6 +230,7 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
         net.wide = need_data && wide_applicable(net) &&
                    (c->fit_path == 2 ||
                     (c->fit_path == 0 && resident_lds_bytes(net) > 160 * 1024 - 512));
+        net.wexp = split_exp(std::max(std::fabs(c->lb), std::fabs(c->ub)));
         if (net.wide && net.S_pad / 256 > fit_max_bpr())
             return fail(MGFWA_EUNSUPPORTED, "too many samples for the wide fitness kernel");
     }
@@ -289,6 +290,7 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
     L.Lpad = take(net.loss == MGFWA_LOSS_CE ? (size_t)net.S_pad * 4 : 0);
     L.Wpack = take(net.wide ? (size_t)L.partial_rows * wide_row_bytes(net) : 0);
     L.Xw = take(net.wide ? (size_t)net.S_pad * wide_kp(net) * (net.bf16 ? 2 : 4) : 0);
+    L.Xe = take(net.wide && !net.bf16 ? (size_t)(net.S_pad + 1) * 4 : 0);
     L.lo = take(s.map_range ? (size_t)s.B * Dp * 4 : 0);
     L.hi = take(s.map_range ? (size_t)s.B * Dp * 4 : 0);
     L.Pnet = take(input && need_data ? (size_t)in.n_packed * 4 : 0);
@@ -301,6 +303,7 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
     L.Xp32 = take(s.recheck && !net.wide ? (size_t)net32.S_pad * net32.in_pad * 4 : 0);
     L.Wpack32 = take(s.recheck && net.wide ? BN * wide_row_bytes(net32) : 0);
     L.Xw32 = take(s.recheck && net.wide ? (size_t)net32.S_pad * wide_kp(net32) * 4 : 0);
+    L.Xe32 = take(s.recheck && net.wide ? (size_t)(net32.S_pad + 1) * 4 : 0);
     L.desc = take(sizeof(JobDesc));
     L.total = off;
     if (s.lag && L.SG != L.SE + BN * s.lam * Dp * 4)
@@ -412,7 +415,8 @@ SparkRegen spark_regen(const mgfwa_ctx *c)
 
 mgfwa_status fit_rows(mgfwa_ctx *c, const FitPlan &plan, const float *W, size_t ld, int rows,
                       OutMap map, float *out, hipStream_t st, hipEvent_t mid = nullptr,
-                      hipEvent_t pre = nullptr, int prepacked = 0, const SparkRegen *rg = nullptr)
+                      hipEvent_t pre = nullptr, int prepacked = 0, const SparkRegen *rg = nullptr,
+                      bool boxed = true)
 {
     if (c->input) {
         STEP(launch_net_input(c->in, plan.net_shape, c->d.Pnet, W, ld, rows, map, out, c->d.H0,
@@ -420,7 +424,7 @@ mgfwa_status fit_rows(mgfwa_ctx *c, const FitPlan &plan, const float *W, size_t 
              "fitness_input");
         if (mid) STEP(hipEventRecord(mid, st), "event");
     } else if (c->net.wide)
-        STEP(launch_fitness_wide(c->net, c->d, W, ld, rows, map, out, st, mid, pre, prepacked),
+        STEP(launch_fitness_wide(c->net, c->d, W, ld, rows, map, out, st, boxed, mid, pre, prepacked),
              "fitness_wide");
     else
         STEP(launch_fitness(c->net, plan, c->d, W, ld, rows, map, out, st, mid, rg), "fitness");
@@ -432,7 +436,7 @@ mgfwa_status fit_rows(mgfwa_ctx *c, const FitPlan &plan, const float *W, size_t 
 mgfwa_status fit_check(mgfwa_ctx *c, const float *W, int rows, float *out, hipStream_t st)
 {
     if (c->net32.wide)
-        STEP(launch_fitness_wide(c->net32, c->d32, W, c->s.Dp, rows, kFlat, out, st),
+        STEP(launch_fitness_wide(c->net32, c->d32, W, c->s.Dp, rows, kFlat, out, st, true),
              "fitness_check_wide");
     else
         STEP(launch_fitness(c->net32, c->plan_check, c->d32, W, c->s.Dp, rows, kFlat, out, st),
@@ -673,6 +677,7 @@ mgfwa_status mgfwa_init(mgfwa_ctx **out, const mgfwa_config *config, const mgfwa
     d.Lpad = c->net.loss == MGFWA_LOSS_CE ? at<int32_t>(b, L.Lpad) : nullptr;
     d.Wpack = c->net.wide ? at<char>(b, L.Wpack) : nullptr;
     d.Xw = c->net.wide ? at<char>(b, L.Xw) : nullptr;
+    d.Xe = c->net.wide && !c->net.bf16 ? at<int32_t>(b, L.Xe) : nullptr;
     d.lo = c->s.map_range ? at<float>(b, L.lo) : nullptr;
     d.hi = c->s.map_range ? at<float>(b, L.hi) : nullptr;
     d.Pnet = c->input && has_data ? at<float>(b, L.Pnet) : nullptr;
@@ -689,6 +694,7 @@ mgfwa_status mgfwa_init(mgfwa_ctx **out, const mgfwa_config *config, const mgfwa
         c->d32.Xp = c->net32.wide ? nullptr : at<float>(b, L.Xp32);
         c->d32.Wpack = c->net32.wide ? at<char>(b, L.Wpack32) : nullptr;
         c->d32.Xw = c->net32.wide ? at<char>(b, L.Xw32) : nullptr;
+        c->d32.Xe = c->net32.wide ? at<int32_t>(b, L.Xe32) : nullptr;
     }
 
     auto bail = [&](mgfwa_status st) {
@@ -707,7 +713,7 @@ mgfwa_status mgfwa_init(mgfwa_ctx **out, const mgfwa_config *config, const mgfwa
                                          problem->labels_dev, d, c->stream), "pack");
         if (r) return bail(r);
         if (c->net.wide) {
-            r = check(c, launch_pack_wide_x(c->net, problem->x_dev, d.Xw, c->stream), "pack_x");
+            r = check(c, launch_pack_wide_x(c->net, problem->x_dev, d, c->stream), "pack_x");
             if (r) return bail(r);
             // the explosion writes only the parameters of its packed rows: the
             // padding must read as zero
@@ -717,7 +723,7 @@ mgfwa_status mgfwa_init(mgfwa_ctx **out, const mgfwa_config *config, const mgfwa
         }
         if (c->s.recheck) {   // FP32 samples of the selection re-check
             r = c->net32.wide
-                    ? check(c, launch_pack_wide_x(c->net32, problem->x_dev, c->d32.Xw, c->stream),
+                    ? check(c, launch_pack_wide_x(c->net32, problem->x_dev, c->d32, c->stream),
                             "pack_x32")
                     : check(c, launch_pack_problem(c->net32, problem->x_dev, problem->y_dev,
                                                    problem->labels_dev, c->d32, c->stream),
@@ -894,7 +900,7 @@ mgfwa_status mgfwa_evaluate(mgfwa_ctx *c, const float *w, int rows, int ld, floa
             HIP_TRY(fit_prepare(plan));
         }
         mgfwa_status r = fit_rows(c, plan, w + (size_t)r0 * ld, (size_t)ld, nr, kFlat, out + r0,
-                                  c->stream);
+                                  c->stream, nullptr, nullptr, 0, nullptr, false);
         if (r) return r;
     }
     return MGFWA_OK;
@@ -1013,7 +1019,10 @@ namespace {
 // device the library runs on holds its own copy until the process ends.  In host
 // code its name is only a stand-in: kernels get the per-device address that
 // hipGetSymbolAddress returns.
-__device__ __align__(256) char scratch[MGFWA_NOALLOC_SCRATCH_BYTES];
+// The wide kernel's sample exponents (at most 64 tiles of 256 samples) follow the
+// bytes whose use the header documents.
+constexpr size_t SCRATCH_EXP_BYTES = 64 * 256 * 4 + ALIGN;
+__device__ __align__(256) char scratch[MGFWA_NOALLOC_SCRATCH_BYTES + SCRATCH_EXP_BYTES];
 
 constexpr int MAX_DEVICES = 64;
 std::mutex g_scratch_mu;
@@ -1115,17 +1124,18 @@ extern "C" mgfwa_status mgfwa_evaluate_noalloc(const mgfwa_problem *problem, int
     d.Lpad = net.loss == MGFWA_LOSS_CE ? at<int32_t>(base, oL) : nullptr;
     d.partial = at<float>(base, oP);
     d.Wpack = net.wide ? at<char>(base, oW) : nullptr;
+    d.Xe = net.wide && !net.bf16 ? at<int32_t>(base, MGFWA_NOALLOC_SCRATCH_BYTES) : nullptr;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     // the array keeps the previous call's contents: every byte a launch reads is
     // rewritten here first (samples, targets, labels and their padding by the
     // packing kernels; packed rows and partial sums by the fitness launch)
     HIP_TRY(launch_pack_problem(net, problem->x_dev, problem->y_dev, problem->labels_dev, d, st));
-    if (net.wide) HIP_TRY(launch_pack_wide_x(net, problem->x_dev, d.Xw, st));
+    if (net.wide) HIP_TRY(launch_pack_wide_x(net, problem->x_dev, d, st));
     for (int r0 = 0; r0 < rows; r0 += chunk) {
         const int nr = std::min(chunk, rows - r0);
         const float *wr = w + (size_t)r0 * ld;
         if (net.wide) {
-            HIP_TRY(launch_fitness_wide(net, d, wr, (size_t)ld, nr, kFlat, out + r0, st));
+            HIP_TRY(launch_fitness_wide(net, d, wr, (size_t)ld, nr, kFlat, out + r0, st, false));
         } else {
             FitPlan plan{};
             if (!fit_select(net, nr, &plan))

@@ -10,50 +10,70 @@
 //             wavefronts owns it, each wavefront a 128 x 128 quarter (16 x 16
 //             MFMA blocks: 8 x 8 accumulator tiles);
 //  * K loop = 32 input columns per step through a ring of LDS stages filled by
-//             direct global->LDS loads (global_load_lds_dwordx4).  BF16
-//             (k_fit_wide_pipe): a 4-stage ring and one barrier per step; each
-//             step refills the stage it consumed with the step 4 ahead and reads
-//             the next step's MFMA fragments into the second of two register
-//             sets, one load and two fragment reads interleaved with every 8
-//             multiplies, so loads, LDS reads and matrix work overlap; a step
-//             needs few other instructions (its look-ahead sources come from
-//             tile bases set once per tile), since with one wavefront per SIMD
-//             they take issue slots from the multiplies.  FP32 (k_fit_wide32):
-//             a 2-stage ring of 64 KiB steps and one barrier per step, placed
-//             before the step's last row block; the next step's loads are
-//             issued in the first quarter of a step's multiplies, each row
-//             block's fragment is read one row block ahead and the last row
-//             block reads the next step's first fragments.  Past the last tile
-//             the look-ahead re-loads the last step (BF16: so its wait counts
-//             are constants);
+//             direct global->LDS loads (global_load_lds_dwordx4).  16-bit operands
+//             (k_fit_wide): a 4-stage ring and one barrier per step; each step
+//             refills the stage it consumed with the step 4 ahead and reads the
+//             next step's MFMA fragments into the second of two register sets, one
+//             load and two fragment reads interleaved with every 8 multiplies, so
+//             loads, LDS reads and matrix work overlap; a step needs few other
+//             instructions (its look-ahead sources come from tile bases set once
+//             per tile), since with one wavefront per SIMD they take issue slots
+//             from the multiplies.  FP32 operands (k_fit_wide32): a 2-stage ring of
+//             64 KiB steps and one barrier per step, placed before the step's last
+//             row block; the next step's loads are issued in the first quarter of
+//             a step's multiplies, each row block's fragment is read one row block
+//             ahead and the last row block reads the next step's first fragments.
+//             Past the last tile the look-ahead re-loads the last step (16-bit: so
+//             its wait counts are constants);
+//  * FP32 from 128 columns on: every operand is split into two FP16 parts,
+//             v 2^e = hi + lo (an exponent e per spark row and per sample,
+//             split_exp), and a tile runs k_fit_wide's loop over its K once per
+//             product of two parts, the small products first: W_lo X_hi, W_hi X_lo,
+//             W_hi X_hi.  The FP32 matrix rate (157 TFLOP/s) bounds a direct FP32
+//             product (k_fit_wide32 reached 0.91 of it); FP16 runs 16x faster, so
+//             three passes have a bound of 833 TFLOP/s.  Precision: two parts hold
+//             23 bits, and the dropped lo-lo product is below 2^-24 of its term
+//             (together 7e-8 rms of a pre-activation); but the running sum at its
+//             full size is rounded once per 32 columns instead of once per few
+//             columns, which from 128 columns on makes the error no larger than
+//             with FP32 instructions (rms at 800 columns, 20 % dense and dense
+//             inputs: 1.4e-7 against 2.3e-7 and 5.1e-7).  Below 128 columns it would
+//             be larger, and k_fit_wide32 stays (networks that narrow come here
+//             only by fit_path).  Infinite inputs or weights (the products of their
+//             parts cancel to NaN) are left to the finalisation (slow_loss);
 //  * swizzle: a 16-byte chunk c of tile row r lives at chunk c ^ s(r), with
-//             s(r) = (r >> 1) & 3 for 64-byte rows (BF16) and r & 7 for 128-byte
-//             rows (FP32).  A 16-byte LDS read serves eight lanes at a time,
+//             s(r) = (r >> 1) & 3 for 64-byte rows (16-bit) and r & 7 for
+//             128-byte rows (FP32).  A 16-byte LDS read serves eight lanes at a time,
 //             four from each half of the wavefront (lanes i..i+3 and
 //             i+32..i+35: here rows 4a..4a+3 with chunks g and g + 2, measured
-//             with the bank-conflict counter); for BF16 those eight land in
+//             with the bank-conflict counter); for 16-bit rows those eight land in
 //             distinct 16-byte bank groups;
-//  * epilogue per tile: activation, layer 2 as MFMAs whose B operand is the
-//             hidden tile straight from the accumulators, the two hidden halves'
-//             logits summed through LDS and stored sample-major, then every lane
-//             computes one sample's loss on its own; one partial per (spark,
-//             sample tile), reduced later in a fixed order;
+//  * epilogue per tile: activation, layer 2 as MFMAs (BF16, or FP32 with FP32
+//             weights) whose B operand is the hidden tile straight from the
+//             accumulators, the two hidden halves' logits summed through LDS and
+//             stored sample-major, then every lane computes one sample's loss on its
+//             own; one partial per (spark, sample tile), reduced later in a fixed
+//             order;
 //  * schedule: blocks are persistent (one per CU); tile groups of GS sparks go
 //             to one XCD, whose blocks split the group's sample tiles round by
 //             round (GS sparks x bx/GS sample tiles at a time), so a spark's rows
 //             are read by one XCD only, by its blocks at about the same time.
-//             A round's operand tiles (4.8 MB at 784-256-10) exceed the XCD's
-//             4 MB L2, so every round fetches them once past the L2 (mostly the
-//             sample tiles, from the Infinity Cache).
+//             A round's operand tiles (4.8 MB at 784-256-10 in BF16) exceed the
+//             XCD's 4 MB L2, so every round fetches them once past the L2 (mostly
+//             the sample tiles, from the Infinity Cache).
 //
 // Packed spark layout (written by k_pack_wide_rows, or by the explosion kernel
-// for explosion sparks; row pitch PR bytes):
+// for explosion sparks; row pitch PR bytes; es = 2 (BF16) or 4 (FP32, two FP16 parts)):
 //   [0, 256*Kp*es)          W1aug as [Kp/32][256][32] (K-blocked: the tile of one
 //                           K step is 16 or 32 KiB of contiguous memory): W1
-//                           (zero-padded), b1 in column `in`
-//   [.., + 16*256*es)       W2[16][256]; in BF16 each 32-column block is stored
-//                           in the order the MFMA lanes consume it
+//                           (zero-padded), b1 in column `in`.  Two FP16 parts: the lo
+//                           plane, then the hi plane
+//   [.., + 16*256*es)       W2[16][256] (FP32, or BF16 with each 32-column block
+//                           stored in the order the MFMA lanes consume it)
 //   [.., + 16*4)            b2[16] (FP32)
+//   [.., + 2*4)             two FP16 parts: the row's exponent, 1 if W1aug has an infinity
+// Packed samples: [S_pad/256] tiles of [Kp/32][256][32] (two FP16 parts: the hi plane,
+// then the lo plane of each tile), with a ones column `in`.
 #pragma once
 
 #include "fit_kernel.h"
@@ -67,13 +87,14 @@ constexpr int WT_K = 32;    // input columns per K step
 constexpr int WT_NW = 4;    // wavefronts per block
 
 typedef __attribute__((address_space(3))) void lds_void_t;
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 
 struct WideArgs {
     const char *Wp;        // packed spark rows
     size_t pr;             // packed row pitch (bytes)
     int rows;
     const char *Xw;        // packed samples, K-blocked per 256-sample tile (kernel element type)
-    int Kp, nk;            // padded K and K steps
+    int Kp, nk, nv;        // padded K, K steps of a plane, K steps of a tile (two FP16 parts: 3 nk)
     int S, S_pad, ntn;     // samples, padded samples, sample tiles
     int fo1;               // output width (<= 16)
     int loss, act;
@@ -81,39 +102,53 @@ struct WideArgs {
     const int32_t *lab;    // [S_pad]
     float *partial;        // [rows][ntn]
     int gs;                // sparks per XCD tile group
+    int hid;               // hidden width
+    const int32_t *Xe;     // two FP16 parts: [S_pad] sample exponents (XE_INF: the sample has an infinity),
+                           // then whether any sample has one
 };
 
 constexpr int ZP = 20;      // LDS pitch (floats) of a sample's logits in the loss exchange
 
-template <bool BF>
-struct WideCfg {
-    static constexpr int ES = BF ? 2 : 4;                  // bytes per element
+// Geometry of k_fit_wide32 (FP32 operands).
+struct Cfg32 {
+    static constexpr int ES = 4;                           // bytes per element
     static constexpr int ROWB = WT_K * ES;                 // bytes per tile row per K step
     static constexpr int NCH = ROWB / 16;                  // 16-byte chunks per row
     static constexpr int RPL = 64 / NCH;                   // rows per wave load (1 KiB)
     static constexpr int TILEB = WT_M * ROWB;              // bytes of one operand tile
     static constexpr int STAGEB = 2 * TILEB;               // W tile + X tile
-    static constexpr int STAGES = 2;                       // FP32 ring (BF16: PipeCfg)
+    static constexpr int STAGES = 2;
     static constexpr int LOADS = STAGEB / 1024 / WT_NW;    // wave loads per wave per step
     static constexpr int ZX = STAGES * STAGEB;             // logits exchange area
-    static constexpr int ZXB = WT_N * ZP * 4;              // logits of the tile's samples
-    static constexpr int LDS = ZX + ZXB;
-    static constexpr int KMULT = WT_K;                     // padded K is a multiple
+    static constexpr int LDS = ZX + WT_N * ZP * 4;         // ... of the tile's samples
 };
 
-// BF16 software pipeline: a 4-stage ring; fragments of the next step are read
-// from LDS while the current step multiplies.
+// Geometry of k_fit_wide (16-bit operands), a software pipeline: a 4-stage ring;
+// fragments of the next step are read from LDS while the current step multiplies.
 struct PipeCfg {
+    static constexpr int ROWB = WT_K * 2;                  // bytes per tile row per K step
+    static constexpr int NCH = ROWB / 16;                  // 16-byte chunks per row
+    static constexpr int RPL = 64 / NCH;                   // rows per wave load (1 KiB)
+    static constexpr int TILEB = WT_M * ROWB;              // bytes of one operand tile
     static constexpr int STAGES = 4;
-    static constexpr int STAGEB = WideCfg<true>::STAGEB;          // 32 KiB
-    static constexpr int LOADS = WideCfg<true>::LOADS;            // 8 per wave per step
-    static constexpr int ZX = STAGES * STAGEB;
-    static constexpr int LDS = ZX + WideCfg<true>::ZXB;           // 148 KiB
+    static constexpr int STAGEB = 2 * TILEB;               // W tile + X tile: 32 KiB
+    static constexpr int LOADS = STAGEB / 1024 / WT_NW;    // 8 wave loads per wave per step
+    static constexpr int ZX = STAGES * STAGEB;             // logits exchange area
+    static constexpr int ZXB = WT_N * ZP * 4;              // logits of the tile's samples
+    static constexpr int LDS = ZX + ZXB;                   // 148 KiB
 };
 
-__device__ __forceinline__ int wide_swz(int row, int nch)
+// Plane tile (of the packed row / of the packed sample tile) that K step v reads: the
+// passes of two parts take the W planes lo, hi, hi and the X planes hi, lo, hi.
+template <int KIND>
+__device__ __forceinline__ int w_tile(const WideArgs &a, int v)
 {
-    return nch == 4 ? ((row >> 1) & 3) : (row & 7);
+    return KIND != WIDE_F16X2 || v < 2 * a.nk ? v : v - a.nk;
+}
+template <int KIND>
+__device__ __forceinline__ int x_tile(const WideArgs &a, int v)
+{
+    return KIND != WIDE_F16X2 || v < 2 * a.nk ? v : v - 2 * a.nk;
 }
 
 // The tile list of a persistent block: groups of gs sparks (gs divides the
@@ -187,7 +222,7 @@ struct PipeLane {
 
 __device__ __forceinline__ PipeLane pipe_lane(int wave, int lane, int nh, int sh)
 {
-    using C = WideCfg<true>;
+    using C = PipeCfg;
     const int n = lane & 15, g = lane >> 4;
     const int lr = lane / C::NCH, pc = lane % C::NCH;
     PipeLane L;
@@ -200,7 +235,7 @@ __device__ __forceinline__ PipeLane pipe_lane(int wave, int lane, int nh, int sh
 }
 
 // Global sources of the look-ahead loads: K step kt of the current tile, or
-// step kt - nk of the next one.  Past the last tile the look-ahead stays on the
+// step kt - nv of the next one.  Past the last tile the look-ahead stays on the
 // current tile's last step (re-loaded into the free stage, so the wait counts
 // are constants).
 struct Look {
@@ -208,23 +243,24 @@ struct Look {
     int nmask;        // -1 while a next tile exists, else 0
 };
 
-template <bool BF = true>
+template <int KIND>
 __device__ __forceinline__ void look_set(const WideArgs &a, const TileIter &it, int i, int ntiles,
                                          Look &lk)
 {
-    using C = WideCfg<BF>;
+    constexpr int TILEB = KIND == WIDE_F32 ? Cfg32::TILEB : PipeCfg::TILEB;
+    const size_t xpitch = (size_t)a.nk * (KIND == WIDE_F16X2 ? 2 : 1) * TILEB;
     int r, col;
     it.tile(i, &r, &col);
     lk.wcur = a.Wp + (size_t)r * a.pr;
-    lk.xcur = a.Xw + (size_t)col * a.nk * C::TILEB;
+    lk.xcur = a.Xw + (size_t)col * xpitch;
     if (i + 1 < ntiles) {
         it.tile(i + 1, &r, &col);
         lk.wnext = a.Wp + (size_t)r * a.pr;
-        lk.xnext = a.Xw + (size_t)col * a.nk * C::TILEB;
+        lk.xnext = a.Xw + (size_t)col * xpitch;
         lk.nmask = -1;
     } else {
-        lk.wnext = lk.wcur + (size_t)(a.nk - 1) * C::TILEB;
-        lk.xnext = lk.xcur + (size_t)(a.nk - 1) * C::TILEB;
+        lk.wnext = lk.wcur + (size_t)w_tile<KIND>(a, a.nv - 1) * TILEB;
+        lk.xnext = lk.xcur + (size_t)x_tile<KIND>(a, a.nv - 1) * TILEB;
         lk.nmask = 0;
     }
 }
@@ -240,7 +276,7 @@ template <int T>
 __device__ __forceinline__ void pipe_issue_one(const char *wsrc, const char *xsrc, char *stage,
                                                const PipeLane &L)
 {
-    using C = WideCfg<true>;
+    using C = PipeCfg;
     constexpr int half = T >> 2, blk = (T & 3) * C::RPL * C::ROWB;
     const char *src = (half ? xsrc : wsrc) + L.woff + L.goff;
     char *dst = stage + half * C::TILEB + L.woff;
@@ -253,7 +289,7 @@ __device__ __forceinline__ void pipe_issue_all(const char *wsrc, const char *xsr
                                                const PipeLane &L)
 {
     pipe_issue_one<T>(wsrc, xsrc, stage, L);
-    if constexpr (T + 1 < WideCfg<true>::LOADS) pipe_issue_all<T + 1>(wsrc, xsrc, stage, L);
+    if constexpr (T + 1 < PipeCfg::LOADS) pipe_issue_all<T + 1>(wsrc, xsrc, stage, L);
 }
 
 // 16-byte LDS read at a lane address plus an immediate offset, issued as an
@@ -271,8 +307,8 @@ __device__ __forceinline__ bf16x8 lds_read16_at(uint32_t addr)
 template <int RB>
 __device__ __forceinline__ void pipe_read_rb(uint32_t st, const PipeLane &L, bf16x8 &fa, bf16x8 &fb)
 {
-    fb = lds_read16_at<RB * 16 * WideCfg<true>::ROWB>(st + L.boff);
-    fa = lds_read16_at<RB * 16 * WideCfg<true>::ROWB>(st + L.aoff);
+    fb = lds_read16_at<RB * 16 * PipeCfg::ROWB>(st + L.boff);
+    fa = lds_read16_at<RB * 16 * PipeCfg::ROWB>(st + L.aoff);
 }
 
 // Wait until this wave's loads of the next step's stage have landed (the loads
@@ -289,20 +325,53 @@ __device__ __forceinline__ void pipe_wait()
     cfence();
 }
 
-// The multiply of one accumulator tile in a K step; the first step of a tile
-// starts from zero (addend 0), so the accumulators need no clearing between
-// tiles.
-template <bool FIRST>
+// Fragments of global step q, whose stage is complete, into set P.
+template <int P>
+__device__ __forceinline__ void pipe_first(char *smem, int q, const PipeLane &L, bf16x8 (&fa)[2][8],
+                                           bf16x8 (&fb)[2][8])
+{
+    const uint32_t st = (uint32_t)(uintptr_t)(lds_void_t *)(smem + (q & (PipeCfg::STAGES - 1)) * PipeCfg::STAGEB);
+    pipe_read_rb<0>(st, L, fa[P][0], fb[P][0]);
+    pipe_read_rb<1>(st, L, fa[P][1], fb[P][1]);
+    pipe_read_rb<2>(st, L, fa[P][2], fb[P][2]);
+    pipe_read_rb<3>(st, L, fa[P][3], fb[P][3]);
+    pipe_read_rb<4>(st, L, fa[P][4], fb[P][4]);
+    pipe_read_rb<5>(st, L, fa[P][5], fb[P][5]);
+    pipe_read_rb<6>(st, L, fa[P][6], fb[P][6]);
+    pipe_read_rb<7>(st, L, fa[P][7], fb[P][7]);
+    lgkm_wait_all(fa[P], fb[P]);
+}
+
+// Matrix-core multiply-accumulate in place: c += a x b with the result written
+// over the addend (dst = srcC) in accumulation registers.  Written as inline
+// assembly because with the builtin the register allocator is free to give the
+// result another register than the addend, and in a K loop over 64
+// accumulator tiles it then copies accumulators around on every step.  The
+// compiler does not track the matrix-core latency of these instructions:
+// mfma_acc_sync() must separate them from any other write or read of the
+// accumulators (zeroing before, the epilogue after).  Not volatile: a volatile
+// statement is a scheduling barrier, which would keep the LDS reads of the next
+// fragments from being issued ahead of the multiplies; the data dependences on
+// the accumulators and operands fix the order that matters.
+// The first step of a tile starts from zero (addend 0), so the accumulators need no
+// clearing between tiles.  (bf16x8 is the operands' bit container: FP32 runs hold
+// FP16 parts in it.)
+template <int KIND, bool FIRST>
 __device__ __forceinline__ void mfma_step(floatx4 &c, const bf16x8 &a, const bf16x8 &b)
 {
-    if constexpr (FIRST) asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
-    else mfma_acc(c, a, b);
+    if constexpr (KIND == WIDE_BF16) {
+        if constexpr (FIRST) asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
+        else asm("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+    } else {
+        if constexpr (FIRST) asm("v_mfma_f32_16x16x32_f16 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
+        else asm("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+    }
 }
 
 // Row block RB of one pipelined K step (register set P holds the step's
 // fragments): two fragment reads of the next step into set 1-P, four
 // multiplies, one look-ahead load, four multiplies.
-template <int P, bool FIRST, int RB>
+template <int KIND, int P, bool FIRST, int RB>
 __device__ __forceinline__ void pipe_rb(uint32_t next, const char *wsrc, const char *xsrc,
                                         char *fill, const PipeLane &L, floatx4 (&acc)[8][8],
                                         bf16x8 (&fa)[2][8], bf16x8 (&fb)[2][8])
@@ -310,14 +379,14 @@ __device__ __forceinline__ void pipe_rb(uint32_t next, const char *wsrc, const c
     pipe_read_rb<RB>(next, L, fa[1 - P][RB], fb[1 - P][RB]);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int cb = 0; cb < 4; ++cb) mfma_step<FIRST>(acc[RB][cb], fa[P][RB], fb[P][cb]);
+    for (int cb = 0; cb < 4; ++cb) mfma_step<KIND, FIRST>(acc[RB][cb], fa[P][RB], fb[P][cb]);
     __builtin_amdgcn_sched_barrier(0);
     pipe_issue_one<RB>(wsrc, xsrc, fill, L);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int cb = 4; cb < 8; ++cb) mfma_step<FIRST>(acc[RB][cb], fa[P][RB], fb[P][cb]);
+    for (int cb = 4; cb < 8; ++cb) mfma_step<KIND, FIRST>(acc[RB][cb], fa[P][RB], fb[P][cb]);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (RB + 1 < 8) pipe_rb<P, FIRST, RB + 1>(next, wsrc, xsrc, fill, L, acc, fa, fb);
+    if constexpr (RB + 1 < 8) pipe_rb<KIND, P, FIRST, RB + 1>(next, wsrc, xsrc, fill, L, acc, fa, fb);
 }
 
 // One pipelined K step: step kt of the tile, global step q.  Refill the stage
@@ -325,40 +394,40 @@ __device__ __forceinline__ void pipe_rb(uint32_t next, const char *wsrc, const c
 // 1-P, and run the 64 multiplies of step q.  The per-step address work is a
 // handful of scalar operations: the look-ahead sources come from the tile
 // bases in lk, the fragment addresses from the per-lane offsets in L.
-template <int P, bool FIRST = false>
+template <int KIND, int P, bool FIRST = false>
 __device__ __forceinline__ void pipe_step(const WideArgs &a, char *smem, const Look &lk, int kt,
                                           int q, const PipeLane &L, floatx4 (&acc)[8][8],
                                           bf16x8 (&fa)[2][8], bf16x8 (&fb)[2][8])
 {
-    using C = WideCfg<true>;
+    using C = PipeCfg;
     pipe_wait();
     const int la = kt + PipeCfg::STAGES;
-    const bool wrap = la >= a.nk;
-    const int lo = wrap ? ((la - a.nk) & lk.nmask) : la;
-    const char *wsrc = (wrap ? lk.wnext : lk.wcur) + (size_t)lo * C::TILEB;
-    const char *xsrc = (wrap ? lk.xnext : lk.xcur) + (size_t)lo * C::TILEB;
+    const bool wrap = la >= a.nv;
+    const int lo = wrap ? ((la - a.nv) & lk.nmask) : la;
+    const char *wsrc = (wrap ? lk.wnext : lk.wcur) + (size_t)w_tile<KIND>(a, lo) * C::TILEB;
+    const char *xsrc = (wrap ? lk.xnext : lk.xcur) + (size_t)x_tile<KIND>(a, lo) * C::TILEB;
     char *fill = smem + (q & (PipeCfg::STAGES - 1)) * PipeCfg::STAGEB;
     const uint32_t next = (uint32_t)(uintptr_t)(lds_void_t *)(smem + ((q + 1) & (PipeCfg::STAGES - 1)) *
                                                                           PipeCfg::STAGEB);
-    pipe_rb<P, FIRST, 0>(next, wsrc, xsrc, fill, L, acc, fa, fb);
+    pipe_rb<KIND, P, FIRST, 0>(next, wsrc, xsrc, fill, L, acc, fa, fb);
     lgkm_wait_all(fa[1 - P], fb[1 - P]);
 }
 
 // The K steps of one tile whose first step (global step qbase) uses register
 // set P0: step kt uses set (P0 + kt) & 1, i.e. the parity of its global step,
 // so an odd step count per tile just alternates P0 from tile to tile.
-template <int P0>
+template <int KIND, int P0>
 __device__ __forceinline__ void pipe_tile(const WideArgs &a, char *smem, const Look &lk, int qbase,
                                           const PipeLane &L, floatx4 (&acc)[8][8],
                                           bf16x8 (&fa)[2][8], bf16x8 (&fb)[2][8])
 {
-    pipe_step<P0, true>(a, smem, lk, 0, qbase, L, acc, fa, fb);
+    pipe_step<KIND, P0, true>(a, smem, lk, 0, qbase, L, acc, fa, fb);
     int kt = 1;
-    for (; kt + 1 < a.nk; kt += 2) {
-        pipe_step<1 - P0>(a, smem, lk, kt, qbase + kt, L, acc, fa, fb);
-        pipe_step<P0>(a, smem, lk, kt + 1, qbase + kt + 1, L, acc, fa, fb);
+    for (; kt + 1 < a.nv; kt += 2) {
+        pipe_step<KIND, 1 - P0>(a, smem, lk, kt, qbase + kt, L, acc, fa, fb);
+        pipe_step<KIND, P0>(a, smem, lk, kt + 1, qbase + kt + 1, L, acc, fa, fb);
     }
-    if (kt < a.nk) pipe_step<1 - P0>(a, smem, lk, kt, qbase + kt, L, acc, fa, fb);
+    if (kt < a.nv) pipe_step<KIND, 1 - P0>(a, smem, lk, kt, qbase + kt, L, acc, fa, fb);
 }
 
 // Layer-2 A fragments of this wave's hidden half, read from the packed row.
@@ -368,12 +437,12 @@ struct W2Frag {
     floatx4 b2;
 };
 
-template <bool BF>
+template <int KIND, bool BF = KIND == WIDE_BF16>
 __device__ __forceinline__ void w2_load(const WideArgs &a, int r, int nh, int n, int g, W2Frag<BF> &w)
 {
-    using C = WideCfg<BF>;
-    const char *base = a.Wp + (size_t)r * a.pr + (size_t)WT_M * a.Kp * C::ES;
-    const char *row = base + (size_t)n * WT_M * C::ES;       // output row n (lane % 16)
+    constexpr int ES = BF ? 2 : 4;
+    const char *base = a.Wp + (size_t)r * a.pr + (size_t)WT_M * a.Kp * ES;
+    const char *row = base + (size_t)n * WT_M * ES;          // output row n (lane % 16)
     if constexpr (BF) {
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb)
@@ -383,7 +452,7 @@ __device__ __forceinline__ void w2_load(const WideArgs &a, int r, int nh, int n,
         for (int rb = 0; rb < 8; ++rb)
             w.f[rb] = *reinterpret_cast<const floatx4 *>(row + (128 * nh + 16 * rb + 4 * g) * 4);
     }
-    const float *b2 = reinterpret_cast<const float *>(base + 16 * WT_M * C::ES);
+    const float *b2 = reinterpret_cast<const float *>(base + 16 * WT_M * ES);
     w.b2 = *reinterpret_cast<const floatx4 *>(b2 + 4 * g);
 }
 
@@ -441,14 +510,6 @@ __device__ __forceinline__ float sample_loss(const WideArgs &a, int s, int label
     return zl == mx ? log1pf(rest) : (mx - zl) + logf(se);
 }
 
-// Label of the sample this lane scores in the epilogue of tile column col
-// (fetched early: its load latency would otherwise sit in the epilogue).
-__device__ __forceinline__ int tile_label(const WideArgs &a, int col, int wave, int lane)
-{
-    const int s = col * WT_N + 64 * wave + lane;
-    return (a.loss == 1 && s < a.S) ? a.lab[s] : 0;
-}
-
 // Sum of a float over the wavefront, exact in lane 0 (other lanes hold partial
 // sums), added in the order of an xor butterfly as lane 0 sees it: pairs and
 // quads by quad permutations, 8 and 16 lanes by rotations within each row of
@@ -473,21 +534,51 @@ __device__ __forceinline__ float wave_sum_lane0(float v)
     return (v + r1) + (r2 + r3);
 }
 
-template <bool BF, int ACT>
-__device__ void wide_epilogue(const WideArgs &a, char *smem, int r, int col, int wave, int lane,
-                              floatx4 (&acc)[8][8], const W2Frag<BF> &w2, float *red, int label,
-                              int zx_off = WideCfg<BF>::ZX)
+constexpr int XE_INF = 1 << 20;    // Xe of a sample with an infinity: its exponent + XE_INF
+constexpr int LABEL_SKIP = -2;     // the sample's loss is not taken here (k_wide_finalize adds it)
+
+__device__ __forceinline__ int sample_exp(int xe) { return xe >= XE_INF / 2 ? xe - XE_INF : xe; }
+
+// What the lane that scores sample s of spark row r in the epilogue needs, fetched
+// early (its load latency would otherwise sit in the epilogue): the label, and with
+// two FP16 parts the exponent e of the pre-activations' scale 2^e.
+struct LaneSample {
+    int label, e;
+};
+
+template <int KIND>
+__device__ __forceinline__ LaneSample lane_sample(const WideArgs &a, int r, int col, int wave, int lane)
 {
-    using C = WideCfg<BF>;
+    const int s = col * WT_N + 64 * wave + lane;
+    LaneSample ls;
+    ls.label = (a.loss == 1 && s < a.S) ? a.lab[s] : 0;
+    ls.e = 0;
+    if constexpr (KIND == WIDE_F16X2) {
+        const int32_t *t = wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp);
+        const int xe = a.Xe[s];
+        ls.e = t[0] + sample_exp(xe);
+        if (t[1] || xe >= XE_INF / 2) ls.label = LABEL_SKIP;
+    }
+    return ls;
+}
+
+template <int KIND, int ACT, bool BF = KIND == WIDE_BF16>
+__device__ void wide_epilogue(const WideArgs &a, char *smem, int r, int col, int wave, int lane,
+                              floatx4 (&acc)[8][8], const W2Frag<BF> &w2, float *red,
+                              const LaneSample &own)
+{
+    constexpr bool SPLIT = KIND == WIDE_F16X2;
+    constexpr bool LATE = SPLIT && ACT <= 1;   // the scale comes off the logits
+    constexpr int ZX_OFF = KIND == WIDE_F32 ? Cfg32::ZX : PipeCfg::ZX;
     const int n = lane & 15, g = lane >> 4, nh = wave & 1, sh = wave >> 1;
     // layer 2: logits of this wave's hidden half.  The activation of the hidden
     // tile (its bias came in through the ones column) is applied as each
     // accumulator is turned into a layer-2 operand: rewriting all 256
     // accumulators in place first would need them all in VGPRs at once.
     floatx4 z[8][1];
-#pragma unroll
-    for (int cb = 0; cb < 8; ++cb) z[cb][0] = zero4();
     if constexpr (BF) {
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) z[cb][0] = zero4();
 #pragma unroll
         for (int kb = 0; kb < 4; ++kb) {
             const bf16x8 afr = __builtin_bit_cast(bf16x8, w2.f[kb]);
@@ -500,18 +591,44 @@ __device__ void wide_epilogue(const WideArgs &a, char *smem, int r, int col, int
             }
         }
     } else {
+        // two FP16 parts: the accumulators hold the pre-activations times 2^e; identity
+        // and ReLU commute with the scale, which the scoring lanes then take off the
+        // logits
+        int e[8];
+        if constexpr (SPLIT && !LATE) {
+            const int re = wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp)[0];
 #pragma unroll
-        for (int rb = 0; rb < 8; ++rb)
+            for (int cb = 0; cb < 8; ++cb)
+                e[cb] = re + sample_exp(a.Xe[(size_t)col * WT_N + 128 * sh + 16 * cb + n]);
+        }
 #pragma unroll
-            for (int cb = 0; cb < 8; ++cb) {
-                const floatx4 h = act4<ACT>(acc[rb][cb]);
+        for (int cb = 0; cb < 8; ++cb) {
+            // two FP16 parts: a sum per weight column of a 16-row block, then the four
+            // together (shorter chains round less than one of 128 terms)
+            floatx4 zv[SPLIT ? 4 : 1];
 #pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    z[cb][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(w2.f[rb][v], h[v], z[cb][0], 0, 0, 0);
+            for (int rb = 0; rb < 8; ++rb) {
+                floatx4 h = acc[rb][cb];
+                if constexpr (SPLIT && !LATE) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) h[v] = __builtin_ldexpf(h[v], -e[cb]);
+                }
+                h = act4<ACT>(h);
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    floatx4 &t = zv[SPLIT ? v : 0];
+                    t = __builtin_amdgcn_mfma_f32_16x16x4f32(
+                        w2.f[rb][v], h[v], rb == 0 && (SPLIT || v == 0) ? zero4() : t, 0, 0, 0);
+                }
             }
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                z[cb][0][v] = SPLIT ? (zv[0][v] + zv[SPLIT ? 1 : 0][v]) + (zv[SPLIT ? 2 : 0][v] + zv[SPLIT ? 3 : 0][v])
+                                    : zv[0][v];
+        }
     }
     // the upper hidden half hands its partial logits to the lower half
-    float *zx = reinterpret_cast<float *>(smem + zx_off);
+    float *zx = reinterpret_cast<float *>(smem + ZX_OFF);
     // (block cb of the 64 lanes' 16-byte partials is contiguous: consecutive
     // lanes hit consecutive bank groups)
     float *mine = zx + ((size_t)sh * 8 * 64 + lane) * 4;
@@ -531,7 +648,10 @@ __device__ void wide_epilogue(const WideArgs &a, char *smem, int r, int col, int
         for (int cb = 0; cb < 8; ++cb) {
             const floatx4 o = *reinterpret_cast<const floatx4 *>(mine + cb * 64 * 4);
 #pragma unroll
-            for (int v = 0; v < 4; ++v) z[cb][0][v] = z[cb][0][v] + o[v] + b2[v];
+            for (int v = 0; v < 4; ++v) {
+                z[cb][0][v] = z[cb][0][v] + o[v];
+                if constexpr (!LATE) z[cb][0][v] = z[cb][0][v] + b2[v];
+            }
         }
     }
     lds_barrier();
@@ -546,7 +666,7 @@ __device__ void wide_epilogue(const WideArgs &a, char *smem, int r, int col, int
     const int sl = 64 * wave + lane;                // sample within the tile
     const int s = col * WT_N + sl;
     float ls = 0.0f;
-    if (s < a.S) {
+    if (s < a.S && own.label != LABEL_SKIP) {
         float zz[16];
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
@@ -554,7 +674,16 @@ __device__ void wide_epilogue(const WideArgs &a, char *smem, int r, int col, int
 #pragma unroll
             for (int e = 0; e < 4; ++e) zz[4 * q4 + e] = v[e];
         }
-        ls = sample_loss<BF>(a, s, label, zz);
+        if constexpr (LATE) {
+            const float *b2 = reinterpret_cast<const float *>(a.Wp + (size_t)r * a.pr +
+                                                              (size_t)WT_M * a.Kp * 4) + 16 * WT_M;
+#pragma unroll
+            for (int o = 0; o < 16; ++o) {
+                zz[o] = __builtin_ldexpf(zz[o], -own.e) + b2[o];
+                if (a.loss == 1 && o >= a.fo1) zz[o] = -__builtin_huge_valf();
+            }
+        }
+        ls = sample_loss<BF>(a, s, own.label, zz);
     }
     // fixed-order reduction: the wavefront's sum, then the four wavefronts in order
     ls = wave_sum_lane0(ls);
@@ -570,9 +699,7 @@ __device__ void wide_epilogue(const WideArgs &a, char *smem, int r, int col, int
 // during the first half, issues the next step's 16 loads into the other stage
 // within the first four row blocks (they have ~10 row blocks, ~4 us, to land),
 // and passes the barrier before its last row block, which reads the next step's
-// first fragments.  Same tiles, layout, multiply order and results as the
-// two-barrier form it replaces; the step's sources come from the tile bases
-// (no divisions).
+// first fragments; the step's sources come from the tile bases (no divisions).
 struct Lane32 {
     uint32_t goff;       // lane's byte offset inside a 1 KiB block of 8 rows (global side)
     uint32_t aoff[2];    // LDS offset of the lane's A fragment of row block 0, half kk
@@ -582,7 +709,7 @@ struct Lane32 {
 
 __device__ __forceinline__ Lane32 lane32(int wave, int lane, int nh, int sh)
 {
-    using C = WideCfg<false>;
+    using C = Cfg32;
     static_assert(C::NCH == 8 && C::RPL == 8, "128-byte rows, 8 rows per wave load");
     const int n = lane & 15, g = lane >> 4;
     const int lr = lane / C::NCH, pc = lane % C::NCH;
@@ -607,7 +734,7 @@ __device__ __forceinline__ Lane32 lane32(int wave, int lane, int nh, int sh)
 template <int T>
 __device__ __forceinline__ void issue32(const char *wsrc, const char *xsrc, char *stage, const Lane32 &L)
 {
-    using C = WideCfg<false>;
+    using C = Cfg32;
     constexpr int half = T >> 3, blk = T & 7;
     constexpr int hi = (blk >> 2) * 4096, lo = (blk & 3) * 1024;
     const char *src = (half ? xsrc : wsrc) + L.woff + hi + L.goff;
@@ -637,7 +764,7 @@ __device__ __forceinline__ void lgkm_wait9(floatx4 &a, floatx4 (&b)[8])
 template <int CB>
 __device__ __forceinline__ void read_b32(uint32_t addr, floatx4 (&b)[8])
 {
-    b[CB] = lds_read4_at<CB * 16 * WideCfg<false>::ROWB>(addr);
+    b[CB] = lds_read4_at<CB * 16 * Cfg32::ROWB>(addr);
     if constexpr (CB + 1 < 8) read_b32<CB + 1>(addr, b);
 }
 
@@ -645,7 +772,7 @@ template <bool FIRST>
 __device__ __forceinline__ void mfma32(floatx4 &c, float a, float b)
 {
     if constexpr (FIRST) asm("v_mfma_f32_16x16x4_f32 %0, %1, %2, 0" : "=a"(c) : "v"(a), "v"(b));
-    else mfma_acc(c, a, b);
+    else asm("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
 }
 
 // Stage complete for every wavefront: this wave's loads have landed and its
@@ -675,7 +802,7 @@ __device__ __forceinline__ void rb32(uint32_t st, uint32_t stn, const char *wsrc
                                      char *fill, const Lane32 &L, floatx4 (&acc)[8][8],
                                      floatx4 (&fa)[2], floatx4 (&b0)[8], floatx4 (&b1)[8])
 {
-    using C = WideCfg<false>;
+    using C = Cfg32;
     constexpr int RB1 = RB + 1 < 8 ? RB + 1 : 0;
     constexpr int J = 8 * KK + RB;              // A fragment J of the step lives in fa[J % 2]
     if constexpr (J < 15)
@@ -728,7 +855,7 @@ __device__ __forceinline__ void step32(const WideArgs &a, char *smem, const Look
                                        const Lane32 &L, floatx4 (&acc)[8][8], floatx4 (&fa)[2],
                                        floatx4 (&b0)[8], floatx4 (&b1)[8])
 {
-    using C = WideCfg<false>;
+    using C = Cfg32;
     const bool wrap = kt + 1 >= a.nk;
     const char *wsrc = wrap ? lk.wnext : lk.wcur + (size_t)(kt + 1) * C::TILEB;
     const char *xsrc = wrap ? lk.xnext : lk.xcur + (size_t)(kt + 1) * C::TILEB;
@@ -742,7 +869,7 @@ __device__ __forceinline__ void step32(const WideArgs &a, char *smem, const Look
 template <int ACT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_fit_wide32(WideArgs a)
 {
-    using C = WideCfg<false>;
+    using C = Cfg32;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ float red[4];
     const int lane = threadIdx.x & 63;
@@ -760,7 +887,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     if (ntiles == 0) return;
     const Lane32 L = lane32(wave, lane, nh, sh);
     Look lk;
-    look_set<false>(a, it, 0, ntiles, lk);
+    look_set<WIDE_F32>(a, it, 0, ntiles, lk);
     // prologue: step 0 of tile 0 into stage 0
     issue32<0>(lk.wcur, lk.xcur, smem, L);
     issue32<1>(lk.wcur, lk.xcur, smem, L);
@@ -789,28 +916,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     for (int i = 0; i < ntiles; ++i) {
         int r, col;
         it.tile(i, &r, &col);
-        if (i > 0) look_set<false>(a, it, i, ntiles, lk);
+        if (i > 0) look_set<WIDE_F32>(a, it, i, ntiles, lk);
         floatx4 acc[8][8];
         const int qbase = i * a.nk;
         step32<true>(a, smem, lk, 0, qbase, L, acc, fa, b0, b1);
         // the epilogue's global inputs, fetched while the tile's K loop runs
         // (after its first step: the next step's wait covers them)
         W2Frag<false> w2;
-        w2_load<false>(a, r, nh, n, g, w2);
-        const int label = tile_label(a, col, wave, lane);
+        w2_load<WIDE_F32>(a, r, nh, n, g, w2);
+        const LaneSample own = lane_sample<WIDE_F32>(a, r, col, wave, lane);
         for (int kt = 1; kt < a.nk; ++kt) step32<false>(a, smem, lk, kt, qbase + kt, L, acc, fa, b0, b1);
         mfma_acc_sync(acc);
-        wide_epilogue<false, ACT>(a, smem, r, col, wave, lane, acc, w2, red, label);
+        wide_epilogue<WIDE_F32, ACT>(a, smem, r, col, wave, lane, acc, w2, red, own);
     }
     __builtin_amdgcn_s_waitcnt(0);
 }
 
-// BF16 wide kernel with the software pipeline above (same tiles, layout and
-// epilogue as the FP32 kernel).
-template <int ACT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_fit_wide_pipe(WideArgs a)
+// 16-bit operands: BF16, or FP32 in two FP16 parts.
+template <int KIND, int ACT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_fit_wide(WideArgs a)
 {
-    using C = WideCfg<true>;
+    using C = PipeCfg;
+    constexpr bool BF = KIND == WIDE_BF16;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ float red[4];
     const int lane = threadIdx.x & 63;
@@ -830,12 +957,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     // own tile or the next one
     const PipeLane L = pipe_lane(wave, lane, nh, sh);
     Look lk;
-    look_set(a, it, 0, ntiles, lk);
+    look_set<KIND>(a, it, 0, ntiles, lk);
     // prologue: steps 0..3 of tile 0 into stages 0..3, then the fragments of step 0
 #pragma unroll
     for (int s = 0; s < PipeCfg::STAGES; ++s)
-        pipe_issue_all(lk.wcur + (size_t)s * C::TILEB, lk.xcur + (size_t)s * C::TILEB,
-                       smem + s * PipeCfg::STAGEB, L);
+        pipe_issue_all(lk.wcur + (size_t)w_tile<KIND>(a, s) * C::TILEB,
+                       lk.xcur + (size_t)x_tile<KIND>(a, s) * C::TILEB, smem + s * PipeCfg::STAGEB, L);
     {
         constexpr int n3 = 3 * PipeCfg::LOADS;
         cfence();
@@ -844,39 +971,108 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         cfence();
     }
     bf16x8 fa[2][8], fb[2][8];
-    {
-        const uint32_t st0 = (uint32_t)(uintptr_t)(lds_void_t *)smem;
-        pipe_read_rb<0>(st0, L, fa[0][0], fb[0][0]);
-        pipe_read_rb<1>(st0, L, fa[0][1], fb[0][1]);
-        pipe_read_rb<2>(st0, L, fa[0][2], fb[0][2]);
-        pipe_read_rb<3>(st0, L, fa[0][3], fb[0][3]);
-        pipe_read_rb<4>(st0, L, fa[0][4], fb[0][4]);
-        pipe_read_rb<5>(st0, L, fa[0][5], fb[0][5]);
-        pipe_read_rb<6>(st0, L, fa[0][6], fb[0][6]);
-        pipe_read_rb<7>(st0, L, fa[0][7], fb[0][7]);
-    }
-    lgkm_wait_all(fa[0], fb[0]);
+    pipe_first<0>(smem, 0, L, fa, fb);
     for (int i = 0; i < ntiles; ++i) {
         int r, col;
         it.tile(i, &r, &col);
-        if (i > 0) look_set(a, it, i, ntiles, lk);
+        if (i > 0) look_set<KIND>(a, it, i, ntiles, lk);
         floatx4 acc[8][8];
         // the epilogue's global inputs are fetched at the start of the tile;
         // then every load in flight (the tile's first look-ahead steps
-        // included) is waited for.  Measured on 784-256-10: with this drain
-        // at each tile start the XCD's blocks stay closer in step and the
+        // included) is waited for.  Measured on 784-256-10 in BF16: with this
+        // drain at each tile start the XCD's blocks stay closer in step and the
         // kernel is 4 % faster at tile groups of 4-8 sparks than without it.
-        W2Frag<true> w2;
-        w2_load<true>(a, r, nh, n, g, w2);
-        const int label = tile_label(a, col, wave, lane);
+        // FP32 with tanh or GELU: its epilogue's registers, added to these and to the
+        // next tile's first fragments, would push accumulators out of the AGPRs
+        // inside the K loop, where nothing orders such a move after the multiplies;
+        // both are fetched when they are needed.
+        constexpr bool EARLY = BF || ACT <= 1;
+        W2Frag<BF> w2;
+        if constexpr (EARLY) w2_load<KIND>(a, r, nh, n, g, w2);
+        const LaneSample own = lane_sample<KIND>(a, r, col, wave, lane);
         __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0)
-        const int qbase = i * a.nk;
-        if (qbase & 1) pipe_tile<1>(a, smem, lk, qbase, L, acc, fa, fb);
-        else pipe_tile<0>(a, smem, lk, qbase, L, acc, fa, fb);
+        const int qbase = i * a.nv;
+        if (qbase & 1) {
+            if constexpr (!EARLY) pipe_first<1>(smem, qbase, L, fa, fb);
+            pipe_tile<KIND, 1>(a, smem, lk, qbase, L, acc, fa, fb);
+        } else {
+            if constexpr (!EARLY) pipe_first<0>(smem, qbase, L, fa, fb);
+            pipe_tile<KIND, 0>(a, smem, lk, qbase, L, acc, fa, fb);
+        }
         mfma_acc_sync(acc);
-        wide_epilogue<true, ACT>(a, smem, r, col, wave, lane, acc, w2, red, label, PipeCfg::ZX);
+        if constexpr (!EARLY) w2_load<KIND>(a, r, nh, n, g, w2);
+        wide_epilogue<KIND, ACT>(a, smem, r, col, wave, lane, acc, w2, red, own);
     }
     __builtin_amdgcn_s_waitcnt(0);
+}
+
+// Loss of sample s of spark row r, column by column from the FP16 parts in FP32: for
+// samples and rows with an infinity, which the products of its parts (the lo part is
+// zero) would turn into a NaN.  Serial and slow; nothing else takes it.
+template <int ACT>
+__device__ float slow_loss(const WideArgs &a, int r, int s)
+{
+    const char *row = a.Wp + (size_t)r * a.pr;
+    const size_t plane = (size_t)WT_M * a.Kp;          // elements of a plane (of W, and of a sample tile)
+    const _Float16 *wlo = reinterpret_cast<const _Float16 *>(row), *whi = wlo + plane;
+    const _Float16 *xhi = reinterpret_cast<const _Float16 *>(a.Xw) + (size_t)(s / WT_N) * 2 * plane +
+                          (size_t)(s % WT_N) * WT_K;
+    const _Float16 *xlo = xhi + plane;
+    const float *w2 = reinterpret_cast<const float *>(row + plane * 4);
+    const int e = wide_row_exp(row, a.Kp)[0] + sample_exp(a.Xe[s]);
+    float zz[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) zz[j] = w2[16 * WT_M + j];
+    for (int o = 0; o < a.hid; ++o) {
+        float h = 0.0f;
+        for (int k = 0; k < a.Kp; ++k) {
+            const size_t ks = (size_t)(k / WT_K) * WT_M * WT_K + k % WT_K, wk = ks + (size_t)o * WT_K;
+            h = __builtin_fmaf((float)whi[wk] + (float)wlo[wk], (float)xhi[ks] + (float)xlo[ks], h);
+        }
+        h = act_c<ACT>(ldexpf(h, -e));
+#pragma unroll
+        for (int j = 0; j < 16; ++j) zz[j] = __builtin_fmaf(w2[j * WT_M + o], h, zz[j]);
+    }
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+        if (a.loss == 1 && j >= a.fo1) zz[j] = -__builtin_huge_valf();
+    return sample_loss<false>(a, s, a.loss == 1 ? a.lab[s] : 0, zz);
+}
+
+// Sum of a row's partials in order, scaled to the mean, NaN -> +inf, scattered: one
+// thread per row; with two FP16 parts one block per row, which first adds the losses
+// of the samples that k_fit_wide left out, and the sum is taken in binary64 (the
+// rounding of this sum was most of the error of an FP32 fitness: 9e-8 of 8,192
+// samples' mean).
+template <int KIND, int ACT>
+__global__ __launch_bounds__(256) void k_wide_finalize(WideArgs a, float inv_norm, OutMap map,
+                                                       float *__restrict__ out)
+{
+    int r;
+    using Sum = std::conditional_t<KIND == WIDE_F16X2, double, float>;
+    Sum t = 0;
+    if constexpr (KIND != WIDE_F16X2) {
+        r = blockIdx.x * 256 + threadIdx.x;
+        if (r >= a.rows) return;
+    } else {
+        r = blockIdx.x;
+        const bool row_inf = wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp)[1] != 0;
+        if (row_inf || a.Xe[a.S_pad]) {
+            __shared__ float red[256];
+            for (int s0 = 0; s0 < a.S; s0 += 256) {
+                const int s = s0 + threadIdx.x;
+                red[threadIdx.x] = s < a.S && (row_inf || a.Xe[s] >= XE_INF / 2) ? slow_loss<ACT>(a, r, s)
+                                                                          : 0.0f;
+                __syncthreads();
+                if (threadIdx.x == 0)
+                    for (int i = 0; i < 256; ++i) t += red[i];
+                __syncthreads();
+            }
+        }
+        if (threadIdx.x != 0) return;
+    }
+    for (int c = 0; c < a.ntn; ++c) t += a.partial[(size_t)r * a.ntn + c];
+    out[map.index(r)] = canon_fitness((float)(t * (Sum)inv_norm));
 }
 
 }  // namespace fit

@@ -13,32 +13,37 @@ namespace {
 constexpr int TPB = 256;
 constexpr int MAX_GRID_Y = 65535;
 
-// One 16-byte chunk of a packed spark row per thread.  Chunk ranges:
-//   W1aug  [Kp/32][256][32]  K-blocked: value(o, k) = W1[o][k] (k < in),
-//                        b1[o] (k == in), 0 otherwise, at ((k/32)*256 + o)*32 + k%32
-//   W2     [16][256]     BF16: chunk (i, kb, g) holds W2[i][32kb + p(g, e)], e = 0..7,
-//                        p(g, e) = 4g + e (e < 4) or 16 + 4g + e - 4 (e >= 4);
-//                        FP32: natural order
-//   b2     [16]          FP32
-constexpr int PACK_CPT = 4;   // 16-byte chunks per thread (strided by the block)
+// Part of a packed spark row per thread.  Chunk ranges:
+//   W1aug  [Kp/32][256][32]  8 columns each, K-blocked: value(o, k) = W1[o][k]
+//                        (k < in), b1[o] (k == in), 0 otherwise, at
+//                        ((k/32)*256 + o)*32 + k%32 of its plane (FP16 parts: both planes)
+//   W2     [16][256]     16 bytes each; BF16: chunk (i, kb, g) holds
+//                        W2[i][32kb + p(g, e)], e = 0..7, p(g, e) = 4g + e (e < 4) or
+//                        16 + 4g + e - 4 (e >= 4); FP32: natural order
+//   b2     [16]          FP32, four each
+constexpr int PACK_CPT = 4;   // chunks per thread (strided by the block)
 constexpr int PACK_RPB = 4;   // spark rows per block
 
-// One 16-byte output chunk of a packed row (see the layout above).
-template <bool BF>
-__device__ __forceinline__ void pack_chunk(const float *__restrict__ w, char *__restrict__ wp,
-                                           int chunk, int c1, int c2, int in, int hid, int out,
-                                           int woff1, int boff1, int woff2, int boff2)
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b)
 {
-    constexpr int ES = BF ? 2 : 4, EPC = 16 / ES;   // elements per chunk
-    float v[EPC];
+    return (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)a) |
+           ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)b) << 16);
+}
+
+template <int KIND>
+__device__ __forceinline__ void pack_chunk(const float *__restrict__ w, char *__restrict__ wp,
+                                           int chunk, int c1, int c2, const WidePack &p, int wexp)
+{
+    constexpr bool BF = KIND == WIDE_BF16;
     if (chunk < c1) {
-        const int e0 = chunk * EPC, kb = e0 / (WT_M * WT_K), rem = e0 % (WT_M * WT_K);
+        const int e0 = chunk * 8, kb = e0 / (WT_M * WT_K), rem = e0 % (WT_M * WT_K);
         const int o = rem / WT_K, k0 = kb * WT_K + rem % WT_K;
-        const float *src = w + woff1 + (size_t)o * in + k0;
-        if (o < hid && k0 + EPC <= in && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
+        const float *src = w + p.woff1 + (size_t)o * p.in + k0;
+        float v[8];
+        if (o < p.hid && k0 + 8 <= p.in && (reinterpret_cast<uintptr_t>(src) & 15) == 0) {
             // inside W1 and 16-byte aligned: vector loads
 #pragma unroll
-            for (int e = 0; e < EPC; e += 4) {
+            for (int e = 0; e < 8; e += 4) {
                 const float4 t = *reinterpret_cast<const float4 *>(src + e);
                 v[e] = t.x;
                 v[e + 1] = t.y;
@@ -47,18 +52,38 @@ __device__ __forceinline__ void pack_chunk(const float *__restrict__ w, char *__
             }
         } else {
 #pragma unroll
-            for (int e = 0; e < EPC; ++e) {
+            for (int e = 0; e < 8; ++e) {
                 const int k = k0 + e;
                 float x = 0.0f;
-                if (o < hid) {
-                    if (k < in) x = w[woff1 + (size_t)o * in + k];
-                    else if (k == in) x = w[boff1 + o];
+                if (o < p.hid) {
+                    if (k < p.in) x = w[p.woff1 + (size_t)o * p.in + k];
+                    else if (k == p.in) x = w[p.boff1 + o];
                 }
                 v[e] = x;
             }
         }
+        if constexpr (BF) {
+            reinterpret_cast<uint4 *>(wp)[chunk] =
+                make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]),
+                           pack_bf16(v[6], v[7]));
+        } else if constexpr (KIND == WIDE_F16X2) {
+            halfx8 hi, lo;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const SplitF16 s = split_f16(v[e], wexp);
+                hi[e] = s.hi;
+                lo[e] = s.lo;
+            }
+            reinterpret_cast<halfx8 *>(wp)[chunk] = lo;
+            reinterpret_cast<halfx8 *>(wp)[c1 + chunk] = hi;
+        } else {
+            reinterpret_cast<float4 *>(wp)[2 * chunk] = make_float4(v[0], v[1], v[2], v[3]);
+            reinterpret_cast<float4 *>(wp)[2 * chunk + 1] = make_float4(v[4], v[5], v[6], v[7]);
+        }
     } else if (chunk < c1 + c2) {
+        constexpr int EPC = BF ? 8 : 4;
         const int e0 = (chunk - c1) * EPC, i = e0 / WT_M, c0 = e0 % WT_M;
+        float v[EPC];
 #pragma unroll
         for (int e = 0; e < EPC; ++e) {
             int col = c0 + e;
@@ -66,65 +91,124 @@ __device__ __forceinline__ void pack_chunk(const float *__restrict__ w, char *__
                 const int blk = c0 & ~31, g = (c0 & 31) >> 3;   // c0 = 32kb + 8g
                 col = blk + (e < 4 ? 4 * g + e : 16 + 4 * g + e - 4);
             }
-            v[e] = (i < out && col < hid) ? w[woff2 + (size_t)i * hid + col] : 0.0f;
+            v[e] = (i < p.out && col < p.hid) ? w[p.woff2 + (size_t)i * p.hid + col] : 0.0f;
         }
+        char *dst = wp + (size_t)c1 * (BF ? 16 : 32) + (size_t)(chunk - c1) * 16;
+        if constexpr (BF)
+            *reinterpret_cast<uint4 *>(dst) = make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]),
+                                                         pack_bf16(v[4], v[5]), pack_bf16(v[6], v[7]));
+        else
+            *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
     } else {
         const int i0 = (chunk - c1 - c2) * 4;
-        float *dst = reinterpret_cast<float *>(wp + (size_t)c1 * 16 + (size_t)c2 * 16);
+        float *dst = reinterpret_cast<float *>(wp + (size_t)c1 * (BF ? 16 : 32) + (size_t)c2 * 16);
         float4 b;
-        b.x = i0 + 0 < out ? w[boff2 + i0 + 0] : 0.0f;
-        b.y = i0 + 1 < out ? w[boff2 + i0 + 1] : 0.0f;
-        b.z = i0 + 2 < out ? w[boff2 + i0 + 2] : 0.0f;
-        b.w = i0 + 3 < out ? w[boff2 + i0 + 3] : 0.0f;
+        b.x = i0 + 0 < p.out ? w[p.boff2 + i0 + 0] : 0.0f;
+        b.y = i0 + 1 < p.out ? w[p.boff2 + i0 + 1] : 0.0f;
+        b.z = i0 + 2 < p.out ? w[p.boff2 + i0 + 2] : 0.0f;
+        b.w = i0 + 3 < p.out ? w[p.boff2 + i0 + 3] : 0.0f;
         reinterpret_cast<float4 *>(dst)[i0 / 4] = b;
-        return;
     }
-    uint4 q;
-    if constexpr (BF) {
-        uint32_t h[4];
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            h[e] = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * e]) |
-                   ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * e + 1]) << 16);
-        q = make_uint4(h[0], h[1], h[2], h[3]);
-    } else {
-        q = make_uint4(__float_as_uint(v[0]), __float_as_uint(v[1]), __float_as_uint(v[2]),
-                       __float_as_uint(v[3]));
-    }
-    reinterpret_cast<uint4 *>(wp)[chunk] = q;
 }
 
 // A block packs PACK_RPB rows x (PACK_CPT * TPB) chunks: fat blocks, so the
-// dispatcher is not what bounds the pass.
-template <bool BF>
+// dispatcher is not what bounds the pass.  boxed: FP16 parts take the box's
+// exponent (and store it), otherwise the one k_wide_row_exp stored.
+template <int KIND>
 __global__ __launch_bounds__(TPB) void k_pack_wide_rows(const float *__restrict__ W, size_t ld,
-                                                        int rows, char *__restrict__ Wp, size_t pr,
-                                                        int in, int hid, int out, int Kp, int woff1,
-                                                        int boff1, int woff2, int boff2)
+                                                        int rows, WidePack p, int boxed)
 {
-    constexpr int ES = BF ? 2 : 4, EPC = 16 / ES;   // elements per chunk
-    const int c1 = WT_M * Kp / EPC;                  // chunks of W1aug
-    const int c2 = 16 * WT_M / EPC;                  // chunks of W2
+    const int c1 = WT_M * p.Kp / 8;                  // chunks of W1aug
+    const int c2 = 16 * WT_M / (KIND == WIDE_BF16 ? 8 : 4);         // chunks of W2
     const int nchunk = c1 + c2 + 4;
     const int cfirst = blockIdx.x * TPB * PACK_CPT + threadIdx.x;
     for (int r0 = blockIdx.y * PACK_RPB; r0 < rows; r0 += gridDim.y * PACK_RPB) {
         const int rend = r0 + PACK_RPB < rows ? r0 + PACK_RPB : rows;
         for (int r = r0; r < rend; ++r) {
             const float *w = W + (size_t)r * ld;
-            char *wp = Wp + (size_t)r * pr;
+            char *wp = p.Wp + (size_t)r * p.pr;
+            int wexp = p.wexp;
+            if constexpr (KIND == WIDE_F16X2) {
+                int32_t *t = wide_row_exp(wp, p.Kp);
+                if (!boxed) {
+                    wexp = t[0];
+                } else if (cfirst == 0) {
+                    t[0] = wexp;
+                    t[1] = 0;
+                }
+            }
 #pragma unroll
             for (int i = 0; i < PACK_CPT; ++i) {
                 const int chunk = cfirst + i * TPB;
-                if (chunk < nchunk)
-                    pack_chunk<BF>(w, wp, chunk, c1, c2, in, hid, out, woff1, boff1, woff2, boff2);
+                if (chunk < nchunk) pack_chunk<KIND>(w, wp, chunk, c1, c2, p, wexp);
             }
         }
     }
 }
 
-// Samples for the wide kernel, column `in` = 1 (the folded bias), K-blocked per
-// 256-sample tile: element (s, k) at ((s/256 * Kp/32 + k/32) * 256 + s%256) * 32 + k%32,
-// so one K step of one sample tile is a contiguous 256 x 32 block.
+__global__ void k_clear_word(int32_t *p) { *p = 0; }
+
+__device__ __forceinline__ void max_inf(float v, float &m, int &inf)
+{
+    const float a = fabsf(v);
+    if (a <= 3.4028234e38f) m = fmaxf(m, a);   // finite (NaN takes no part)
+    else if (a == __builtin_huge_valf()) inf = 1;
+}
+
+// Exponent and infinity flag of rows that need not lie in the box: one block per
+// row, over W1 and b1 (adjacent, at the start of the spark, which is 16-byte
+// aligned).  A few rows leave most of the chip idle, so a block keeps as many loads
+// in flight as it can: 1024 threads x 4 x 16 bytes.
+constexpr int ROW_EXP_TPB = 1024;
+__global__ __launch_bounds__(ROW_EXP_TPB) void k_wide_row_exp(const float *__restrict__ W, size_t ld,
+                                                              WidePack p)
+{
+    __shared__ float sm[ROW_EXP_TPB / 64];
+    __shared__ int si[ROW_EXP_TPB / 64];
+    const float *w = W + (size_t)blockIdx.x * ld + p.woff1;
+    const int n = p.hid * (p.in + 1), n4 = n / 4;
+    float m = 0.0f;
+    int inf = 0;
+    for (int i0 = threadIdx.x; i0 < n4; i0 += 4 * ROW_EXP_TPB) {
+        float4 v[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = i0 + u * ROW_EXP_TPB;
+            v[u] = i < n4 ? reinterpret_cast<const float4 *>(w)[i] : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            max_inf(v[u].x, m, inf);
+            max_inf(v[u].y, m, inf);
+            max_inf(v[u].z, m, inf);
+            max_inf(v[u].w, m, inf);
+        }
+    }
+    if ((int)threadIdx.x < n - 4 * n4) max_inf(w[4 * n4 + threadIdx.x], m, inf);
+    for (int off = 32; off > 0; off >>= 1) {
+        m = fmaxf(m, __shfl_xor(m, off));
+        inf |= __shfl_xor(inf, off);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        sm[threadIdx.x >> 6] = m;
+        si[threadIdx.x >> 6] = inf;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < ROW_EXP_TPB / 64; ++i) {
+            m = fmaxf(m, sm[i]);
+            inf |= si[i];
+        }
+        int32_t *t = wide_row_exp(p.Wp + (size_t)blockIdx.x * p.pr, p.Kp);
+        t[0] = split_exp(m);
+        t[1] = inf;
+    }
+}
+
+// FP32 or BF16 samples for the wide kernel, column `in` = 1 (the folded bias),
+// K-blocked per 256-sample tile: element (s, k) at
+// ((s/256 * Kp/32 + k/32) * 256 + s%256) * 32 + k%32, so one K step of one sample
+// tile is a contiguous 256 x 32 block.
 template <bool BF>
 __global__ __launch_bounds__(TPB) void k_pack_wide_x(const float *__restrict__ x, int S, int S_pad,
                                                      int in, int Kp, char *__restrict__ Xw)
@@ -140,30 +224,61 @@ __global__ __launch_bounds__(TPB) void k_pack_wide_x(const float *__restrict__ x
     else reinterpret_cast<float *>(Xw)[dst] = v;
 }
 
-__global__ __launch_bounds__(256) void k_wide_finalize(const float *__restrict__ partial, int rows,
-                                                       int ntn, float inv_norm, OutMap map,
-                                                       float *__restrict__ out)
+// Samples in two FP16 parts: one wavefront per sample takes its exponent (the ones
+// column included), then writes both parts of every column (a tile's hi plane, then
+// its lo plane, each K-blocked as above).
+__global__ __launch_bounds__(TPB) void k_pack_wide_x_f16x2(const float *__restrict__ x, int S, int S_pad,
+                                                           int in, int Kp, char *__restrict__ Xw,
+                                                           int32_t *__restrict__ Xe)
 {
-    const int r = blockIdx.x * 256 + threadIdx.x;
-    if (r >= rows) return;
-    float t = 0.0f;
-    for (int c = 0; c < ntn; ++c) t += partial[(size_t)r * ntn + c];
-    out[map.index(r)] = canon_fitness(t * inv_norm);
+    const int s = blockIdx.x * (TPB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (s >= S_pad) return;
+    const float *row = x + (size_t)s * in;
+    float m = 1.0f;
+    int inf = 0;
+    for (int k = lane; s < S && k < in; k += 64) max_inf(row[k], m, inf);
+    for (int off = 32; off > 0; off >>= 1) {
+        m = fmaxf(m, __shfl_xor(m, off));
+        inf |= __shfl_xor(inf, off);
+    }
+    const int e = split_exp(m);
+    if (lane == 0) {
+        Xe[s] = e + (inf ? XE_INF : 0);
+        if (inf) atomicOr(&Xe[S_pad], 1);
+    }
+    const size_t plane = (size_t)WT_N * Kp;
+    _Float16 *hi = reinterpret_cast<_Float16 *>(Xw) + (size_t)(s / WT_N) * 2 * plane;
+    for (int k = lane; k < Kp; k += 64) {
+        const float v = s >= S ? 0.0f : k < in ? row[k] : k == in ? 1.0f : 0.0f;
+        const SplitF16 p = split_f16(v, e);
+        const size_t at = ((size_t)(k / WT_K) * WT_N + s % WT_N) * WT_K + k % WT_K;
+        hi[at] = p.hi;
+        hi[plane + at] = p.lo;
+    }
 }
 
 // One instance per (precision, hidden activation): a run-time activation
 // switch over the 256 accumulators would push them out of registers.
-const void *const kWide[2][4] = {
-    {reinterpret_cast<const void *>(&k_fit_wide32<0>), reinterpret_cast<const void *>(&k_fit_wide32<1>),
-     reinterpret_cast<const void *>(&k_fit_wide32<2>), reinterpret_cast<const void *>(&k_fit_wide32<3>)},
-    {reinterpret_cast<const void *>(&k_fit_wide_pipe<0>), reinterpret_cast<const void *>(&k_fit_wide_pipe<1>),
-     reinterpret_cast<const void *>(&k_fit_wide_pipe<2>), reinterpret_cast<const void *>(&k_fit_wide_pipe<3>)},
+typedef void (*WideFn)(WideArgs);
+typedef void (*WideFin)(WideArgs, float, OutMap, float *);
+struct WideKernels {
+    WideFn fit;
+    WideFin finalize;
 };
+#define WIDE_KIND(K, FIT)                                                                       \
+    {{&FIT 0>, &k_wide_finalize<K, 0>}, {&FIT 1>, &k_wide_finalize<K, 1>},                      \
+     {&FIT 2>, &k_wide_finalize<K, 2>}, {&FIT 3>, &k_wide_finalize<K, 3>}}
+#define COMMA ,
+const WideKernels kWide[3][4] = {WIDE_KIND(WIDE_F32, k_fit_wide32<),
+                                 WIDE_KIND(WIDE_BF16, k_fit_wide<WIDE_BF16 COMMA),
+                                 WIDE_KIND(WIDE_F16X2, k_fit_wide<WIDE_F16X2 COMMA)};
+#undef COMMA
+#undef WIDE_KIND
 
-const void *wide_kernel(const Net &net)
+const WideKernels &wide_kernels(const Net &net)
 {
     const int act = net.act[0] >= 0 && net.act[0] <= 3 ? net.act[0] : 0;
-    return kWide[net.bf16 ? 1 : 0][act];
+    return kWide[wide_kind(net)][act];
 }
 
 // Sparks per XCD tile group.  Enough tiles for the XCD's blocks; when the
@@ -197,42 +312,51 @@ bool wide_applicable(const Net &net)
     return net.nl == 2 && net.fo[0] <= WT_M && net.fo[1] <= 16;
 }
 
-// K (inputs plus the ones column) padded to the kernels' K-step rounds
+// K (inputs plus the ones column) padded to K steps; the 16-bit pipeline looks STAGES
+// steps ahead within a tile and the next, so a tile has at least as many
 int wide_kp(const Net &net)
 {
-    const int step = net.bf16 ? WideCfg<true>::KMULT : WideCfg<false>::KMULT;
-    const int kp = (net.fi[0] + 1 + step - 1) / step * step;
-    // the BF16 pipeline looks STAGES K steps ahead within a tile and the next
+    const int kp = (net.fi[0] + 1 + WT_K - 1) / WT_K * WT_K;
     const int kmin = net.bf16 ? PipeCfg::STAGES * WT_K : 0;
     return kp > kmin ? kp : kmin;
+}
+
+// FP32 takes two FP16 parts from 128 columns on, where their products are at least as
+// accurate as FP32 instructions (fit_wide.h has the figures)
+WideKind wide_kind(const Net &net)
+{
+    return net.bf16 ? WIDE_BF16 : wide_kp(net) >= 128 ? WIDE_F16X2 : WIDE_F32;
 }
 
 size_t wide_row_bytes(const Net &net)
 {
     const size_t es = net.bf16 ? 2 : 4;
-    const size_t b = (size_t)WT_M * wide_kp(net) * es + 16 * WT_M * es + 64;
+    const size_t b = (size_t)WT_M * wide_kp(net) * es + 16 * WT_M * es + 64 + 8;
     return (b + 255) / 256 * 256;
 }
 
-int wide_lds_bytes(const Net &net) { return net.bf16 ? PipeCfg::LDS : WideCfg<false>::LDS; }
+int wide_lds_bytes(const Net &net) { return wide_kind(net) == WIDE_F32 ? Cfg32::LDS : PipeCfg::LDS; }
 
 hipError_t wide_prepare(const Net &net)
 {
-    return hipFuncSetAttribute(wide_kernel(net), hipFuncAttributeMaxDynamicSharedMemorySize,
+    return hipFuncSetAttribute(reinterpret_cast<const void *>(wide_kernels(net).fit), hipFuncAttributeMaxDynamicSharedMemorySize,
                                wide_lds_bytes(net));
 }
 
-hipError_t launch_pack_wide_x(const Net &net, const float *x, char *Xw, hipStream_t st)
+hipError_t launch_pack_wide_x(const Net &net, const float *x, const DevState &d, hipStream_t st)
 {
     const int Kp = wide_kp(net);
-    const size_t n = (size_t)net.S_pad * Kp;
-    const unsigned blocks = (unsigned)((n + TPB - 1) / TPB);
-    if (net.bf16)
-        hipLaunchKernelGGL(k_pack_wide_x<true>, dim3(blocks), dim3(TPB), 0, st, x, net.S, net.S_pad,
-                           net.fi[0], Kp, Xw);
-    else
-        hipLaunchKernelGGL(k_pack_wide_x<false>, dim3(blocks), dim3(TPB), 0, st, x, net.S, net.S_pad,
-                           net.fi[0], Kp, Xw);
+    if (wide_kind(net) == WIDE_F16X2) {
+        constexpr int per = TPB / 64;
+        hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, st, d.Xe + net.S_pad);
+        hipLaunchKernelGGL(k_pack_wide_x_f16x2, dim3((unsigned)((net.S_pad + per - 1) / per)), dim3(TPB),
+                           0, st, x, net.S, net.S_pad, net.fi[0], Kp, d.Xw, d.Xe);
+    } else {
+        const size_t n = (size_t)net.S_pad * Kp;
+        hipLaunchKernelGGL(net.bf16 ? &k_pack_wide_x<true> : &k_pack_wide_x<false>,
+                           dim3((unsigned)((n + TPB - 1) / TPB)), dim3(TPB), 0, st, x, net.S, net.S_pad,
+                           net.fi[0], Kp, d.Xw);
+    }
     return hipGetLastError();
 }
 
@@ -246,7 +370,8 @@ WidePack wide_pack_geometry(const Net &net, const DevState &d)
     p.hid = net.fo[0];
     p.out = net.fo[1];
     p.Kp = wide_kp(net);
-    p.bf16 = net.bf16;
+    p.kind = wide_kind(net);
+    p.wexp = net.wexp;
     p.woff1 = net.woff[0];
     p.boff1 = net.boff[0];
     p.woff2 = net.woff[1];
@@ -255,8 +380,8 @@ WidePack wide_pack_geometry(const Net &net, const DevState &d)
 }
 
 hipError_t launch_fitness_wide(const Net &net, const DevState &d, const float *W, size_t ld,
-                               int rows, OutMap map, float *out, hipStream_t st, hipEvent_t mid,
-                               hipEvent_t pre, int prepacked)
+                               int rows, OutMap map, float *out, hipStream_t st, bool boxed,
+                               hipEvent_t mid, hipEvent_t pre, int prepacked)
 {
     if (rows <= 0) return hipSuccess;
     const int Kp = wide_kp(net);
@@ -264,21 +389,19 @@ hipError_t launch_fitness_wide(const Net &net, const DevState &d, const float *W
     hipError_t e = hipSuccess;
     const int npack = rows - prepacked;
     if (npack > 0) {
-        const int es = net.bf16 ? 2 : 4, epc = 16 / es;
-        const int nchunk = WT_M * Kp / epc + 16 * WT_M / epc + 4;
+        const int nchunk = WT_M * Kp / 8 + 16 * WT_M / (net.bf16 ? 8 : 4) + 4;
         const int rgroups = (npack + PACK_RPB - 1) / PACK_RPB;
         dim3 pg((nchunk + TPB * PACK_CPT - 1) / (TPB * PACK_CPT),
                 rgroups < MAX_GRID_Y ? rgroups : MAX_GRID_Y);
         const float *Wsrc = W + (size_t)prepacked * ld;
-        char *Wdst = d.Wpack + (size_t)prepacked * pr;
-        if (net.bf16)
-            hipLaunchKernelGGL(k_pack_wide_rows<true>, pg, dim3(TPB), 0, st, Wsrc, ld, npack, Wdst, pr,
-                               net.fi[0], net.fo[0], net.fo[1], Kp, net.woff[0], net.boff[0],
-                               net.woff[1], net.boff[1]);
-        else
-            hipLaunchKernelGGL(k_pack_wide_rows<false>, pg, dim3(TPB), 0, st, Wsrc, ld, npack, Wdst,
-                               pr, net.fi[0], net.fo[0], net.fo[1], Kp, net.woff[0], net.boff[0],
-                               net.woff[1], net.boff[1]);
+        WidePack p = wide_pack_geometry(net, d);
+        p.Wp += (size_t)prepacked * pr;
+        if (p.kind == WIDE_F16X2 && !boxed)
+            hipLaunchKernelGGL(k_wide_row_exp, dim3(npack), dim3(ROW_EXP_TPB), 0, st, Wsrc, ld, p);
+        auto *k = p.kind == WIDE_BF16    ? &k_pack_wide_rows<WIDE_BF16>
+                  : p.kind == WIDE_F16X2 ? &k_pack_wide_rows<WIDE_F16X2>
+                                         : &k_pack_wide_rows<WIDE_F32>;
+        hipLaunchKernelGGL(k, pg, dim3(TPB), 0, st, Wsrc, ld, npack, p, boxed ? 1 : 0);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -293,6 +416,10 @@ hipError_t launch_fitness_wide(const Net &net, const DevState &d, const float *W
     a.Xw = d.Xw;
     a.Kp = Kp;
     a.nk = Kp / WT_K;
+    const bool f16x2 = wide_kind(net) == WIDE_F16X2;
+    a.nv = f16x2 ? 3 * a.nk : a.nk;
+    a.hid = net.fo[0];
+    a.Xe = d.Xe;
     a.S = net.S;
     a.S_pad = net.S_pad;
     a.ntn = net.S_pad / WT_N;
@@ -303,16 +430,16 @@ hipError_t launch_fitness_wide(const Net &net, const DevState &d, const float *W
     a.lab = d.Lpad;
     a.partial = d.partial;
     a.gs = wide_group(net, rows, a.ntn);
-    void *args[] = {&a};
-    e = hipLaunchKernel(wide_kernel(net), dim3((unsigned)net.num_cu), dim3(TPB), args,
-                        (size_t)wide_lds_bytes(net), st);
+    const WideKernels &k = wide_kernels(net);
+    hipLaunchKernelGGL(k.fit, dim3((unsigned)net.num_cu), dim3(TPB), (size_t)wide_lds_bytes(net), st, a);
+    e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (mid) {
         e = hipEventRecord(mid, st);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k_wide_finalize, dim3((rows + 255) / 256), dim3(256), 0, st, d.partial, rows,
-                       a.ntn, net.inv_norm, map, out);
+    hipLaunchKernelGGL(k.finalize, dim3((unsigned)(f16x2 ? rows : (rows + 255) / 256)), dim3(256), 0, st,
+                       a, net.inv_norm, map, out);
     return hipGetLastError();
 }
 

@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stddef.h>
 #include <stdint.h>
 
@@ -39,6 +40,7 @@ struct DevState {
     int32_t *Lpad;     // [S_pad] CE labels (-1 padded)
     char *Wpack;       // packed spark rows for the wide-first-layer kernel
     char *Xw;          // [S_pad][Kp] samples with a ones column (wide kernel)
+    int32_t *Xe;       // [S_pad + 1] exponents of samples in two FP16 parts, any-infinity flag
     float *lo, *hi;    // [B][Dp] population ranges (range mapping)
     float *Pnet;       // packed parameters of a fixed network (input problems)
     float *H0, *H1;    // [partial_rows][hnp] activations between layers (input problems)
@@ -77,6 +79,7 @@ struct Net {
     float inv_norm;                    // 1/(S*out) for MSE, 1/S for CE
     int lds_max;                       // LDS bytes a block may use (0: weights stay in global)
     int wide;                          // first layer streamed through LDS (two-layer nets)
+    int wexp;                          // in two FP16 parts: the exponent of weights in the box
     int num_cu;                        // compute units (persistent grid size)
 };
 
@@ -152,30 +155,60 @@ struct FitPlan {
     int net_shape = -1;   // input problems: NET_* kernel shape (-1 chosen per launch)
 };
 
+// Operands of the wide fitness kernel: FP32, BF16, or FP32 in two FP16 parts.
+enum WideKind : int { WIDE_F32 = 0, WIDE_BF16 = 1, WIDE_F16X2 = 2 };
+
 // The wide fitness kernel's packed spark rows, for the explosion kernel to
 // write each spark there as well (the fitness launch then skips packing them).
-// Row layout (fit_wide.hip): W1 with b1 as column `in`, K-blocked as
-// [Kp/32][256][32]; W2 [16][256] (BF16: each 32-column block in MFMA lane
-// order); b2 [16] FP32.  Padding stays zero from initialisation.
+// Row layout (fit_wide.h): W1 with b1 as column `in`, K-blocked as
+// [Kp/32][256][32] (two FP16 parts: lo plane, hi plane); W2 [16][256] (BF16: each 32-column
+// block in MFMA lane order); b2 [16] FP32; two FP16 parts: the row's exponent and infinity
+// flag.  Padding stays zero from initialisation.
 struct WidePack {
     char *Wp;                           // packed rows
     size_t pr;                          // row pitch (bytes)
-    int in, hid, out, Kp, bf16;
+    int in, hid, out, Kp, kind;
+    int wexp;                           // two FP16 parts: exponent of weights inside the box
     int woff1, boff1, woff2, boff2;     // parameter offsets inside a spark
 };
 
-// Byte offset of W1aug element (o, k) (b1 is column k = in) in a packed row.
-__device__ __forceinline__ size_t wide_w1_offset(int o, int k, size_t es)
+// Element offset of W1aug element (o, k) (b1 is column k = in) in its plane.
+__host__ __device__ __forceinline__ size_t wide_w1_offset(int o, int k)
 {
-    return (((size_t)(k >> 5) * 256 + o) * 32 + (k & 31)) * es;
+    return ((size_t)(k >> 5) * 256 + o) * 32 + (k & 31);
 }
 
-// Byte offset of spark coordinate j (< D) in its packed row; *f32 is set when
-// the element is stored as FP32 whatever the precision (b2).
-__device__ __forceinline__ size_t wide_pack_offset(const WidePack &p, int j, bool *f32)
+// Exponent that brings values up to `bound` in magnitude below 2^15 (a bound of
+// 0 or less, or not finite, gives that of 1).  The same for every bound in
+// (2^-3, 2^3], so that ordinary rows get the same parts, bit for bit, whether the
+// bound is their own maximum or the search box's: at 12, an FP16 pair keeps its
+// full precision down to 2^-14.
+__host__ __device__ __forceinline__ int split_exp(float bound)
 {
-    const size_t es = p.bf16 ? 2 : 4;
-    *f32 = false;
+    if (!(bound > 0.0f) || bound > 3.4028234e38f || (bound > 0.125f && bound <= 8.0f)) return 12;
+    int e;
+    (void)frexpf(bound, &e);          // bound < 2^e
+    return 15 - e;
+}
+
+// FP16 parts of v 2^e: hi + lo has 23 of its 24 bits.  An infinity is all hi.
+struct SplitF16 {
+    _Float16 hi, lo;
+};
+__device__ __forceinline__ SplitF16 split_f16(float v, int e)
+{
+    const float x = __builtin_ldexpf(v, e);
+    SplitF16 p;
+    p.hi = (_Float16)x;
+    p.lo = __builtin_isinf(x) ? (_Float16)0.0f : (_Float16)(x - (float)p.hi);
+    return p;
+}
+
+// Store spark coordinate j (< D) in its packed row at dst, in the row's precision.
+__device__ __forceinline__ void wide_store(const WidePack &p, char *dst, int j, float v)
+{
+    const size_t plane = (size_t)256 * p.Kp;   // elements of a W1aug plane
+    char *w2 = dst + plane * (p.kind == WIDE_BF16 ? 2 : 4);
     int o, k;
     if (j >= p.woff1 && j < p.woff1 + p.hid * p.in) {
         const int rel = j - p.woff1;
@@ -186,17 +219,38 @@ __device__ __forceinline__ size_t wide_pack_offset(const WidePack &p, int j, boo
         k = p.in;
     } else if (j >= p.woff2 && j < p.woff2 + p.out * p.hid) {
         const int rel = j - p.woff2, i = rel / p.hid, c = rel - i * p.hid;
-        int pos = c;
-        if (p.bf16) {
+        if (p.kind == WIDE_BF16) {
             const int r = c & 31;
-            pos = (c & ~31) + (r < 16 ? (r >> 2) * 8 + (r & 3) : ((r - 16) >> 2) * 8 + 4 + (r & 3));
+            const int pos = (c & ~31) + (r < 16 ? (r >> 2) * 8 + (r & 3) : ((r - 16) >> 2) * 8 + 4 + (r & 3));
+            reinterpret_cast<__bf16 *>(w2)[(size_t)i * 256 + pos] = (__bf16)v;
+        } else {
+            reinterpret_cast<float *>(w2)[(size_t)i * 256 + c] = v;
         }
-        return (size_t)256 * p.Kp * es + ((size_t)i * 256 + pos) * es;
+        return;
     } else {
-        *f32 = true;
-        return (size_t)256 * p.Kp * es + (size_t)16 * 256 * es + (size_t)(j - p.boff2) * 4;
+        reinterpret_cast<float *>(w2 + 16 * 256 * (p.kind == WIDE_BF16 ? 2 : 4))[j - p.boff2] = v;
+        return;
     }
-    return wide_w1_offset(o, k, es);
+    const size_t at = wide_w1_offset(o, k);
+    if (p.kind == WIDE_BF16) {
+        reinterpret_cast<__bf16 *>(dst)[at] = (__bf16)v;
+    } else if (p.kind == WIDE_F16X2) {
+        const SplitF16 s = split_f16(v, p.wexp);
+        reinterpret_cast<_Float16 *>(dst)[at] = s.lo;
+        reinterpret_cast<_Float16 *>(dst)[plane + at] = s.hi;
+    } else {
+        reinterpret_cast<float *>(dst)[at] = v;
+    }
+}
+
+// The exponent and infinity flag at the end of a packed row of two FP16 parts.
+__device__ __forceinline__ int32_t *wide_row_exp(char *row, int Kp)
+{
+    return reinterpret_cast<int32_t *>(row + (size_t)256 * Kp * 4 + 16 * 256 * 4 + 64);
+}
+__device__ __forceinline__ const int32_t *wide_row_exp(const char *row, int Kp)
+{
+    return wide_row_exp(const_cast<char *>(row), Kp);
 }
 
 // ---- grouped launches (batched generations) --------------------------------
@@ -370,14 +424,18 @@ hipError_t net_input_prepare(const InNet &net);   // raises the kernels' LDS lim
 // ---- fit_wide.hip
 bool wide_applicable(const Net &net);
 int wide_kp(const Net &net);
+WideKind wide_kind(const Net &net);
 size_t wide_row_bytes(const Net &net);
 int wide_lds_bytes(const Net &net);
 hipError_t wide_prepare(const Net &net);
-hipError_t launch_pack_wide_x(const Net &net, const float *x, char *Xw, hipStream_t st);
-// prepacked: the first rows are already in d.Wpack (written by the explosion)
+// Packed samples into d.Xw (two FP16 parts: their exponents into d.Xe).
+hipError_t launch_pack_wide_x(const Net &net, const float *x, const DevState &d, hipStream_t st);
+// prepacked: the first rows are already in d.Wpack (written by the explosion).
+// boxed: every row lies in the search box (FP16 parts take the box's exponent);
+// otherwise each row's exponent comes from its own largest weight.
 hipError_t launch_fitness_wide(const Net &net, const DevState &d, const float *W, size_t ld,
                                int rows, OutMap map, float *out, hipStream_t st,
-                               hipEvent_t mid = nullptr, hipEvent_t pre = nullptr,
+                               bool boxed, hipEvent_t mid = nullptr, hipEvent_t pre = nullptr,
                                int prepacked = 0);
 WidePack wide_pack_geometry(const Net &net, const DevState &d);
 

@@ -82,8 +82,12 @@ __global__ __launch_bounds__(TPB) void k_pop_range_group(GroupTable t)
 // the mapping stream of the same (chunk, row, generation).
 // With PACK the spark is also written in the wide fitness kernel's packed
 // layout (row `row` of wp.Wp): four coordinates of one W1 row inside one
-// 32-column block (the common case) as one store, others one by one.
-template <bool BF>
+// 32-column block (the common case) as one store (one per FP16 part), others one
+// by one.
+typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+
+template <int KIND>
 __device__ __forceinline__ void pack_four(const WidePack &wp, int row, int j0, int D,
                                           const float (&s)[4])
 {
@@ -96,31 +100,46 @@ __device__ __forceinline__ void pack_four(const WidePack &wp, int row, int j0, i
     }
     // four columns of one W1 row inside one 32-column block, 4-aligned
     if (o >= 0 && k + 3 < wp.in && (k & 31) <= 28 && (k & 3) == 0) {
-        const size_t off = wide_w1_offset(o, k, BF ? 2 : 4);
-        if constexpr (BF) {
+        const size_t at = wide_w1_offset(o, k);
+        if constexpr (KIND == WIDE_BF16) {
             const uint32_t lo = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)s[0]) |
                                 ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)s[1]) << 16);
             const uint32_t hi = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)s[2]) |
                                 ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)s[3]) << 16);
-            *reinterpret_cast<uint2 *>(dst + off) = make_uint2(lo, hi);
+            *reinterpret_cast<uint2 *>(dst + at * 2) = make_uint2(lo, hi);
+        } else if constexpr (KIND == WIDE_F16X2) {
+            halfx4 hi, lo;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const SplitF16 p = split_f16(s[e], wp.wexp);
+                hi[e] = p.hi;
+                lo[e] = p.lo;
+            }
+            *reinterpret_cast<halfx4 *>(dst + at * 2) = lo;
+            *reinterpret_cast<halfx4 *>(dst + ((size_t)256 * wp.Kp + at) * 2) = hi;
         } else {
-            *reinterpret_cast<float4 *>(dst + off) = make_float4(s[0], s[1], s[2], s[3]);
+            *reinterpret_cast<float4 *>(dst + at * 4) = make_float4(s[0], s[1], s[2], s[3]);
         }
         return;
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         if (j0 + e >= D) break;
-        bool f32;
-        const size_t off = wide_pack_offset(wp, j0 + e, &f32);
-        if (BF && !f32) *reinterpret_cast<uint16_t *>(dst + off) = __builtin_bit_cast(uint16_t, (__bf16)s[e]);
-        else *reinterpret_cast<float *>(dst + off) = s[e];
+        wide_store(wp, dst, j0 + e, s[e]);
     }
+}
+
+// The exponent of an explosion spark's packed row (its weights lie in the box).
+__device__ __forceinline__ void pack_row_exp(const WidePack &wp, int row)
+{
+    int32_t *t = wide_row_exp(wp.Wp + (size_t)row * wp.pr, wp.Kp);
+    t[0] = wp.wexp;
+    t[1] = 0;
 }
 
 // SE null: the FP32 rows are not stored (the packed rows are the only copy the
 // fitness needs; later steps regenerate the sparks they read).
-template <int PACK>   // 0: no packing, 1: FP32 packed rows, 2: BF16
+template <int PACK>   // -1: no packing, else the WideKind of the packed rows
 __device__ __forceinline__ void explode_body(const float *__restrict__ F, const float *__restrict__ A,
                                              float *__restrict__ SE, int lam, int rows, int D,
                                              int Dp, uint2 key, Box box,
@@ -144,8 +163,10 @@ __device__ __forceinline__ void explode_body(const float *__restrict__ F, const 
         explosion_chunk(x, amp, key, chunk, (uint32_t)row, tn, box, plo, phi, D, s);
         if (SE)
             reinterpret_cast<float4 *>(SE + (size_t)row * Dp)[chunk] = make_float4(s[0], s[1], s[2], s[3]);
-        if constexpr (PACK != 0)
-            if (4 * chunk < D) pack_four<PACK == 2>(wp, row, 4 * chunk, D, s);
+        if constexpr (PACK >= 0)
+            if (4 * chunk < D) pack_four<PACK>(wp, row, 4 * chunk, D, s);
+        if constexpr (PACK == WIDE_F16X2)
+            if (chunk == 0) pack_row_exp(wp, row);
     }
 }
 
@@ -173,7 +194,7 @@ __global__ __launch_bounds__(TPB) void k_explode_group(GroupTable t)
     const DevState jd = t.job[j]->d;
     const Shape &s = js;
     const DevState &d = jd;
-    explode_body<0>(d.F, d.A, d.SE, s.lam, s.BN * s.lam, s.D, s.Dp, s.key, s.box, d.ctrl, s.N,
+    explode_body<-1>(d.F, d.A, d.SE, s.lam, s.BN * s.lam, s.D, s.Dp, s.key, s.box, d.ctrl, s.N,
                     s.map_range ? d.lo : nullptr, s.map_range ? d.hi : nullptr, WidePack{},
                     gb);
 }
@@ -182,14 +203,14 @@ __global__ __launch_bounds__(TPB) void k_explode_group(GroupTable t)
 // rows' own K-blocked order (the FP32 rows are not stored).  x-blocks below
 // `units`: a wavefront produces 16 rows x 32 columns of one K block of W1aug (b1
 // is column `in`), 8 consecutive columns per lane, and writes them as one
-// contiguous 1 KiB (BF16) or 2 KiB (FP32) segment; rows past the hidden width
+// contiguous segment of 1 KiB (BF16; FP16 parts: one of each plane) or 2 KiB (FP32); rows past the hidden width
 // and the zero columns past `in` are left to the initial zeroing except inside a
 // written segment.  The x-blocks from `units` on take the W2 and b2
 // coordinates, four per thread, placed one by one.  Values are those of
 // explosion_chunk, as in k_explode.
 constexpr int XP_ROWS = 64;   // W1aug rows per block (16 per wavefront)
 
-template <bool BF>
+template <int KIND>
 __global__ __launch_bounds__(TPB) void k_explode_packed(const float *__restrict__ F,
                                                         const float *__restrict__ A, int lam,
                                                         int rows, int D, int Dp, uint2 key, Box box,
@@ -217,7 +238,8 @@ __global__ __launch_bounds__(TPB) void k_explode_packed(const float *__restrict_
             const int o = ob * XP_ROWS + wave * 16 + (lane >> 2);
             const int k0 = kb * 32 + 8 * (lane & 3);
             if (o >= wp.hid) continue;
-            char *p = dst + wide_w1_offset(o, k0, BF ? 2 : 4);
+            char *p = dst + wide_w1_offset(o, k0) * (KIND == WIDE_F32 ? 4 : 2);
+            char *ph = p + (size_t)512 * wp.Kp;   // FP16 parts: p in the lo plane, ph in the hi plane
             if (aligned && k0 + 8 <= wp.in) {
                 float v[8];
                 const int c0 = (wp.woff1 + o * wp.in + k0) >> 2;
@@ -230,13 +252,23 @@ __global__ __launch_bounds__(TPB) void k_explode_packed(const float *__restrict_
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[4 * h + e] = s4[e];
                 }
-                if constexpr (BF) {
+                if constexpr (KIND == WIDE_BF16) {
                     uint32_t h[4];
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         h[e] = (uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * e]) |
                                ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * e + 1]) << 16);
                     *reinterpret_cast<uint4 *>(p) = make_uint4(h[0], h[1], h[2], h[3]);
+                } else if constexpr (KIND == WIDE_F16X2) {
+                    halfx8 hi, lo;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const SplitF16 sp = split_f16(v[e], wp.wexp);
+                        hi[e] = sp.hi;
+                        lo[e] = sp.lo;
+                    }
+                    *reinterpret_cast<halfx8 *>(p) = lo;
+                    *reinterpret_cast<halfx8 *>(ph) = hi;
                 } else {
                     reinterpret_cast<float4 *>(p)[0] = make_float4(v[0], v[1], v[2], v[3]);
                     reinterpret_cast<float4 *>(p)[1] = make_float4(v[4], v[5], v[6], v[7]);
@@ -261,16 +293,23 @@ __global__ __launch_bounds__(TPB) void k_explode_packed(const float *__restrict_
                         const int q = j & 3;
                         val = q == 0 ? s4[0] : q == 1 ? s4[1] : q == 2 ? s4[2] : s4[3];
                     }
-                    if constexpr (BF)
+                    if constexpr (KIND == WIDE_BF16) {
                         reinterpret_cast<uint16_t *>(p)[e] = __builtin_bit_cast(uint16_t, (__bf16)val);
-                    else
+                    } else if constexpr (KIND == WIDE_F16X2) {
+                        const SplitF16 sp = split_f16(val, wp.wexp);
+                        reinterpret_cast<_Float16 *>(p)[e] = sp.lo;
+                        reinterpret_cast<_Float16 *>(ph)[e] = sp.hi;
+                    } else {
                         reinterpret_cast<float *>(p)[e] = val;
+                    }
                 }
             }
         } else {
             // W2 and b2: chunk c covers coordinates 4c..4c+3; those below woff2 (b1)
             // belong to the W1aug blocks
             const int c = (woff2 >> 2) + ((int)blockIdx.x - units) * TPB + threadIdx.x;
+            if constexpr (KIND == WIDE_F16X2)
+                if (c == (woff2 >> 2)) pack_row_exp(wp, row);
             if (4 * c >= D) continue;
             const float4 x4 = xrow[c];
             const float x[4] = {x4.x, x4.y, x4.z, x4.w};
@@ -280,11 +319,7 @@ __global__ __launch_bounds__(TPB) void k_explode_packed(const float *__restrict_
             for (int e = 0; e < 4; ++e) {
                 const int j = 4 * c + e;
                 if (j < woff2 || j >= D) continue;
-                bool f32;
-                const size_t off = wide_pack_offset(wp, j, &f32);
-                const float val = e == 0 ? s4[0] : e == 1 ? s4[1] : e == 2 ? s4[2] : s4[3];
-                if (BF && !f32) *reinterpret_cast<uint16_t *>(dst + off) = __builtin_bit_cast(uint16_t, (__bf16)val);
-                else *reinterpret_cast<float *>(dst + off) = val;
+                wide_store(wp, dst, j, e == 0 ? s4[0] : e == 1 ? s4[1] : e == 2 ? s4[2] : s4[3]);
             }
         }
     }
@@ -355,17 +390,19 @@ hipError_t launch_explode(const Shape &s, const DevState &d, hipStream_t st, con
         const int ry = (rows + rpb - 1) / rpb;
         const dim3 grid((unsigned)bx, ry < MAX_GRID_Y ? ry : MAX_GRID_Y);
         const float *lo = s.map_range ? d.lo : nullptr, *hi = s.map_range ? d.hi : nullptr;
-        if (wp->bf16)
-            hipLaunchKernelGGL(k_explode_packed<true>, grid, dim3(TPB), 0, st, d.F, d.A, s.lam, rows,
-                               s.D, s.Dp, s.key, s.box, d.ctrl, s.N, lo, hi, *wp, units);
-        else
-            hipLaunchKernelGGL(k_explode_packed<false>, grid, dim3(TPB), 0, st, d.F, d.A, s.lam, rows,
-                               s.D, s.Dp, s.key, s.box, d.ctrl, s.N, lo, hi, *wp, units);
+        auto *k = wp->kind == WIDE_BF16    ? &k_explode_packed<WIDE_BF16>
+                  : wp->kind == WIDE_F16X2 ? &k_explode_packed<WIDE_F16X2>
+                                           : &k_explode_packed<WIDE_F32>;
+        hipLaunchKernelGGL(k, grid, dim3(TPB), 0, st, d.F, d.A, s.lam, rows, s.D, s.Dp, s.key, s.box, d.ctrl,
+                           s.N, lo, hi, *wp, units);
         return hipGetLastError();
     }
     const WidePack none{};
     const WidePack &w = wp ? *wp : none;
-    auto *k = !wp ? &k_explode<0> : wp->bf16 ? &k_explode<2> : &k_explode<1>;
+    auto *k = !wp                      ? &k_explode<-1>
+              : wp->kind == WIDE_BF16  ? &k_explode<WIDE_BF16>
+              : wp->kind == WIDE_F16X2 ? &k_explode<WIDE_F16X2>
+                                       : &k_explode<WIDE_F32>;
     hipLaunchKernelGGL(k, explode_grid(s), dim3(TPB), 0, st, d.F, d.A,
                        write_se || !wp ? d.SE : nullptr, s.lam, rows,
                        s.D, s.Dp, s.key, s.box, d.ctrl, s.N, s.map_range ? d.lo : nullptr,
