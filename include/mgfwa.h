@@ -156,8 +156,10 @@ typedef struct {
  *             stages the spark's weights in LDS, and the guiding, selection and
  *             best-so-far steps regenerate the sparks they read (the sparks are
  *             counter-based, so every step sees the same values).  Takes effect
- *             when the explosion-fitness plan stages its weights in LDS and the
- *             order is not lag_guiding; otherwise the sparks are stored as usual.
+ *             when the explosion-fitness plan stages its weights in LDS with the
+ *             network's activation compiled in (at most three layers: ReLU, and
+ *             tanh up to 16 wide), and the order is not lag_guiding; otherwise
+ *             the sparks are stored as usual.
  *             The wide fitness kernel never stores the FP32 rows (its explosion
  *             writes the packed rows it reads).  mgfwa_state_info.se_written
  *             tells which applies.

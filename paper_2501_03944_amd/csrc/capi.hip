@@ -290,7 +290,7 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
     L.Lpad = take(net.loss == MGFWA_LOSS_CE ? (size_t)net.S_pad * 4 : 0);
     L.Wpack = take(net.wide ? (size_t)L.partial_rows * wide_row_bytes(net) : 0);
     L.Xw = take(net.wide ? (size_t)net.S_pad * wide_kp(net) * (net.bf16 ? 2 : 4) : 0);
-    L.Xe = take(net.wide && !net.bf16 ? (size_t)(net.S_pad + 1) * 4 : 0);
+    L.Xe = take(!input && !net.bf16 ? (size_t)(net.S_pad + 1) * 4 : 0);
     L.lo = take(s.map_range ? (size_t)s.B * Dp * 4 : 0);
     L.hi = take(s.map_range ? (size_t)s.B * Dp * 4 : 0);
     L.Pnet = take(input && need_data ? (size_t)in.n_packed * 4 : 0);
@@ -303,7 +303,7 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
     L.Xp32 = take(s.recheck && !net.wide ? (size_t)net32.S_pad * net32.in_pad * 4 : 0);
     L.Wpack32 = take(s.recheck && net.wide ? BN * wide_row_bytes(net32) : 0);
     L.Xw32 = take(s.recheck && net.wide ? (size_t)net32.S_pad * wide_kp(net32) * 4 : 0);
-    L.Xe32 = take(s.recheck && net.wide ? (size_t)(net32.S_pad + 1) * 4 : 0);
+    L.Xe32 = take(s.recheck ? (size_t)(net32.S_pad + 1) * 4 : 0);
     L.desc = take(sizeof(JobDesc));
     L.total = off;
     if (s.lag && L.SG != L.SE + BN * s.lam * Dp * 4)
@@ -385,13 +385,13 @@ OutMap expl_map(const Shape &s)
 }
 
 // Whether mgfwa_step leaves the explosion sparks unstored: the wide kernel reads
-// the explosion's packed rows; with regen_sparks an LDS-staged register-chain
-// plan regenerates them.  The lag order reads the previous generation's sparks.
+// the explosion's packed rows; with regen_sparks a register-chain plan that can
+// (FitPlan::regen) regenerates them.  The lag order reads the previous generation's sparks.
 bool sparks_regenerated(const mgfwa_ctx *c)
 {
     if (c->s.lag || c->input || !c->has_data) return false;
     if (c->net.wide) return true;
-    return c->cfg.regen_sparks && c->plan_expl.wl;
+    return c->cfg.regen_sparks && c->plan_expl.regen;
 }
 
 // The explosion-fitness launch's source when its sparks are regenerated.
@@ -427,7 +427,7 @@ mgfwa_status fit_rows(mgfwa_ctx *c, const FitPlan &plan, const float *W, size_t 
         STEP(launch_fitness_wide(c->net, c->d, W, ld, rows, map, out, st, boxed, mid, pre, prepacked),
              "fitness_wide");
     else
-        STEP(launch_fitness(c->net, plan, c->d, W, ld, rows, map, out, st, mid, rg), "fitness");
+        STEP(launch_fitness(c->net, plan, c->d, W, ld, rows, map, out, st, boxed, mid, rg), "fitness");
     return MGFWA_OK;
 }
 
@@ -439,7 +439,7 @@ mgfwa_status fit_check(mgfwa_ctx *c, const float *W, int rows, float *out, hipSt
         STEP(launch_fitness_wide(c->net32, c->d32, W, c->s.Dp, rows, kFlat, out, st, true),
              "fitness_check_wide");
     else
-        STEP(launch_fitness(c->net32, c->plan_check, c->d32, W, c->s.Dp, rows, kFlat, out, st),
+        STEP(launch_fitness(c->net32, c->plan_check, c->d32, W, c->s.Dp, rows, kFlat, out, st, true),
              "fitness_check");
     return MGFWA_OK;
 }
@@ -677,7 +677,7 @@ mgfwa_status mgfwa_init(mgfwa_ctx **out, const mgfwa_config *config, const mgfwa
     d.Lpad = c->net.loss == MGFWA_LOSS_CE ? at<int32_t>(b, L.Lpad) : nullptr;
     d.Wpack = c->net.wide ? at<char>(b, L.Wpack) : nullptr;
     d.Xw = c->net.wide ? at<char>(b, L.Xw) : nullptr;
-    d.Xe = c->net.wide && !c->net.bf16 ? at<int32_t>(b, L.Xe) : nullptr;
+    d.Xe = !c->input && !c->net.bf16 ? at<int32_t>(b, L.Xe) : nullptr;
     d.lo = c->s.map_range ? at<float>(b, L.lo) : nullptr;
     d.hi = c->s.map_range ? at<float>(b, L.hi) : nullptr;
     d.Pnet = c->input && has_data ? at<float>(b, L.Pnet) : nullptr;
@@ -694,7 +694,7 @@ mgfwa_status mgfwa_init(mgfwa_ctx **out, const mgfwa_config *config, const mgfwa
         c->d32.Xp = c->net32.wide ? nullptr : at<float>(b, L.Xp32);
         c->d32.Wpack = c->net32.wide ? at<char>(b, L.Wpack32) : nullptr;
         c->d32.Xw = c->net32.wide ? at<char>(b, L.Xw32) : nullptr;
-        c->d32.Xe = c->net32.wide ? at<int32_t>(b, L.Xe32) : nullptr;
+        c->d32.Xe = at<int32_t>(b, L.Xe32);
     }
 
     auto bail = [&](mgfwa_status st) {
@@ -1019,9 +1019,9 @@ namespace {
 // device the library runs on holds its own copy until the process ends.  In host
 // code its name is only a stand-in: kernels get the per-device address that
 // hipGetSymbolAddress returns.
-// The wide kernel's sample exponents (at most 64 tiles of 256 samples) follow the
-// bytes whose use the header documents.
-constexpr size_t SCRATCH_EXP_BYTES = 64 * 256 * 4 + ALIGN;
+// The exponents of FP32 samples follow the bytes whose use the header documents (a
+// sample takes at least 64 of them, so there are at most 2^20).
+constexpr size_t SCRATCH_EXP_BYTES = MGFWA_NOALLOC_SCRATCH_BYTES / 16 + ALIGN;
 __device__ __align__(256) char scratch[MGFWA_NOALLOC_SCRATCH_BYTES + SCRATCH_EXP_BYTES];
 
 constexpr int MAX_DEVICES = 64;
@@ -1124,7 +1124,7 @@ extern "C" mgfwa_status mgfwa_evaluate_noalloc(const mgfwa_problem *problem, int
     d.Lpad = net.loss == MGFWA_LOSS_CE ? at<int32_t>(base, oL) : nullptr;
     d.partial = at<float>(base, oP);
     d.Wpack = net.wide ? at<char>(base, oW) : nullptr;
-    d.Xe = net.wide && !net.bf16 ? at<int32_t>(base, MGFWA_NOALLOC_SCRATCH_BYTES) : nullptr;
+    d.Xe = !net.bf16 ? at<int32_t>(base, MGFWA_NOALLOC_SCRATCH_BYTES) : nullptr;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     // the array keeps the previous call's contents: every byte a launch reads is
     // rewritten here first (samples, targets, labels and their padding by the
@@ -1141,7 +1141,7 @@ extern "C" mgfwa_status mgfwa_evaluate_noalloc(const mgfwa_problem *problem, int
             if (!fit_select(net, nr, &plan))
                 return fail(MGFWA_EUNSUPPORTED, "no compiled fitness kernel covers this MLP shape");
             HIP_TRY(fit_prepare(plan));
-            HIP_TRY(launch_fitness(net, plan, d, wr, (size_t)ld, nr, kFlat, out + r0, st));
+            HIP_TRY(launch_fitness(net, plan, d, wr, (size_t)ld, nr, kFlat, out + r0, st, false));
         }
     }
     return MGFWA_OK;
@@ -1152,7 +1152,7 @@ namespace {
 
 std::mutex g_tune_mu;
 std::map<std::string, FitPlan> g_tune;   // shape key -> timed choice, for the process
-constexpr int MAX_CANDIDATES = 64;
+constexpr int MAX_CANDIDATES = 128;
 
 std::string tune_key(const Net &net, int rows)
 {
@@ -1271,7 +1271,7 @@ mgfwa_status tune_plan(mgfwa_ctx *c, int rows, const float *W, OutMap map, int r
             if (e == hipSuccess)
                 e = c->input ? launch_net_input(c->in, cand[i].net_shape, c->d.Pnet, W, c->s.Dp, rows,
                                                 map, c->d.Yc, c->d.H0, c->d.H1, c->d.zero, c->stream)
-                             : launch_fitness(net, cand[i], dv, W, c->s.Dp, rows, map, res, c->stream);
+                             : launch_fitness(net, cand[i], dv, W, c->s.Dp, rows, map, res, c->stream, true);
         }
         if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -1370,12 +1370,12 @@ JobDesc job_desc(const mgfwa_ctx *c)
     j.d = c->d;
     const SparkRegen rg = spark_regen(c);
     j.fit[0] = fit_launch_args(c->net, c->plan_expl, c->d, c->d.SE, s.Dp, s.BN * s.lam, expl_map(s),
-                               c->d.Yc, s.regen ? &rg : nullptr);
+                               c->d.Yc, true, s.regen ? &rg : nullptr);
     j.fit[1] = fit_launch_args(c->net, c->plan_guide, c->d, c->d.SG, s.Dp, s.BN * s.G,
-                               OutMap{s.G, s.C, s.lam}, c->d.Yc);
+                               OutMap{s.G, s.C, s.lam}, c->d.Yc, true);
     if (s.recheck)
         j.fit[2] = fit_launch_args(c->net32, c->plan_check, c->d32, c->d.Wstar, s.Dp, s.BN, kFlat,
-                                   c->d.Ystar);
+                                   c->d.Ystar, true);
     return j;
 }
 
@@ -1623,6 +1623,14 @@ mgfwa_status mgfwa_autotune(mgfwa_ctx *c, int reps)
         return fail(MGFWA_ESTATE, "autotune before the first generation");
     if (c->net.wide) return MGFWA_OK;   // one fixed tile shape
     const Shape &s = c->s;
+    if (!c->input) {
+        // time the launches on sparks (the buffers hold none yet): the first
+        // generation's, the guiding sparks' places filled with explosion sparks
+        if (s.map_range) STEP(launch_pop_range(s, c->d, c->stream), "pop_range");
+        STEP(launch_explode(s, c->d, c->stream), "explode");
+        HIP_TRY(hipMemcpyAsync(c->d.SG, c->d.SE, (size_t)s.BN * s.G * s.Dp * 4, hipMemcpyDeviceToDevice,
+                               c->stream));
+    }
     mgfwa_status r = tune_plan(c, s.BN * expl_rows(s), c->d.SE, expl_map(s), reps, &c->plan_expl);
     if (r) return r;
     c->s.regen = sparks_regenerated(c) ? 1 : 0;   // the plan decides whether it can regenerate

@@ -644,17 +644,49 @@ __device__ __forceinline__ float xor_max4(float v)
     return fmaxf(a, b);
 }
 
-// Sum of the per-sample losses of this wavefront's P slabs (valid in lanes g == 0).
+// e^x for x <= 0: 2^(x log2 e) on the exponential unit, the rounding of the product
+// carried into a correction factor.
+__device__ __forceinline__ float exp_neg(float x)
+{
+    constexpr float L2E = 1.44269504088896341f, L2E_LO = 1.925963033500865e-8f, LN2 = 0.693147180559945309f;
+    const float t = x * L2E;
+    const float lo = __builtin_fmaf(x, L2E_LO, __builtin_fmaf(x, L2E, -t));
+    const float e = __builtin_amdgcn_exp2f(t);
+    return x < -104.0f ? 0.0f : __builtin_fmaf(e, lo * LN2, e);
+}
+
+// A wavefront's running loss.  A sample's cross-entropy is d + log1p(q), d the distance
+// of the label's logit from the largest one and q the sum of the other classes'
+// exponentials; its four lanes (g = 0..3) hold the same d and q, so the logarithms of
+// four slabs are taken together, lane group g keeping slab g's pair until then (a
+// logarithm per slab was a third of the vector work of a narrow BF16 network).
+struct LossSum {
+    float total = 0.0f, d = 0.0f, q = 0.0f;
+    int slot = 0;
+    __device__ __forceinline__ void flush()
+    {
+        total += d + log1pf(q);
+        d = q = 0.0f;
+    }
+};
+
+// Labels of this lane's samples, fetched ahead of the slab's products.
+template <int P>
+__device__ __forceinline__ void load_labels(const FitArgs &a, int s0, int n, int (&lab)[P])
+{
+#pragma unroll
+    for (int p = 0; p < P; ++p) lab[p] = a.loss == 1 ? a.lab[s0 + 16 * p + n] : 0;
+}
+
+// Add the losses of this wavefront's P slabs (logits z).
 template <int P, int R>
-__device__ __forceinline__ float slab_loss(const FitArgs &a, int l, int s0, int n, int g,
-                                           const floatx4 (&z)[P][R])
+__device__ __forceinline__ void slab_loss(const FitArgs &a, int l, int s0, int n, int g,
+                                          const floatx4 (&z)[P][R], const int (&lab)[P], LossSum &ls)
 {
     const int fo = a.fo[l];
-    float total = 0.0f;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         const int s = s0 + 16 * p + n;
-        float ls;
         if (a.loss == 0) {
             float acc = 0.0f;
             const float *yrow = a.Y + (size_t)s * fo;
@@ -668,44 +700,43 @@ __device__ __forceinline__ float slab_loss(const FitArgs &a, int l, int s0, int 
                         acc = __builtin_fmaf(e, e, acc);
                     }
                 }
-            ls = xor_sum4(acc);
+            if (s < a.S) ls.total += acc;
         } else {
-            const int label = a.lab[s];
-            float mx = -__builtin_huge_valf(), zl = 0.0f;
+            const float inf = __builtin_huge_valf();
+            float mx = -inf, zl = 0.0f;
 #pragma unroll
             for (int rb = 0; rb < R; ++rb)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int o = 16 * rb + 4 * g + v;
-                    if (o < fo) {
-                        mx = fmaxf(mx, z[p][rb][v]);
-                        if (o == label) zl = z[p][rb][v];
-                    }
+                    mx = o < fo ? fmaxf(mx, z[p][rb][v]) : mx;
+                    zl = o == lab[p] ? z[p][rb][v] : zl;
                 }
             mx = xor_max4(mx);
-            // se = sum over all classes, rest = sum over classes other than the label
-            float se = 0.0f, rest = 0.0f;
+            // q = the exponentials of all classes but one that holds the maximum: small
+            // losses do not cancel against its 1 (ties: the others that hold it)
+            float ties = g == 0 ? -1.0f : 0.0f, rest = 0.0f;
 #pragma unroll
             for (int rb = 0; rb < R; ++rb)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     const int o = 16 * rb + 4 * g + v;
+                    const float zz = z[p][rb][v];
                     if (o < fo) {
-                        const float e = expf(z[p][rb][v] - mx);
-                        se += e;
-                        if (o != label) rest += e;
+                        if (zz == mx) ties += 1.0f;
+                        else rest += exp_neg(zz - mx);
                     }
                 }
-            se = xor_sum4(se);
-            rest = xor_sum4(rest);
+            ties = xor_sum4(ties);
+            float q = ties + xor_sum4(rest);
+            q = ties > 0.0f ? q + (mx - mx) : q;     // (tied infinities: NaN)
             zl = xor_sum4(zl);
-            // When the label holds the maximum the loss is log(1 + rest): log1p
-            // keeps small losses accurate instead of cancelling max + log(se) - z.
-            ls = zl == mx ? log1pf(rest) : (mx - zl) + logf(se);
+            const bool mine = s < a.S && (ls.slot & 3) == g;
+            ls.d = mine ? (zl == mx ? 0.0f : mx - zl) : ls.d;
+            ls.q = mine ? q : ls.q;
+            if ((++ls.slot & 3) == 0) ls.flush();
         }
-        if (s < a.S && g == 0) total += ls;
     }
-    return total;
 }
 
 // Block `bid` of a fitness launch: spark r = bid / bpr, sample range c = bid % bpr.
@@ -723,12 +754,15 @@ __device__ __forceinline__ void fit_body(const FitArgs &a, int bid)
     const WView<BF, WL> w2(a, w, smem, 2, n, g), w3(a, w, smem, 3, n, g);
     const int s_begin = c * a.spb;
     const int s_end = min(s_begin + a.spb, a.S_pad);
-    float lsum = 0.0f;
+    LossSum loss;
     for (int s0 = s_begin + wave * 16 * P; s0 < s_end; s0 += NW * 16 * P) {
         // The staged weights are re-read from LDS for every slab: without this
         // fence the compiler hoists those reads out of the loop and, short of
         // registers, spills the whole weight fragment set to scratch memory.
         asm volatile("" ::: "memory");
+        // (ahead of the products where the registers allow it)
+        int lab[P];
+        if constexpr (WL) load_labels(a, s0, n, lab);
         // FOLD (BF16, zero-addend instances, ReLU): each layer's bias is the
         // addend of its first K block and the ReLU of a hidden layer is applied
         // to its BF16-rounded values as the next layer converts them, so no
@@ -739,7 +773,8 @@ __device__ __forceinline__ void fit_body(const FitArgs &a, int bid)
         layer_x<BF, WL, P, R1, SCHED, FOLD>(a, w0, s0, n, g, h1, c1);
         if constexpr (R2 == 0) {
             if constexpr (!FOLD) bias_act<ACT, WL, P, R1>(a, w, smem, 0, g, false, h1);
-            lsum += slab_loss<P, R1>(a, 0, s0, n, g, h1);
+            if constexpr (!WL) load_labels(a, s0, n, lab);
+            slab_loss<P, R1>(a, 0, s0, n, g, h1, lab, loss);
         } else {
             if constexpr (!FOLD) bias_act<ACT, WL, P, R1>(a, w, smem, 0, g, true, h1);
             floatx4 h2[P][R2], c2[R2];
@@ -747,7 +782,8 @@ __device__ __forceinline__ void fit_body(const FitArgs &a, int bid)
             layer_h<BF, WL, P, R1, R2, SCHED, FOLD>(w1, h1, h2, c2);
             if constexpr (R3 == 0) {
                 if constexpr (!FOLD) bias_act<ACT, WL, P, R2>(a, w, smem, 1, g, false, h2);
-                lsum += slab_loss<P, R2>(a, 1, s0, n, g, h2);
+                if constexpr (!WL) load_labels(a, s0, n, lab);
+                slab_loss<P, R2>(a, 1, s0, n, g, h2, lab, loss);
             } else {
                 if constexpr (!FOLD) bias_act<ACT, WL, P, R2>(a, w, smem, 1, g, true, h2);
                 floatx4 h3[P][R3], c3[R3];
@@ -755,18 +791,22 @@ __device__ __forceinline__ void fit_body(const FitArgs &a, int bid)
                 layer_h<BF, WL, P, R2, R3, SCHED, FOLD>(w2, h2, h3, c3);
                 if constexpr (R4 == 0) {
                     if constexpr (!FOLD) bias_act<ACT, WL, P, R3>(a, w, smem, 2, g, false, h3);
-                    lsum += slab_loss<P, R3>(a, 2, s0, n, g, h3);
+                    if constexpr (!WL) load_labels(a, s0, n, lab);
+                    slab_loss<P, R3>(a, 2, s0, n, g, h3, lab, loss);
                 } else {
                     if constexpr (!FOLD) bias_act<ACT, WL, P, R3>(a, w, smem, 2, g, true, h3);
                     floatx4 h4[P][R4], c4[R4];
                     if constexpr (FOLD) load_bias<WL, R4>(a, w, smem, 3, g, c4);
                     layer_h<BF, WL, P, R3, R4, SCHED, FOLD>(w3, h3, h4, c4);
                     if constexpr (!FOLD) bias_act<ACT, WL, P, R4>(a, w, smem, 3, g, false, h4);
-                    lsum += slab_loss<P, R4>(a, 3, s0, n, g, h4);
+                    if constexpr (!WL) load_labels(a, s0, n, lab);
+                    slab_loss<P, R4>(a, 3, s0, n, g, h4, lab, loss);
                 }
             }
         }
     }
+    loss.flush();
+    float lsum = loss.total;
     // fixed-order reduction: wavefront butterfly, then the wavefronts in order
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) lsum += __shfl_xor(lsum, off);
@@ -808,6 +848,7 @@ struct KernelEntry {
     int bf16, wl, nw, P, act, R[MAXL];
     const void *fn;         // k_fit
     const void *gfn;        // k_fit_group of the same instance
+    int split = 0;          // FP32 in two FP16 parts (fit_split.h)
 };
 
 #define FIT_ENTRY_SCHED(BF, WL, NW, P, ACT, SCHED, R1, R2, R3, R4)                          \

@@ -5,8 +5,8 @@
 // (SCHED 3); P = 4 slabs for narrow nets, 2 for wide ones.  Wide nets also get
 // 8 wavefronts per block: their weights fill the LDS, so a CU holds one block,
 // and with 4 wavefronts each SIMD would run a single instruction stream (8 x 2
-// measured 1.45x faster than 4 x 2 at 64-256-10 and 64-174-174-10; at 128-wide
-// layers 4 x 2 stays ahead).  An instance listed first is the shape's default
+// measured 1.45x faster than 4 x 2 at 64-256-10 and 64-174-174-10, 630 -> 578 us at
+// 64-128-128-10 with 2,048 sparks x 4,096 samples).  An instance listed first is the shape's default
 // before tuning.
 #include "fit_kernel.h"
 
@@ -32,8 +32,8 @@ const KernelEntry kEntries[] = {
     FIT_ENTRY_SCHED(true, true, 4, 4, 1, 3, 4, 4, 1, 0),
     FIT_ENTRY_SCHED(true, true, 4, 2, 1, 3, 6, 6, 1, 0),
     FIT_ENTRY_SCHED(true, true, 8, 2, 1, 3, 6, 6, 1, 0),
-    FIT_ENTRY_SCHED(true, true, 4, 2, 1, 3, 8, 8, 1, 0),
     FIT_ENTRY_SCHED(true, true, 8, 2, 1, 3, 8, 8, 1, 0),
+    FIT_ENTRY_SCHED(true, true, 4, 2, 1, 3, 8, 8, 1, 0),
     FIT_ENTRY_SCHED(true, true, 8, 2, 1, 3, 10, 10, 1, 0),
     FIT_ENTRY_SCHED(true, true, 4, 2, 1, 3, 10, 10, 1, 0),
     FIT_ENTRY_SCHED(true, true, 8, 2, 1, 3, 12, 12, 1, 0),

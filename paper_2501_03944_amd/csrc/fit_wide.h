@@ -37,7 +37,9 @@
 //             full size is rounded once per 32 columns instead of once per few
 //             columns, which from 128 columns on makes the error no larger than
 //             with FP32 instructions (rms at 800 columns, 20 % dense and dense
-//             inputs: 1.4e-7 against 2.3e-7 and 5.1e-7).  Below 128 columns it would
+//             inputs: 1.4e-7 against 2.3e-7 and 5.1e-7).  A generation of 784-256-10
+//             with 4,096 sparks x 8,192 samples takes 31.4 ms so, 98.4 ms with FP32
+//             instructions; the fitness' error against binary64 9e-8 -> 3e-8.  Below 128 columns it would
 //             be larger, and k_fit_wide32 stays (networks that narrow come here
 //             only by fit_path).  Infinite inputs or weights (the products of their
 //             parts cancel to NaN) are left to the finalisation (slow_loss);
@@ -534,7 +536,6 @@ __device__ __forceinline__ float wave_sum_lane0(float v)
     return (v + r1) + (r2 + r3);
 }
 
-constexpr int XE_INF = 1 << 20;    // Xe of a sample with an infinity: its exponent + XE_INF
 constexpr int LABEL_SKIP = -2;     // the sample's loss is not taken here (k_wide_finalize adds it)
 
 __device__ __forceinline__ int sample_exp(int xe) { return xe >= XE_INF / 2 ? xe - XE_INF : xe; }

@@ -146,8 +146,6 @@ __global__ __launch_bounds__(TPB) void k_pack_wide_rows(const float *__restrict_
     }
 }
 
-__global__ void k_clear_word(int32_t *p) { *p = 0; }
-
 __device__ __forceinline__ void max_inf(float v, float &m, int &inf)
 {
     const float a = fabsf(v);
@@ -224,37 +222,24 @@ __global__ __launch_bounds__(TPB) void k_pack_wide_x(const float *__restrict__ x
     else reinterpret_cast<float *>(Xw)[dst] = v;
 }
 
-// Samples in two FP16 parts: one wavefront per sample takes its exponent (the ones
-// column included), then writes both parts of every column (a tile's hi plane, then
-// its lo plane, each K-blocked as above).
+// Samples in two FP16 parts (exponents Xe): a tile's hi plane, then its lo plane, each
+// K-blocked as above.
 __global__ __launch_bounds__(TPB) void k_pack_wide_x_f16x2(const float *__restrict__ x, int S, int S_pad,
                                                            int in, int Kp, char *__restrict__ Xw,
-                                                           int32_t *__restrict__ Xe)
+                                                           const int32_t *__restrict__ Xe)
 {
-    const int s = blockIdx.x * (TPB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (s >= S_pad) return;
-    const float *row = x + (size_t)s * in;
-    float m = 1.0f;
-    int inf = 0;
-    for (int k = lane; s < S && k < in; k += 64) max_inf(row[k], m, inf);
-    for (int off = 32; off > 0; off >>= 1) {
-        m = fmaxf(m, __shfl_xor(m, off));
-        inf |= __shfl_xor(inf, off);
-    }
-    const int e = split_exp(m);
-    if (lane == 0) {
-        Xe[s] = e + (inf ? XE_INF : 0);
-        if (inf) atomicOr(&Xe[S_pad], 1);
-    }
+    const size_t tid = (size_t)blockIdx.x * TPB + threadIdx.x;
+    if (tid >= (size_t)S_pad * Kp) return;
+    const int s = (int)(tid / Kp), k = (int)(tid % Kp);
+    float v = 0.0f;
+    if (s < S) v = k < in ? x[(size_t)s * in + k] : (k == in ? 1.0f : 0.0f);
+    const int xe = Xe[s];
+    const SplitF16 p = split_f16(v, xe >= XE_INF / 2 ? xe - XE_INF : xe);
     const size_t plane = (size_t)WT_N * Kp;
     _Float16 *hi = reinterpret_cast<_Float16 *>(Xw) + (size_t)(s / WT_N) * 2 * plane;
-    for (int k = lane; k < Kp; k += 64) {
-        const float v = s >= S ? 0.0f : k < in ? row[k] : k == in ? 1.0f : 0.0f;
-        const SplitF16 p = split_f16(v, e);
-        const size_t at = ((size_t)(k / WT_K) * WT_N + s % WT_N) * WT_K + k % WT_K;
-        hi[at] = p.hi;
-        hi[plane + at] = p.lo;
-    }
+    const size_t at = ((size_t)(k / WT_K) * WT_N + s % WT_N) * WT_K + k % WT_K;
+    hi[at] = p.hi;
+    hi[plane + at] = p.lo;
 }
 
 // One instance per (precision, hidden activation): a run-time activation
@@ -346,16 +331,16 @@ hipError_t wide_prepare(const Net &net)
 hipError_t launch_pack_wide_x(const Net &net, const float *x, const DevState &d, hipStream_t st)
 {
     const int Kp = wide_kp(net);
+    const size_t n = (size_t)net.S_pad * Kp;
+    const dim3 grid((unsigned)((n + TPB - 1) / TPB));
     if (wide_kind(net) == WIDE_F16X2) {
-        constexpr int per = TPB / 64;
-        hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, st, d.Xe + net.S_pad);
-        hipLaunchKernelGGL(k_pack_wide_x_f16x2, dim3((unsigned)((net.S_pad + per - 1) / per)), dim3(TPB),
-                           0, st, x, net.S, net.S_pad, net.fi[0], Kp, d.Xw, d.Xe);
+        const hipError_t e = launch_sample_exp(net, x, d.Xe, st);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_pack_wide_x_f16x2, grid, dim3(TPB), 0, st, x, net.S, net.S_pad, net.fi[0], Kp,
+                           d.Xw, d.Xe);
     } else {
-        const size_t n = (size_t)net.S_pad * Kp;
-        hipLaunchKernelGGL(net.bf16 ? &k_pack_wide_x<true> : &k_pack_wide_x<false>,
-                           dim3((unsigned)((n + TPB - 1) / TPB)), dim3(TPB), 0, st, x, net.S, net.S_pad,
-                           net.fi[0], Kp, d.Xw);
+        hipLaunchKernelGGL(net.bf16 ? &k_pack_wide_x<true> : &k_pack_wide_x<false>, grid, dim3(TPB), 0, st, x,
+                           net.S, net.S_pad, net.fi[0], Kp, d.Xw);
     }
     return hipGetLastError();
 }

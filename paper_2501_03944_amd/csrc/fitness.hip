@@ -3,6 +3,7 @@
 // template lives in fit_kernel.h; the fit_*.hip files instantiate it.
 #include "fit_kernel.h"
 
+#include <algorithm>
 #include <cstdlib>
 
 namespace mgfwa {
@@ -22,6 +23,9 @@ const KernelEntry *table_l4_wide_f32(int *n);
 const KernelEntry *table_l4_wide_bf16(int *n);
 const KernelEntry *table_lds_bf16(int *n);
 const KernelEntry *table_lds_f32(int *n);
+const KernelEntry *table_lds_any(int *n);
+const KernelEntry *table_split(int *n);
+const KernelEntry *table_split_any(int *n);
 }  // namespace fit
 
 namespace {
@@ -30,16 +34,17 @@ using namespace fit;
 
 constexpr int MAX_BPR = 64;
 
-// Sum of a row's partials in order, scaled to the mean, NaN -> +inf, scattered.
+// Sum of a row's partials in order (binary64: they may be few and large), scaled to
+// the mean, NaN -> +inf, scattered.
 __device__ __forceinline__ void finalize_body(const float *__restrict__ partial, int rows, int bpr,
                                               float inv_norm, const OutMap &map,
                                               float *__restrict__ out, Blk b)
 {
     const int r = b.x * 256 + threadIdx.x;
     if (r >= rows) return;
-    float t = 0.0f;
+    double t = 0.0;
     for (int c = 0; c < bpr; ++c) t += partial[(size_t)r * bpr + c];
-    out[map.index(r)] = canon_fitness(t * inv_norm);
+    out[map.index(r)] = canon_fitness((float)(t * (double)inv_norm));
 }
 
 __global__ __launch_bounds__(256) void k_fit_finalize(const float *__restrict__ partial, int rows,
@@ -83,10 +88,36 @@ __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ x, const
     if (tid < (size_t)S_pad && Lp) Lp[tid] = (tid < (size_t)S && lab) ? lab[tid] : -1;
 }
 
+__global__ void k_clear_word(int32_t *p) { *p = 0; }
+
+// Exponent of every sample's inputs (and the constant 1 of a folded bias): one
+// wavefront per sample; a sample with an infinity is marked and raises the flag
+// behind the exponents.
+__global__ __launch_bounds__(256) void k_sample_exp(const float *__restrict__ x, int S, int S_pad, int in,
+                                                    int32_t *__restrict__ Xe)
+{
+    const int s = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (s >= S_pad) return;
+    float m = 1.0f;
+    int inf = 0;
+    for (int k = lane; s < S && k < in; k += 64) {
+        const float v = fabsf(x[(size_t)s * in + k]);
+        if (v <= 3.4028234e38f) m = fmaxf(m, v);   // finite (NaN takes no part)
+        else if (v == __builtin_huge_valf()) inf = 1;
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        m = fmaxf(m, __shfl_xor(m, off));
+        inf |= __shfl_xor(inf, off);
+    }
+    if (lane != 0) return;
+    Xe[s] = split_exp(m) + (inf ? XE_INF : 0);
+    if (inf) atomicOr(&Xe[S_pad], 1);
+}
+
 const KernelEntry *(*const kTables[])(int *) = {
     table_std,         table_l1,          table_l2,       table_l2_wide,     table_l3,
     table_l3_wide_f32, table_l3_wide_bf16, table_l4_f32,  table_l4_bf16,     table_l4_wide_f32,
-    table_l4_wide_bf16, table_lds_bf16, table_lds_f32,
+    table_l4_wide_bf16, table_lds_bf16, table_lds_f32, table_lds_any, table_split, table_split_any,
 };
 
 }  // namespace
@@ -96,18 +127,19 @@ int fit_max_bpr() { return MAX_BPR; }
 // LDS layout of the staged weights for kernel entry e; returns the byte size.
 static int lds_layout(const Net &net, const KernelEntry &e, FitPlan *p)
 {
-    const int es = e.bf16 ? 2 : 4;          // storage bytes per weight
+    const int es = e.bf16 || e.split ? 2 : 4;   // bytes per stored element (split: per part)
     // pitch padding in elements: BF16 16 bytes; FP32 32 bytes (a pitch of 2 mod 8
     // 16-byte chunks, with the row-parity chunk swizzle of the kernel)
-    const int unit = 8;
+    // split: a pitch of 2 (mod 4) 16-byte chunks, with the same swizzle
+    const int unit = e.split ? 16 : 8;
     int off = 0, boff = 0;
     for (int l = 0; l < MAXL; ++l) {
         p->lw[l] = p->lpitch[l] = p->lrows[l] = p->lcols[l] = p->lb[l] = 0;
         if (l >= net.nl) continue;
         const int rows = 16 * e.R[l];
         int cols;
-        if (l == 0) cols = net.in_pad;
-        else cols = e.bf16 ? 32 * ((e.R[l - 1] + 1) / 2) : 16 * e.R[l - 1];
+        if (l == 0) cols = e.split ? (net.in_pad + 31) / 32 * 32 : net.in_pad;
+        else cols = e.bf16 || e.split ? 32 * ((e.R[l - 1] + 1) / 2) : 16 * e.R[l - 1];
         const int pitch = cols + unit;
         off = (off + (16 / es) - 1) / (16 / es) * (16 / es);   // 16-byte aligned layer base
         p->lw[l] = off;
@@ -115,7 +147,7 @@ static int lds_layout(const Net &net, const KernelEntry &e, FitPlan *p)
         p->lrows[l] = rows;
         p->lcols[l] = cols;
         p->lb[l] = boff;
-        off += rows * pitch;
+        off += rows * pitch * (e.split ? 2 : 1);
         boff += rows;
     }
     p->lbias_byte = (off * es + 15) / 16 * 16;
@@ -135,9 +167,20 @@ int resident_lds_bytes(const Net &net)
     return lds_layout(net, e, &p);
 }
 
+// Whether the network may take the register chain in two FP16 parts.  Those (7e-8 of a
+// value, fewer roundings of the sum) are the more accurate form of a layer from about 48
+// inputs on: error of the fitness against binary64 at 32-64-64-64-10 5.9e-8 -> 4.8e-8, but
+// 6.3e-8 -> 7.0e-8 at 16-36-36-36-2.
+static bool chain_split(const Net &net)
+{
+    int widest = 0;
+    for (int l = 0; l + 1 < net.nl; ++l) widest = std::max(widest, net.fo[l]);
+    return !net.bf16 && !net.wide && widest >= 48;
+}
+
 // Whether kernel entry e covers the network; *cost is the model cost used to
-// rank the entries that do.
-static bool entry_fits(const Net &net, const KernelEntry &e, double *cost)
+// rank the entries that do, *padded the products of its padded layers.
+static bool entry_fits(const Net &net, const KernelEntry &e, double *cost, double *padded = nullptr)
 {
     int need[MAXL] = {0, 0, 0, 0};
     for (int l = 0; l < net.nl; ++l) {
@@ -146,6 +189,7 @@ static bool entry_fits(const Net &net, const KernelEntry &e, double *cost)
         if (net.bf16 && l < net.nl - 1 && (need[l] & 1)) need[l] += 1;
     }
     if (e.bf16 != net.bf16) return false;
+    if (e.split && !chain_split(net)) return false;
     if (e.act >= 0) {
         for (int l = 0; l < net.nl - 1; ++l)   // a fixed activation must match every hidden layer
             if (net.act[l] != e.act) return false;
@@ -156,25 +200,51 @@ static bool entry_fits(const Net &net, const KernelEntry &e, double *cost)
         if (present != (e.R[l] > 0) || (present && e.R[l] < need[l])) return false;
         if (present) c += (double)e.R[l] * (l == 0 ? net.in_pad : net.fo[l - 1] + 16);
     }
+    if (padded) *padded = c;
     if (e.wl) {
         FitPlan tmp{};
         if (lds_layout(net, e, &tmp) > net.lds_max) return false;
-        c *= 0.5;                             // staged weights beat global fragment loads
+        // staged weights beat global fragment loads; run-time activations with more row
+        // blocks than twice the network's do not (12-45-1 in GELU, 156 sparks: 23 us a
+        // generation from global memory in 4 row blocks, 29 us from LDS in 8)
+        c *= e.act >= 0 || e.split ? 0.5 : 0.6;
     }
     if (e.act >= 0) c *= 0.9;                 // specialised activation: straight-line epilogue
+    if (e.split) c *= 0.5;                    // three FP16 products against one in FP32
     *cost = c;
     return true;
 }
 
-// Blocks per spark row by default: enough blocks to fill the chip (about 4 per
-// CU) while keeping at least two slab groups per wavefront.  A launch too small
-// to fill the chip even then (a few rows: the re-check of the winners, the
-// guiding sparks of a small job) takes one slab group per wavefront, since its
-// duration is the chain of passes a block runs one after another.
+// Blocks per spark row by default.  Weights in global memory: enough blocks to fill
+// the chip (about 4 per CU) while keeping at least two slab groups per wavefront; a
+// launch too small to fill the chip even then (a few rows) takes one slab group per
+// wavefront, since its duration is the chain of passes a block runs.  Weights in LDS:
+// every block stages them first (about half a pass of the FP32 kernels, a whole one
+// of BF16's), so the least time over the rounds that the chip needs, eight wavefronts
+// per CU at a time: 64 sparks of 64-128-128-10 in FP32 80 -> 59 us, 512 of 32-64-64-10
+// in BF16 53 -> 46 us against four blocks per CU.
 static int default_bpr(const Net &net, const KernelEntry &e, int rows)
 {
     const int group = e.nw * 16 * e.P;                    // samples per block pass
     const int max_bpr = (net.S_pad + group - 1) / group;
+    if (e.wl) {
+        FitPlan tmp{};
+        const int fit = (160 * 1024) / std::max(1, lds_layout(net, e, &tmp));
+        const long at_once = (long)std::max(1, net.num_cu) * std::max(1, std::min(8 / e.nw, fit));
+        int best = 1;
+        double least = 0.0;
+        for (int b = 1; b <= std::min(max_bpr, MAX_BPR); ++b) {
+            const int passes = (max_bpr + b - 1) / b;
+            if (b > 1 && passes == (max_bpr + b - 2) / (b - 1)) continue;   // no shorter blocks
+            const long blocks = (long)rows * ((max_bpr + passes - 1) / passes);
+            const double t = (double)((blocks + at_once - 1) / at_once) * (passes + (e.bf16 ? 1.0 : 0.5));
+            if (b == 1 || t < least) {
+                least = t;
+                best = b;
+            }
+        }
+        return best;
+    }
     int bpr = (1024 + rows - 1) / (rows > 0 ? rows : 1);
     const int lim = (long)rows * max_bpr <= 1024 ? max_bpr : max_bpr / 2 > 0 ? max_bpr / 2 : 1;
     if (bpr > lim) bpr = lim;
@@ -190,6 +260,11 @@ static void make_plan(const Net &net, const KernelEntry &e, int rows, int bpr, F
     plan->nw = e.nw;
     plan->P = e.P;
     plan->wl = e.wl;
+    plan->split = e.split;
+    // Every block of a row draws the row's weights again, which the kernels of up to
+    // three layers with the activation compiled in carry; others store the sparks (156
+    // sparks of 12-45-1 in GELU: 33 us a generation drawn in the kernel, 23 us stored).
+    plan->regen = e.wl && e.act >= 0 && net.nl <= 3;
     plan->rows = rows;
     lds_layout(net, e, plan);
     if (!e.wl) plan->lds_bytes = 0;
@@ -223,13 +298,24 @@ bool fit_select(const Net &net, int rows, FitPlan *plan)
 
 int fit_candidates(const Net &net, int rows, FitPlan *out, int max_out)
 {
+    // entries that pad the layers to more than twice what the tightest one does are
+    // never the fastest
+    double least = 0.0;
+    for (auto table : kTables) {
+        int nent = 0;
+        const KernelEntry *ents = table(&nent);
+        for (int ie = 0; ie < nent; ++ie) {
+            double cost = 0.0, padded = 0.0;
+            if (entry_fits(net, ents[ie], &cost, &padded) && (least == 0.0 || padded < least)) least = padded;
+        }
+    }
     int n = 0;
     for (auto table : kTables) {
         int nent = 0;
         const KernelEntry *ents = table(&nent);
         for (int ie = 0; ie < nent; ++ie) {
-            double cost = 0.0;
-            if (!entry_fits(net, ents[ie], &cost)) continue;
+            double cost = 0.0, padded = 0.0;
+            if (!entry_fits(net, ents[ie], &cost, &padded) || padded > 2.0 * least) continue;
             const int b0 = default_bpr(net, ents[ie], rows);
             for (int b : {b0, 2 * b0, b0 / 2, 4 * b0}) {
                 if (b < 1 || b > MAX_BPR || n >= max_out) continue;
@@ -253,7 +339,7 @@ hipError_t fit_prepare(const FitPlan &plan)
 }
 
 FitLaunch fit_launch_args(const Net &net, const FitPlan &plan, const DevState &d, const float *W,
-                          size_t ld, int rows, OutMap map, float *out, const SparkRegen *rg)
+                          size_t ld, int rows, OutMap map, float *out, bool boxed, const SparkRegen *rg)
 {
     FitLaunch f;
     FitArgs &a = f.a;
@@ -287,6 +373,9 @@ FitLaunch fit_launch_args(const Net &net, const FitPlan &plan, const DevState &d
     a.bpr = plan.bpr;
     a.spb = plan.spb;
     a.partial = d.partial;
+    a.Xe = d.Xe;
+    a.boxed = boxed ? 1 : 0;
+    a.wexp = net.wexp;
     f.inv_norm = net.inv_norm;
     f.map = map;
     f.out = out;
@@ -297,12 +386,12 @@ dim3 fitness_grid(const FitLaunch &f) { return dim3((unsigned)(f.a.rows * f.a.bp
 dim3 finalize_grid(const FitLaunch &f) { return dim3((unsigned)((f.a.rows + 255) / 256)); }
 
 hipError_t launch_fitness(const Net &net, const FitPlan &plan, const DevState &d, const float *W,
-                          size_t ld, int rows, OutMap map, float *out, hipStream_t st,
+                          size_t ld, int rows, OutMap map, float *out, hipStream_t st, bool boxed,
                           hipEvent_t mid, const SparkRegen *rg)
 {
     if (rows <= 0) return hipSuccess;
-    if (rg && !plan.wl) return hipErrorInvalidValue;   // only the staging regenerates
-    FitLaunch f = fit_launch_args(net, plan, d, W, ld, rows, map, out, rg);
+    if (rg && !plan.regen) return hipErrorInvalidValue;   // only the staging regenerates
+    FitLaunch f = fit_launch_args(net, plan, d, W, ld, rows, map, out, boxed, rg);
     FitArgs &a = f.a;
     void *args[] = {&a};
     hipError_t e = hipLaunchKernel(plan.kernel, dim3((unsigned)(rows * plan.bpr)),
@@ -339,9 +428,22 @@ hipError_t launch_finalize_group(const GroupTable &t, int which, hipStream_t st)
     return hipGetLastError();
 }
 
+hipError_t launch_sample_exp(const Net &net, const float *x, int32_t *Xe, hipStream_t st)
+{
+    if (net.wide)   // (the chain reads the samples' marks only)
+        hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, st, Xe + net.S_pad);
+    hipLaunchKernelGGL(k_sample_exp, dim3((unsigned)((net.S_pad + 3) / 4)), dim3(256), 0, st, x, net.S,
+                       net.S_pad, net.fi[0], Xe);
+    return hipGetLastError();
+}
+
 hipError_t launch_pack_problem(const Net &net, const float *x, const float *y,
                                const int32_t *labels, const DevState &d, hipStream_t st)
 {
+    if (d.Xe && chain_split(net)) {   // (the wide kernel packs its samples itself)
+        const hipError_t e = launch_sample_exp(net, x, d.Xe, st);
+        if (e != hipSuccess) return e;
+    }
     const int out = net.fo[net.nl - 1];
     size_t n = (size_t)net.S_pad * net.in_pad;
     if ((size_t)net.S_pad * out > n) n = (size_t)net.S_pad * out;

@@ -79,7 +79,7 @@ struct Net {
     float inv_norm;                    // 1/(S*out) for MSE, 1/S for CE
     int lds_max;                       // LDS bytes a block may use (0: weights stay in global)
     int wide;                          // first layer streamed through LDS (two-layer nets)
-    int wexp;                          // in two FP16 parts: the exponent of weights in the box
+    int wexp;                          // FP16 parts: the exponent of weights in the search box
     int num_cu;                        // compute units (persistent grid size)
 };
 
@@ -134,6 +134,10 @@ struct FitArgs {
     const int32_t *lab;    // [S_pad]
     int bpr, spb;
     float *partial;        // [rows][bpr]
+    // FP32 in two FP16 parts: the samples' exponents; whether the sparks lie in the
+    // search box, and then the exponent of their weights
+    const int32_t *Xe;
+    int boxed, wexp;
     // Explosion sparks regenerated while staging (rg.F non-null, LDS-staged
     // kernels only); W is then not read.
     SparkRegen rg;
@@ -146,6 +150,8 @@ struct FitPlan {
     int nw;               // wavefronts per block
     int P;                // 16-sample slabs per wave in flight
     int wl;               // weights staged in LDS
+    int split;            // FP32 in two FP16 parts
+    int regen;            // may draw the sparks itself (regen_sparks)
     int bpr;              // blocks per spark row
     int spb;              // samples per block
     int rows;
@@ -378,14 +384,15 @@ hipError_t fit_prepare(const FitPlan &plan);
 // per (row, block); the finalisation sums them in order.  `mid` (optional) is
 // recorded between the two launches.
 // rg (LDS-staged plans only): the sparks are regenerated, W is not read.
+// boxed: every row lies in the search box.
 hipError_t launch_fitness(const Net &net, const FitPlan &plan, const DevState &d,
                           const float *W, size_t ld, int rows, OutMap map, float *out,
-                          hipStream_t st, hipEvent_t mid = nullptr,
+                          hipStream_t st, bool boxed, hipEvent_t mid = nullptr,
                           const SparkRegen *rg = nullptr);
 // The kernel arguments and finalisation of one fitness launch (what
 // launch_fitness passes), for a grouped launch's job descriptor.
 FitLaunch fit_launch_args(const Net &net, const FitPlan &plan, const DevState &d, const float *W,
-                          size_t ld, int rows, OutMap map, float *out,
+                          size_t ld, int rows, OutMap map, float *out, bool boxed,
                           const SparkRegen *rg = nullptr);
 // Fitness launch `which` of every job of t, all on the same kernel instance
 // (gkernel, nw wavefronts, lds_bytes of dynamic LDS: the most any of them needs;
@@ -398,6 +405,9 @@ dim3 fitness_grid(const FitLaunch &f);     // the job's own grid of the GEMM ker
 dim3 finalize_grid(const FitLaunch &f);
 hipError_t launch_pack_problem(const Net &net, const float *x, const float *y,
                                const int32_t *labels, const DevState &d, hipStream_t st);
+// The samples' exponents and any-infinity flag for FP16 parts, into d.Xe.
+constexpr int XE_INF = 1 << 20;    // Xe of a sample with an infinity: its exponent + XE_INF
+hipError_t launch_sample_exp(const Net &net, const float *x, int32_t *Xe, hipStream_t st);
 // largest partial-sum count per row any plan may use
 int fit_max_bpr();
 // LDS bytes the resident-weights kernel would need for this network
