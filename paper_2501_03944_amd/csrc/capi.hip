@@ -172,6 +172,7 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
         }
         in.n_packed = off;
         in.hs = hmax + 4;   // 16-byte skew between the rows of the activation tile
+        in.frag = hmax <= NET_NARROW;
         in.hnp = hmax;      // hidden outputs: np[l] = kp[l+1]
         // fit_path 1 / 2 / 3 forces the whole-network / layer-by-layer /
         // LDS-staged layer-by-layer kernels (before autotuning)
@@ -293,7 +294,7 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
     L.Xe = take(!input && !net.bf16 ? (size_t)(net.S_pad + 1) * 4 : 0);
     L.lo = take(s.map_range ? (size_t)s.B * Dp * 4 : 0);
     L.hi = take(s.map_range ? (size_t)s.B * Dp * 4 : 0);
-    L.Pnet = take(input && need_data ? (size_t)in.n_packed * 4 : 0);
+    L.Pnet = take(input && need_data ? (size_t)in.n_packed * (in.frag ? 8 : 4) : 0);
     const size_t hbytes = input && need_data ? (size_t)L.partial_rows * in.hnp * 4 : 0;
     L.H0 = take(hbytes);
     L.H1 = take(hbytes);

@@ -89,6 +89,7 @@ struct Net {
 // np[l]; kp of a hidden layer is np of the layer before it.
 constexpr int NET_MAXL = 12;
 constexpr int NET_MAXW = 512;
+constexpr int NET_NARROW = 128;        // widest hidden layer of the narrow whole-network kernel
 struct InNet {
     int nl;                            // layers (the last has one output)
     int fi[NET_MAXL], fo[NET_MAXL];    // true widths
@@ -96,6 +97,7 @@ struct InNet {
     int act[NET_MAXL];                 // activation after layer l (identity for the last)
     int woff[NET_MAXL], boff[NET_MAXL];// float offsets into the packed parameters
     int n_packed;                      // floats of the packed parameters
+    int frag;                          // narrow networks: their weights in fragment order follow
     int hs;                            // LDS row pitch (floats) of the activation tile
     int hnp;                           // widest hidden output (padded): activation row pitch
     int num_cu;                        // compute units (rows per block choice)

@@ -36,8 +36,10 @@ namespace mgfwa {
 namespace {
 
 constexpr int NI_NW = 8;                      // waves per block
+static_assert(NET_NARROW == 16 * NI_NW, "one column block per wave");
 constexpr int NI_CB = NET_MAXW / 16 / NI_NW;  // output column blocks per wave at most
 constexpr int TPB = 256;
+constexpr int NARROW_D = 512;                  // longest input of one k_net_narrow launch
 
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 
@@ -158,8 +160,169 @@ __global__ __launch_bounds__(NI_NW * 64) void k_net_input(InNet net, const float
     }
 }
 
+// Elements k..k+3 of an input row, zeros from `cols` on.
+__device__ __forceinline__ float4 load_a(const float *row, int k, int cols)
+{
+    if (k + 4 <= cols) return *reinterpret_cast<const float4 *>(row + k);
+    return make_float4(k < cols ? row[k] : 0.0f, k + 1 < cols ? row[k + 1] : 0.0f,
+                       k + 2 < cols ? row[k + 2] : 0.0f, k + 3 < cols ? row[k + 3] : 0.0f);
+}
+
+// The whole network where no layer has more than 128 outputs: a wave owns one 16-column
+// block of each layer.  A block is a chain of small layers, bound by what a layer waits
+// for (4.2 us a layer of k_net_input, 2.5 us of it at any width): its weights, its bias
+// and its place in memory are therefore fetched a layer ahead, into the other of two
+// register sets, the input layer in groups of G0 chunks likewise, and the outputs go to
+// the other of two LDS tiles, one barrier a layer.  Loads are never conditional (past
+// the end they repeat the last chunk or layer): a wait behind a branch is for all of
+// them.  NG: chunks of the widest hidden layer.
+//
+// KS: partial sums per output, K chunk i in sum i % KS, added in order: 1 are the sums of
+// k_net_input, 4 those of k_net_layer<1, 1, 4>, so a launch's values do not depend on
+// which of them runs it.
+template <int KS, int NG>
+__global__ __launch_bounds__(NI_NW * 64) void k_net_narrow(InNet net, const float *__restrict__ P,
+                                                           const float *__restrict__ X, size_t ld,
+                                                           int rows, OutMap map,
+                                                           float *__restrict__ out)
+{
+    extern __shared__ float tiles[];   // [2][16][hs]
+    constexpr int G0 = 4;   // (8: 178 registers, and the kernel waits for compute units that others hold)
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int c = lane & 15, q = lane >> 4;
+    const int r0 = blockIdx.x * 16;
+    const int hs = net.hs, d = net.fi[0], nl = net.nl;
+    struct Layer {
+        int K, nb, act;
+        const float *W, *bias;
+    };
+    auto layer = [&](int l) {
+        l = min(l, nl - 1);
+        return Layer{net.kp[l], net.np[l] >> 4, net.act[l], P + net.n_packed + net.woff[l], P + net.boff[l]};
+    };
+    // weights of chunks kc.. of this wave's block (without one: the last block's)
+    auto fetch = [&](const Layer &m, int kc, auto &b) {
+        constexpr int N = sizeof(b) / sizeof(b[0]);
+        const float *W = m.W + (size_t)min(wave, m.nb - 1) * 16 * m.K + 4 * lane;
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+            b[i] = *reinterpret_cast<const float4 *>(W + 16 * min(kc + 16 * i, m.K - 16));
+    };
+    auto fetch_bias = [&](const Layer &m) { return m.bias[16 * min(wave, m.nb - 1) + c]; };
+    floatx4 acc[KS];
+#pragma unroll
+    for (int s = 0; s < KS; ++s) acc[s] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    // outputs of layer l into tile l & 1, or the network's; the sums start again
+    auto store = [&](const Layer &m, int l, float bias) {
+        const int col = 16 * wave + c;
+        float *tile = tiles + (l & 1) * 16 * hs;
+        if (wave < m.nb) {
+            floatx4 t = acc[0];
+#pragma unroll
+            for (int s = 1; s < KS; ++s) t += acc[s];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = 4 * q + v;
+                const float z = t[v] + bias;
+                if (l + 1 < nl) tile[row * hs + col] = ni_act(m.act, z);
+                else if (col == 0 && r0 + row < rows) out[map.index(r0 + row)] = canon_fitness(z);
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < KS; ++s) acc[s] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    Layer m = layer(0), m1 = layer(1);
+    float4 ba[NG], bb[NG];
+    float biasa, biasb;
+    {
+        const float *xr = X + (size_t)min(r0 + c, rows - 1) * ld;   // (past the end: the last row)
+        // input elements from d on read as zero (a row is readable to a multiple of four)
+        auto fetch_x = [&](int kc, float4 (&x)[G0]) {
+#pragma unroll
+            for (int i = 0; i < G0; ++i)
+                x[i] = *reinterpret_cast<const float4 *>(xr + min(kc + 16 * i + 4 * q, (d - 1) & ~3));
+        };
+        auto group = [&](int kc, const float4 (&w)[G0], float4 (&x)[G0]) {
+            if (kc + 16 * G0 <= d) {
+#pragma unroll
+                for (int i = 0; i < G0; ++i) mfma4(acc[i % KS], x[i], w[i]);
+                return;
+            }
+#pragma unroll
+            for (int i = 0; i < G0; ++i) {
+                const int k = kc + 16 * i + 4 * q;
+                if (kc + 16 * i >= d) continue;
+                mfma4(acc[i % KS],
+                      make_float4(k < d ? x[i].x : 0.0f, k + 1 < d ? x[i].y : 0.0f, k + 2 < d ? x[i].z : 0.0f,
+                                  k + 3 < d ? x[i].w : 0.0f),
+                      w[i]);
+            }
+        };
+        float4 wa[G0], wb[G0], xa[G0], xb[G0];
+        const float bias0 = fetch_bias(m);
+        fetch(m, 0, wa);
+        fetch_x(0, xa);
+        if (d > 16 * G0) {
+            for (int kc = 0;;) {
+                fetch(m, kc + 16 * G0, wb);
+                fetch_x(kc + 16 * G0, xb);
+                group(kc, wa, xa);
+                if ((kc += 16 * G0) >= d) break;
+                fetch(m, kc + 16 * G0, wa);
+                fetch_x(kc + 16 * G0, xa);
+                group(kc, wb, xb);
+                if ((kc += 16 * G0) >= d) break;
+            }
+            fetch(m1, 0, ba);
+            biasa = fetch_bias(m1);
+        } else {
+            fetch(m1, 0, ba);
+            biasa = fetch_bias(m1);
+            group(0, wa, xa);
+        }
+        store(m, 0, bias0);
+    }
+    if (nl == 1) return;
+    Layer m2 = layer(2);
+    __syncthreads();
+    // layer l with its weights in b; layer l + 1's go to bn
+    auto hidden = [&](int l, const float4 (&b)[NG], float bias, float4 (&bn)[NG], float &biasn) {
+        m = m1;
+        m1 = m2;
+        fetch(m1, 0, bn);
+        biasn = fetch_bias(m1);
+        m2 = layer(l + 2);
+        const float *in = tiles + ((l - 1) & 1) * 16 * hs + c * hs + 4 * q;
+        if (wave < m.nb) {
+            if (m.K == 16 * NG) {
+                float4 x[NG];
+#pragma unroll
+                for (int i = 0; i < NG; ++i) x[i] = *reinterpret_cast<const float4 *>(in + 16 * i);
+#pragma unroll
+                for (int i = 0; i < NG; ++i) mfma4(acc[i % KS], x[i], b[i]);
+            } else {
+#pragma unroll
+                for (int i = 0; i < NG; ++i)
+                    if (16 * i < m.K)
+                        mfma4(acc[i % KS], *reinterpret_cast<const float4 *>(in + 16 * i), b[i]);
+            }
+        }
+        store(m, l, bias);
+    };
+    for (int l = 1;;) {
+        hidden(l, ba, biasa, bb, biasb);
+        if (++l == nl) break;
+        __syncthreads();
+        hidden(l, bb, biasb, ba, biasa);
+        if (++l == nl) break;
+        __syncthreads();
+    }
+}
+
 // Packed parameter i of layer l: W block [np][kp] then the bias [np], zeros
-// outside the true fo x fi (and fo) extents.
+// outside the true fo x fi (and fo) extents.  A narrow network's weights follow once
+// more, in the order that a wavefront's lanes read a 16 x 16 fragment.
 __global__ __launch_bounds__(TPB) void k_pack_net(InNet net, const float *__restrict__ src,
                                                   float *__restrict__ dst)
 {
@@ -177,6 +340,10 @@ __global__ __launch_bounds__(TPB) void k_pack_net(InNet net, const float *__rest
     if (i < net.boff[l]) {
         const int n = o / kp, k = o % kp;
         if (n < fo && k < fi) v = src[soff + (size_t)n * fi + k];
+        if (net.frag) {
+            const int lane = (k & 12) * 4 + (n & 15);
+            dst[net.n_packed + net.woff[l] + ((n >> 4) * (kp >> 4) + (k >> 4)) * 256 + 4 * lane + (k & 3)] = v;
+        }
     } else {
         const int n = i - net.boff[l];
         if (n < fo) v = src[soff + (size_t)fi * fo + n];
@@ -200,13 +367,6 @@ struct LayerArgs {
     OutMap map;           // last layer: where row r's output goes
     float *out;
 };
-
-__device__ __forceinline__ float4 load_a(const float *row, int k, int cols)
-{
-    if (k + 4 <= cols) return *reinterpret_cast<const float4 *>(row + k);
-    return make_float4(k < cols ? row[k] : 0.0f, k + 1 < cols ? row[k + 1] : 0.0f,
-                       k + 2 < cols ? row[k + 2] : 0.0f, k + 3 < cols ? row[k + 3] : 0.0f);
-}
 
 // One layer over a tile grid (blockIdx.x: row tiles, blockIdx.y: column tiles).
 // KS = 1: waves 2 x 2 over (rows, columns), each a (16 RBW) x (16 CBW) tile.
@@ -639,8 +799,42 @@ hipError_t launch_net_input(const InNet &net, int shape, const float *packed, co
     // the LDS-staged kernels copy whole 16-byte input segments
     if ((shape == NET_LDS || shape == NET_LDS64) && (net.fi[0] % 4 != 0 || ld % 4 != 0))
         shape = shape == NET_LDS ? 0 : 1;
-    if (shape != NET_WHOLE)
+    // Narrow networks: whole-network tiles with the K-split layers' sums where few rows
+    // would take those, and in place of k_net_input up to NARROW_D inputs, until
+    // two of its row blocks per tile pay (8,192 rows of 10-96x4: 31 us a generation, 32 us
+    // with these).
+    const bool few = shape == 3;
+    const bool narrow = net.frag && ld % 4 == 0 && (few || (shape == NET_WHOLE));
+    if (shape != NET_WHOLE && !narrow)
         return launch_layers(net, shape, packed, X, ld, rows, map, out, H0, H1, st, zero);
+    if (narrow) {
+        InNet n = net;
+        if (few && net.fi[0] > NARROW_D) {
+            // an input layer this long is split over more blocks than the rows' own: its
+            // outputs by a launch of their own, the rest of the network behind it
+            const LayerArgs a{X, ld, net.fi[0], packed + net.woff[0], packed + net.boff[0], net.kp[0], net.np[0],
+                              H0, net.hnp, net.act[0], net.nl == 1, rows, map, out};
+            hipLaunchKernelGGL((k_net_layer<1, 1, 4>), dim3((rows + 15) / 16, net.np[0] / 16), dim3(256), 0, st, a);
+            if (--n.nl == 0) return hipGetLastError();
+            for (int l = 0; l < n.nl; ++l) {
+                n.fi[l] = net.fi[l + 1];
+                n.fo[l] = net.fo[l + 1];
+                n.kp[l] = net.kp[l + 1];
+                n.np[l] = net.np[l + 1];
+                n.act[l] = net.act[l + 1];
+                n.woff[l] = net.woff[l + 1];
+                n.boff[l] = net.boff[l + 1];
+            }
+            X = H0;
+            ld = net.hnp;
+        }
+        const auto kernel = net.hnp <= 32   ? few ? k_net_narrow<4, 2> : k_net_narrow<1, 2>
+                            : net.hnp <= 64 ? few ? k_net_narrow<4, 4> : k_net_narrow<1, 4>
+                                            : few ? k_net_narrow<4, 8> : k_net_narrow<1, 8>;
+        hipLaunchKernelGGL(kernel, dim3((rows + 15) / 16), dim3(NI_NW * 64), 2 * lds_bytes_rb<1>(net), st, n,
+                           packed, X, ld, rows, map, out);
+        return hipGetLastError();
+    }
     // the most rows per block that still gives every compute unit a block
     const dim3 block(NI_NW * 64);
     if (rows >= 32 * cu) {
