@@ -509,9 +509,7 @@ mgfwa_status enqueue_generation(mgfwa_ctx *c, hipStream_t st, hipEvent_t *ev)
         if (r) return r;
         if (ev) STEP(hipEventRecord(ev[9], st), "event");
     }
-    STEP(launch_select(s, c->d, st, s.recheck), "select");
-    STEP(launch_apply(s, c->d, st, s.recheck), "apply");
-    STEP(launch_finish(c->d, 1, st), "finish");
+    STEP(launch_update(s, c->d, st, s.recheck), "update");
     if (ev) STEP(hipEventRecord(ev[5], st), "event");
     return MGFWA_OK;
 }
@@ -870,9 +868,7 @@ mgfwa_status mgfwa_tell(mgfwa_ctx *c, const float *fit)
     case PH_GUIDE_TELL:
         STEP(launch_store_fitness(fit, s.BN * s.G, OutMap{s.G, s.C, s.lam}, c->d.Yc, c->d.ctrl,
                                   c->stream), "store");
-        STEP(launch_select(s, c->d, c->stream), "select");
-        STEP(launch_apply(s, c->d, c->stream), "apply");
-        STEP(launch_finish(c->d, 1, c->stream), "finish");
+        STEP(launch_update(s, c->d, c->stream), "update");
         c->phase = PH_READY;
         c->gen_host += 1;
         break;

@@ -11,7 +11,7 @@ namespace mgfwa {
 enum : uint32_t { TAG_INIT = 0, TAG_EXPL = 1, TAG_EXPL_MAP = 2, TAG_GUIDE_MAP = 3, TAG_REINIT = 4 };
 
 // Device control words (int32 array in the workspace).
-enum : int { CTRL_GEN = 0, CTRL_DONE = 1, CTRL_DONE_PENDING = 2, CTRL_WORDS = 4 };
+enum : int { CTRL_GEN = 0, CTRL_DONE = 1, CTRL_DONE_PENDING = 2, CTRL_COUNT = 3, CTRL_WORDS = 4 };
 
 struct Box {
     float lb, ub, span;  // span = ub - lb rounded once to binary32

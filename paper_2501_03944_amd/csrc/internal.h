@@ -369,6 +369,8 @@ hipError_t launch_apply(const Shape &s, const DevState &d, hipStream_t st, bool 
 // s.regen).
 hipError_t launch_gather_best(const Shape &s, const DevState &d, hipStream_t st);
 hipError_t launch_finish(const DevState &d, int advance, hipStream_t st);
+// The end of a generation: select, apply and finish.
+hipError_t launch_update(const Shape &s, const DevState &d, hipStream_t st, bool checked = false);
 // Zero the control words (generation counter, stop flags) in stream order.
 hipError_t launch_clear_ctrl(int32_t *ctrl, hipStream_t st);
 hipError_t launch_store_fitness(const float *src, int rows, OutMap map, float *out,

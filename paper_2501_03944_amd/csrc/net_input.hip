@@ -800,9 +800,8 @@ hipError_t launch_net_input(const InNet &net, int shape, const float *packed, co
     if ((shape == NET_LDS || shape == NET_LDS64) && (net.fi[0] % 4 != 0 || ld % 4 != 0))
         shape = shape == NET_LDS ? 0 : 1;
     // Narrow networks: whole-network tiles with the K-split layers' sums where few rows
-    // would take those, and in place of k_net_input up to NARROW_D inputs, until
-    // two of its row blocks per tile pay (8,192 rows of 10-96x4: 31 us a generation, 32 us
-    // with these).
+    // would take those (600 rows of 414-128x8: 47.5 -> 30 us a generation), and in place of
+    // k_net_input (4,096 rows of 1000-64x5: 48 -> 41 us).
     const bool few = shape == 3;
     const bool narrow = net.frag && ld % 4 == 0 && (few || (shape == NET_WHOLE));
     if (shape != NET_WHOLE && !narrow)

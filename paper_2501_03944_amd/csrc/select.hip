@@ -26,6 +26,7 @@ namespace mgfwa {
 namespace {
 
 constexpr int TPB = 256;
+constexpr int UPDATE_TPB = 1024;
 constexpr int MAX_GRID_Y = 65535;
 constexpr int SRC_NONE = -1;
 
@@ -55,20 +56,6 @@ __device__ __forceinline__ void best_candidate(const float *yc, int C, int lane,
     }
     *ymin_out = ymin;
     *cs_out = cs;
-}
-
-__device__ void population_best(const float *Y, int N, int *fb_out, float *yb_out)
-{
-    // lowest fitness, lower index on ties; N is small, one thread scans in order
-    int fb = 0;
-    float yb = Y[0];
-    for (int f = 1; f < N; ++f)
-        if (Y[f] < yb) {
-            yb = Y[f];
-            fb = f;
-        }
-    *fb_out = fb;
-    *yb_out = yb;
 }
 
 __device__ __forceinline__ void select_body(const Shape &s, const DevState &d, bool checked,
@@ -127,7 +114,15 @@ __device__ __forceinline__ void select_body(const Shape &s, const DevState &d, b
         }
     }
     __syncthreads();
-    if (threadIdx.x == 0) population_best(Y + (size_t)b * N, N, &s_fb, &s_yb);
+    if (threadIdx.x < 64) {   // (one thread after another through Y: 0.5 us a firework)
+        int fb;
+        float yb;
+        best_candidate(Y + (size_t)b * N, N, lane, &yb, &fb);
+        if (lane == 0) {
+            s_fb = fb;
+            s_yb = yb;
+        }
+    }
     __syncthreads();
     const int fb = s_fb;
     const float yb = s_yb;
@@ -159,7 +154,8 @@ __device__ __forceinline__ void select_body(const Shape &s, const DevState &d, b
     }
 }
 
-__global__ __launch_bounds__(TPB) void k_select(Shape s, DevState d, int checked)
+// (a wavefront per firework of most jobs)
+__global__ __launch_bounds__(UPDATE_TPB) void k_select(Shape s, DevState d, int checked)
 {
     select_body(s, d, checked != 0, own_block());
 }
@@ -184,10 +180,10 @@ __global__ __launch_bounds__(TPB) void k_init_select(Shape s, const float *__res
         reinit[gf] = 0;
         src[gf] = SRC_NONE;
     }
+    int fb = 0;
+    float yb = 0.0f;
+    if (threadIdx.x < 64) best_candidate(Y + (size_t)b * N, N, threadIdx.x, &yb, &fb);
     if (threadIdx.x == 0) {
-        int fb;
-        float yb;
-        population_best(Y + (size_t)b * N, N, &fb, &yb);
         best_y[b] = yb;
         best_f[b] = fb;
         best_gen[b] = 0;
@@ -200,71 +196,98 @@ __global__ __launch_bounds__(TPB) void k_init_select(Shape s, const float *__res
 // row (still the generation's, read before it is overwritten), its explosion
 // amplitude and the population range, exactly as the explosion drew it.  With
 // wstar the winner is the row k_gather_best stored there.
+__device__ __forceinline__ void apply_chunk(const Shape &s, const DevState &d, bool checked, uint32_t t,
+                                            int gf, int chunk)
+{
+    float *F = d.F;
+    const float *SE = d.SE;
+    const float *SG = d.SG;
+    const float *lo = s.map_range ? d.lo : nullptr;
+    const float *hi = s.map_range ? d.hi : nullptr;
+    const float *wstar = checked ? d.Wstar : nullptr;
+    const int b = gf / s.N, f = gf % s.N;
+    const int sr = d.src[gf], ri = d.reinit[gf];
+    const bool copy_best = d.best_upd[b] && d.best_f[b] == f;
+    if (!ri && sr < 0 && !copy_best) return;
+    float4 *frow = reinterpret_cast<float4 *>(F + (size_t)gf * s.Dp);
+    float4 v;
+    if (ri) {
+        const uint4 r = draw4(s.key, (uint32_t)chunk, (uint32_t)gf, t, TAG_REINIT);
+        const uint32_t w[4] = {r.x, r.y, r.z, r.w};
+        float e4[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            e4[e] = box_uniform(s.box, u01(w[e]));
+            if (4 * chunk + e >= s.D) e4[e] = 0.0f;
+        }
+        v = make_float4(e4[0], e4[1], e4[2], e4[3]);
+        frow[chunk] = v;
+    } else if (sr >= 0 && wstar) {
+        // the gathered candidate row (the one its FP32 fitness was taken of)
+        v = reinterpret_cast<const float4 *>(wstar + (size_t)gf * s.Dp)[chunk];
+        frow[chunk] = v;
+    } else if (sr >= 0 && sr < s.lam && s.regen) {
+        const float4 x4 = frow[chunk];
+        const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+        const size_t pb = (size_t)b * s.Dp;
+        float e4[4];
+        explosion_chunk(x, d.Aexp[gf], s.key, chunk, (uint32_t)(gf * s.lam + sr), t, s.box,
+                        lo ? lo + pb : nullptr, hi ? hi + pb : nullptr, s.D, e4);
+        v = make_float4(e4[0], e4[1], e4[2], e4[3]);
+        frow[chunk] = v;
+    } else if (sr >= 0) {
+        const float *row = sr < s.lam ? SE + ((size_t)gf * s.lam + sr) * s.Dp
+                                      : SG + ((size_t)gf * s.G + (sr - s.lam)) * s.Dp;
+        v = reinterpret_cast<const float4 *>(row)[chunk];
+        frow[chunk] = v;
+    } else {
+        v = frow[chunk];
+    }
+    if (copy_best) reinterpret_cast<float4 *>(d.best_x + (size_t)b * s.Dp)[chunk] = v;
+}
+
 __device__ __forceinline__ void apply_body(const Shape &s, const DevState &d, bool checked, Blk blk)
 {
-    float *__restrict__ F = d.F;
-    const float *__restrict__ SE = d.SE;
-    const float *__restrict__ SG = d.SG;
-    const float *__restrict__ Aexp = d.Aexp;
-    const float *__restrict__ lo = s.map_range ? d.lo : nullptr;
-    const float *__restrict__ hi = s.map_range ? d.hi : nullptr;
-    const int32_t *__restrict__ src = d.src;
-    const int32_t *__restrict__ reinit = d.reinit;
-    const int32_t *__restrict__ best_f = d.best_f;
-    const int32_t *__restrict__ best_upd = d.best_upd;
-    float *__restrict__ best_x = d.best_x;
-    const float *__restrict__ wstar = checked ? d.Wstar : nullptr;
     const int32_t *__restrict__ ctrl = d.ctrl;
     if (ctrl[CTRL_DONE]) return;
     const uint32_t t = (uint32_t)ctrl[CTRL_GEN] + 1u;
     const int chunk = blk.x * TPB + threadIdx.x;
     if (chunk >= (s.Dp >> 2)) return;
-    for (int gf = blk.y; gf < s.BN; gf += blk.gy) {
-        const int b = gf / s.N, f = gf % s.N;
-        const int sr = src[gf], ri = reinit[gf];
-        const bool copy_best = best_upd[b] && best_f[b] == f;
-        if (!ri && sr < 0 && !copy_best) continue;
-        float4 *frow = reinterpret_cast<float4 *>(F + (size_t)gf * s.Dp);
-        float4 v;
-        if (ri) {
-            const uint4 r = draw4(s.key, (uint32_t)chunk, (uint32_t)gf, t, TAG_REINIT);
-            const uint32_t w[4] = {r.x, r.y, r.z, r.w};
-            float e4[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                e4[e] = box_uniform(s.box, u01(w[e]));
-                if (4 * chunk + e >= s.D) e4[e] = 0.0f;
-            }
-            v = make_float4(e4[0], e4[1], e4[2], e4[3]);
-            frow[chunk] = v;
-        } else if (sr >= 0 && wstar) {
-            // the gathered candidate row (the one its FP32 fitness was taken of)
-            v = reinterpret_cast<const float4 *>(wstar + (size_t)gf * s.Dp)[chunk];
-            frow[chunk] = v;
-        } else if (sr >= 0 && sr < s.lam && s.regen) {
-            const float4 x4 = frow[chunk];
-            const float x[4] = {x4.x, x4.y, x4.z, x4.w};
-            const size_t pb = (size_t)b * s.Dp;
-            float e4[4];
-            explosion_chunk(x, Aexp[gf], s.key, chunk, (uint32_t)(gf * s.lam + sr), t, s.box,
-                            lo ? lo + pb : nullptr, hi ? hi + pb : nullptr, s.D, e4);
-            v = make_float4(e4[0], e4[1], e4[2], e4[3]);
-            frow[chunk] = v;
-        } else if (sr >= 0) {
-            const float *row = sr < s.lam ? SE + ((size_t)gf * s.lam + sr) * s.Dp
-                                          : SG + ((size_t)gf * s.G + (sr - s.lam)) * s.Dp;
-            v = reinterpret_cast<const float4 *>(row)[chunk];
-            frow[chunk] = v;
-        } else {
-            v = frow[chunk];
-        }
-        if (copy_best) reinterpret_cast<float4 *>(best_x + (size_t)b * s.Dp)[chunk] = v;
-    }
+    for (int gf = blk.y; gf < s.BN; gf += blk.gy) apply_chunk(s, d, checked, t, gf, chunk);
 }
 
 __global__ __launch_bounds__(TPB) void k_apply(Shape s, DevState d, int checked)
 {
     apply_body(s, d, checked != 0, own_block());
+}
+
+// Selection, apply and the end of a small generation in one launch, a block per
+// population: the launches themselves are most of such a generation's end (three of 1.5
+// to 4 us each; 100-128x8, eight fireworks of 512 sparks, 10.1 + 4.6 + 3.9 us -> one of
+// 8 us, a generation among others 40.2 -> 36.0 us).  The last block to finish ends the
+// generation; none waits for another.
+__global__ __launch_bounds__(UPDATE_TPB) void k_update(Shape s, DevState d, int checked)
+{
+    if (d.ctrl[CTRL_DONE]) return;
+    const uint32_t t = (uint32_t)d.ctrl[CTRL_GEN] + 1u;
+    select_body(s, d, checked != 0, own_block());
+    __syncthreads();
+    const int nchunk = s.Dp >> 2;
+    for (int i = threadIdx.x; i < s.N * nchunk; i += UPDATE_TPB)
+        apply_chunk(s, d, checked != 0, t, blockIdx.x * s.N + i / nchunk, i % nchunk);
+    __syncthreads();   // the block has read the control words
+    if (threadIdx.x != 0) return;
+    int32_t pending;
+    if (gridDim.x > 1) {
+        __threadfence();
+        if (atomicAdd(&d.ctrl[CTRL_COUNT], 1) != (int)gridDim.x - 1) return;
+        atomicExch(&d.ctrl[CTRL_COUNT], 0);
+        pending = atomicOr(&d.ctrl[CTRL_DONE_PENDING], 0);   // (set by any block)
+    } else {
+        pending = d.ctrl[CTRL_DONE_PENDING];
+    }
+    d.ctrl[CTRL_GEN] = (int)t;
+    if (pending) d.ctrl[CTRL_DONE] = 1;
 }
 
 // c* of firework blk.y (every block recomputes it: C values, one
@@ -409,7 +432,7 @@ dim3 firework_row_grid(const Shape &s)
 
 hipError_t launch_select(const Shape &s, const DevState &d, hipStream_t st, bool checked)
 {
-    hipLaunchKernelGGL(k_select, select_grid(s), dim3(TPB), 0, st, s, d, checked ? 1 : 0);
+    hipLaunchKernelGGL(k_select, select_grid(s), dim3(UPDATE_TPB), 0, st, s, d, checked ? 1 : 0);
     return hipGetLastError();
 }
 
@@ -454,6 +477,20 @@ hipError_t launch_apply(const Shape &s, const DevState &d, hipStream_t st, bool 
 {
     hipLaunchKernelGGL(k_apply, firework_row_grid(s), dim3(TPB), 0, st, s, d, checked ? 1 : 0);
     return hipGetLastError();
+}
+
+hipError_t launch_update(const Shape &s, const DevState &d, hipStream_t st, bool checked)
+{
+    // up to four chunks of four coordinates a thread of the one block that a population
+    // then has; larger rows are copied faster by the apply launch's many blocks
+    if ((long)s.N * (s.Dp >> 2) <= 4 * UPDATE_TPB) {
+        hipLaunchKernelGGL(k_update, select_grid(s), dim3(UPDATE_TPB), 0, st, s, d, checked ? 1 : 0);
+        return hipGetLastError();
+    }
+    hipError_t e = launch_select(s, d, st, checked);
+    if (e == hipSuccess) e = launch_apply(s, d, st, checked);
+    if (e == hipSuccess) e = launch_finish(d, 1, st);
+    return e;
 }
 
 hipError_t launch_clear_ctrl(int32_t *ctrl, hipStream_t st)
