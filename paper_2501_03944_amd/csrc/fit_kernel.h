@@ -739,6 +739,14 @@ __device__ __forceinline__ void slab_loss(const FitArgs &a, int l, int s0, int n
     }
 }
 
+// Block c's part of row r's loss; the row's only block also finishes its fitness (what
+// k_fit_finalize makes of one partial sum: a launch of 3 us less).
+__device__ __forceinline__ void store_loss(const FitArgs &a, int r, int c, float t)
+{
+    a.partial[(size_t)r * a.bpr + c] = t;
+    if (a.bpr == 1) a.out[a.map.index(r)] = canon_fitness((float)((double)t * (double)a.inv_norm));
+}
+
 // Block `bid` of a fitness launch: spark r = bid / bpr, sample range c = bid % bpr.
 template <bool BF, bool WL, int NW, int P, int ACT, int R1, int R2, int R3, int R4, int SCHED>
 __device__ __forceinline__ void fit_body(const FitArgs &a, int bid)
@@ -816,7 +824,7 @@ __device__ __forceinline__ void fit_body(const FitArgs &a, int bid)
         float t = red[0];
 #pragma unroll
         for (int i = 1; i < NW; ++i) t += red[i];
-        a.partial[(size_t)r * a.bpr + c] = t;
+        store_loss(a, r, c, t);
     }
 }
 

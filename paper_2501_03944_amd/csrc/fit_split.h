@@ -19,8 +19,7 @@
 //
 // Measured, FP32 instructions -> so: a generation of 64-128-128-10 (2,048 sparks x 4,096
 // samples) 3,478 -> 1,350 us; 300 rows x 4,096 samples of it 574 -> 258 us, their error
-// against binary64 5.2e-8 -> 4.5e-8; 224 sparks x 6,044 samples of 32-98-98-2 in tanh
-// 1,746 -> 515 us (from global memory before).
+// against binary64 5.2e-8 -> 4.5e-8.
 //
 // Samples, weights or activations that are not finite, or whose exponents leave the
 // FP32 range, are scored by slow_losses in FP32 without parts.
@@ -431,7 +430,7 @@ __device__ __forceinline__ void split_body(const FitArgs &a, int bid)
     }
     if (__syncthreads_or(bad)) {
         const float t = slow_losses(a, w, r, s_begin, s_end, reinterpret_cast<float *>(smem));
-        if (threadIdx.x == 0) a.partial[(size_t)r * a.bpr + c] = t;
+        if (threadIdx.x == 0) store_loss(a, r, c, t);
         return;
     }
     loss.flush();
@@ -445,7 +444,7 @@ __device__ __forceinline__ void split_body(const FitArgs &a, int bid)
         float t = red[0];
 #pragma unroll
         for (int i = 1; i < NW; ++i) t += red[i];
-        a.partial[(size_t)r * a.bpr + c] = t;
+        store_loss(a, r, c, t);
     }
 }
 

@@ -6,9 +6,11 @@ namespace fit {
 
 namespace {
 const KernelEntry kEntries[] = {
-    // 8-16-1 tanh: weights in LDS; FP32 with 2 wavefronts x 2 slabs, so that a
-    // 256-sample launch spreads over 4 blocks per spark (measured 0.042 -> 0.040
-    // ms per generation against 4 x 4; 1 x 2, 2 x 1 and 4 x 1 within noise of it)
+    // 8-16-1 tanh: weights in LDS; FP32 with 8 wavefronts x 2 slabs, so that one block
+    // takes 256 samples and finishes the row itself (256 sparks x 256 samples: 33 us a
+    // generation, 35 with 2 x 2 in four blocks and the finalisation's launch, 34.5 with
+    // 4 x 4)
+    FIT_ENTRY_ACT(false, true, 8, 2, 2, 1, 1, 0, 0),
     FIT_ENTRY_ACT(false, true, 2, 2, 2, 1, 1, 0, 0),
     FIT_ENTRY_ACT(false, true, 4, 4, 2, 1, 1, 0, 0),
     FIT_ENTRY_ACT(true, true, 4, 4, 2, 2, 1, 0, 0),

@@ -60,8 +60,7 @@ __global__ __launch_bounds__(256) void k_fit_finalize_group(GroupTable t, int wh
     Blk gb;
     if (!group_block(t, j, blockIdx.x, &gb)) return;   // padding
     const FitLaunch f = t.job[j]->fit[which];
-    finalize_body(f.a.partial, f.a.rows, f.a.bpr, f.inv_norm, f.map, f.out,
-                  gb);
+    finalize_body(f.a.partial, f.a.rows, f.a.bpr, f.a.inv_norm, f.a.map, f.a.out, gb);
 }
 
 // Pack the problem data: X zero-padded to [S_pad][in_pad] (FP32 or bf16 RNE;
@@ -170,12 +169,18 @@ int resident_lds_bytes(const Net &net)
 // Whether the network may take the register chain in two FP16 parts.  Those (7e-8 of a
 // value, fewer roundings of the sum) are the more accurate form of a layer from about 48
 // inputs on: error of the fitness against binary64 at 32-64-64-64-10 5.9e-8 -> 4.8e-8, but
-// 6.3e-8 -> 7.0e-8 at 16-36-36-36-2.
+// 6.3e-8 -> 7.0e-8 at 16-36-36-36-2, 5.4e-8 -> 5.6e-8 at 16-209-10 and 7.5e-8 -> 8.4e-8
+// at 3-58-1, where the first layer's few products are all but exact in FP32, and with few
+// outputs, where fewer logits average it out (5.9e-8 -> 6.2e-8 at 32-128-2, 5.6e-8 ->
+// 6.8e-8 at 20-48-48-3; 5.9e-8 -> 5.8e-8 at 30-96-96-10, 5.3e-8 -> 4.0e-8 at 32-64-10).
 static bool chain_split(const Net &net)
 {
-    int widest = 0;
-    for (int l = 0; l + 1 < net.nl; ++l) widest = std::max(widest, net.fo[l]);
-    return !net.bf16 && !net.wide && widest >= 48;
+    int widest = 0, narrowest = net.fi[0];
+    for (int l = 0; l + 1 < net.nl; ++l) {
+        widest = std::max(widest, net.fo[l]);
+        narrowest = std::min(narrowest, net.fo[l]);
+    }
+    return !net.bf16 && !net.wide && widest >= 48 && narrowest >= 20 && net.fo[net.nl - 1] >= 8;
 }
 
 // Whether kernel entry e covers the network; *cost is the model cost used to
@@ -231,13 +236,16 @@ static int default_bpr(const Net &net, const KernelEntry &e, int rows)
         FitPlan tmp{};
         const int fit = (160 * 1024) / std::max(1, lds_layout(net, e, &tmp));
         const long at_once = (long)std::max(1, net.num_cu) * std::max(1, std::min(8 / e.nw, fit));
-        int best = 1;
+        int best = 1, widest = 0;
+        for (int l = 0; l < net.nl; ++l) widest = std::max(widest, net.fo[l]);
         double least = 0.0;
         for (int b = 1; b <= std::min(max_bpr, MAX_BPR); ++b) {
             const int passes = (max_bpr + b - 1) / b;
             if (b > 1 && passes == (max_bpr + b - 2) / (b - 1)) continue;   // no shorter blocks
             const long blocks = (long)rows * ((max_bpr + passes - 1) / passes);
-            const double t = (double)((blocks + at_once - 1) / at_once) * (passes + (e.bf16 ? 1.0 : 0.5));
+            // (several blocks a row: the finalisation's launch, a pass of a small network)
+            const double t = (double)((blocks + at_once - 1) / at_once) * (passes + (e.bf16 ? 1.0 : 0.5)) +
+                             (b > 1 && widest <= 32 ? 1.0 : 0.0);
             if (b == 1 || t < least) {
                 least = t;
                 best = b;
@@ -285,6 +293,11 @@ bool fit_select(const Net &net, int rows, FitPlan *plan)
         for (int ie = 0; ie < nent; ++ie) {
             double cost = 0.0;
             if (!entry_fits(net, ents[ie], &cost)) continue;
+            // rows that fill the chip by themselves: with few samples a network of 16
+            // units takes the blocks of fewer wavefronts (2,048 sparks x 256 samples of
+            // 8-16-1: 51 us a generation with 2 x 2, 57 with 8 x 2; 256 sparks: 37 and 33)
+            if (ents[ie].R[0] == 1 && ents[ie].nw > 4 && rows >= 4L * net.num_cu && net.S_pad < 1024)
+                cost *= 1.1;
             if (!best || cost < best_cost) {
                 best = &ents[ie];
                 best_cost = cost;
@@ -376,9 +389,9 @@ FitLaunch fit_launch_args(const Net &net, const FitPlan &plan, const DevState &d
     a.Xe = d.Xe;
     a.boxed = boxed ? 1 : 0;
     a.wexp = net.wexp;
-    f.inv_norm = net.inv_norm;
-    f.map = map;
-    f.out = out;
+    a.inv_norm = net.inv_norm;
+    a.map = map;
+    a.out = out;
     return f;
 }
 
@@ -401,6 +414,7 @@ hipError_t launch_fitness(const Net &net, const FitPlan &plan, const DevState &d
         e = hipEventRecord(mid, st);
         if (e != hipSuccess) return e;
     }
+    if (plan.bpr == 1) return hipSuccess;   // (the blocks have finished their rows)
     hipLaunchKernelGGL(k_fit_finalize, finalize_grid(f), dim3(256), 0, st, d.partial, rows,
                        plan.bpr, net.inv_norm, map, out);
     return hipGetLastError();

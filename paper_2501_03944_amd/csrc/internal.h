@@ -136,6 +136,10 @@ struct FitArgs {
     const int32_t *lab;    // [S_pad]
     int bpr, spb;
     float *partial;        // [rows][bpr]
+    // the row's fitness: sum of its partials times inv_norm, at out[map.index(row)]
+    float inv_norm;
+    OutMap map;
+    float *out;
     // FP32 in two FP16 parts: the samples' exponents; whether the sparks lie in the
     // search box, and then the exponent of their weights
     const int32_t *Xe;
@@ -279,9 +283,6 @@ __device__ __forceinline__ Blk own_block()
 // One fitness launch of a job: the kernel's arguments and its finalisation.
 struct FitLaunch {
     FitArgs a;              // a.rows sparks, a.bpr partials each
-    float inv_norm;
-    OutMap map;
-    float *out;
 };
 
 // Per-job arguments of the grouped kernels, in device memory (the job's workspace).

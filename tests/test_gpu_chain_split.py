@@ -27,10 +27,10 @@ def _evaluate(wl, W):
 # widths at and beside the row blocks' edges; 37 inputs end inside a K block, 48 leave
 # half of one; 33 samples leave most of the last slab group empty
 @pytest.mark.parametrize("widths,acts", [
-    ((37, 49, 3), "relu"), ((16, 64, 10), "tanh"), ((48, 255, 16), "relu"), ((20, 113, 2), "gelu"),
-    ((37, 65, 64, 2), "relu"), ((30, 128, 128, 10), "tanh"), ((64, 129, 160, 10), "relu"),
-    ((37, 48, 20, 33, 5), "gelu"), ((32, 96, 96, 96, 10), "relu"), ((32, 112, 97, 112, 10), "tanh"),
-    ((9, 50, 50, 50, 2), "identity")])
+    ((37, 49, 9), "relu"), ((20, 64, 10), "tanh"), ((48, 255, 16), "relu"), ((20, 113, 8), "gelu"),
+    ((37, 65, 64, 11), "relu"), ((30, 128, 128, 10), "tanh"), ((64, 129, 160, 10), "relu"),
+    ((37, 48, 20, 33, 15), "gelu"), ((32, 96, 96, 96, 10), "relu"), ((32, 112, 97, 112, 10), "tanh"),
+    ((29, 50, 50, 50, 12), "identity"), ((9, 50, 50, 50, 2), "identity")])
 @pytest.mark.parametrize("S", [33, 700])
 def test_every_plan(widths, acts, S):
     torch, M = require_gpu()
@@ -55,8 +55,8 @@ def test_every_plan(widths, acts, S):
         assert_fitness_close(y, want, f"{widths} {acts} S={S} plan {i} {info['row_blocks']}")
 
 
-@pytest.mark.parametrize("widths,act", [((37, 60, 3), "relu"), ((20, 200, 2), "tanh"),
-                                        ((48, 50, 64, 1), "gelu"), ((30, 64, 64, 64, 2), "identity")])
+@pytest.mark.parametrize("widths,act", [((37, 60, 9), "relu"), ((20, 200, 8), "tanh"),
+                                        ((48, 50, 64, 10), "gelu"), ((30, 64, 64, 64, 16), "identity")])
 @pytest.mark.parametrize("xs,ws", [(1e-5, 1.0), (1.0, 1e-6), (3e5, 1e-3), (1e6, 2.0), (1.0, 1e4)])
 def test_scales(widths, act, xs, ws):
     """Squared error has no cancellation against its own scale: 1e-5 relative (the FP32
@@ -78,7 +78,7 @@ def test_not_finite(act):
     """An infinite weight, bias, input or activation gives the loss that IEEE arithmetic
     gives (NaN counts as +inf)."""
     in_, hid = 40, 60
-    wl = inputs.random_mlp_problem((in_, hid, 3), (act,), "mse", 70, seed=8)
+    wl = inputs.random_mlp_problem((in_, hid, 9), (act,), "mse", 70, seed=8)
     W = inputs.random_weights(wl.dim, 7, seed=9, lo=-1.0, hi=1.0)
     W[1, in_ * hid + 4] = -np.inf         # b1 of unit 4
     W[2, in_ * hid + 5] = np.inf
