@@ -226,7 +226,7 @@ static bool entry_fits(const Net &net, const KernelEntry &e, double *cost, doubl
 // wavefront, since its duration is the chain of passes a block runs.  Weights in LDS:
 // every block stages them first (about half a pass of the FP32 kernels, a whole one
 // of BF16's), so the least time over the rounds that the chip needs, eight wavefronts
-// per CU at a time: 64 sparks of 64-128-128-10 in FP32 80 -> 59 us, 512 of 32-64-64-10
+// per CU at a time (16 of the narrow networks): 64 sparks of 64-128-128-10 in FP32 80 -> 59 us, 512 of 32-64-64-10
 // in BF16 53 -> 46 us against four blocks per CU.
 static int default_bpr(const Net &net, const KernelEntry &e, int rows)
 {
@@ -235,9 +235,10 @@ static int default_bpr(const Net &net, const KernelEntry &e, int rows)
     if (e.wl) {
         FitPlan tmp{};
         const int fit = (160 * 1024) / std::max(1, lds_layout(net, e, &tmp));
-        const long at_once = (long)std::max(1, net.num_cu) * std::max(1, std::min(8 / e.nw, fit));
         int best = 1, widest = 0;
         for (int l = 0; l < net.nl; ++l) widest = std::max(widest, net.fo[l]);
+        const int waves = widest <= 32 ? 16 : 8;
+        const long at_once = (long)std::max(1, net.num_cu) * std::max(1, std::min(waves / e.nw, fit));
         double least = 0.0;
         for (int b = 1; b <= std::min(max_bpr, MAX_BPR); ++b) {
             const int passes = (max_bpr + b - 1) / b;

@@ -279,7 +279,10 @@ __global__ __launch_bounds__(UPDATE_TPB) void k_update(Shape s, DevState d, int 
     if (threadIdx.x != 0) return;
     int32_t pending;
     if (gridDim.x > 1) {
-        __threadfence();
+        // this thread's own flag (select_body) has arrived before it counts itself; the
+        // rows need no fence, they are read by later launches (one would write the L2
+        // back: 2 us)
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
         if (atomicAdd(&d.ctrl[CTRL_COUNT], 1) != (int)gridDim.x - 1) return;
         atomicExch(&d.ctrl[CTRL_COUNT], 0);
         pending = atomicOr(&d.ctrl[CTRL_DONE_PENDING], 0);   // (set by any block)
