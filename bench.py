@@ -32,6 +32,7 @@ if ROOT not in sys.path:
 
 METRIC = "spark-evals/sec & MFMA % peak, BF16 vs FP32 fitness; gen latency p50/p99"
 PEAK_TFLOPS = {"fp32": 157.3, "bf16": 2500.0}   # MI355X dense matrix peaks
+PEAK_SPLIT = 2500.0 / 3     # FP32 as three products of FP16 parts (16-bit units)
 WORKLOAD_TAG = {
     "mlp8-16-1": "mgfwa-mlp8-16-1-tanh-mse-teacher256",
     "mlp64-128-128-10": "mgfwa-mlp64-128-128-10-relu-ce-gmm4096",
@@ -282,18 +283,21 @@ def kernel_roofline(wl, precision, fit_ms, workload_name):
     rows = wl.n_fireworks * wl.n_sparks
     flops = wl.flops_per_eval() * rows
     achieved = flops / (fit_ms / 1e3) / 1e12
-    peak = PEAK_TFLOPS[precision]
+    # wide FP32 networks and register chains from 48 units on run in two FP16 parts
+    testbed = getattr(wl, "net", None) is not None
+    split = (precision == "fp32" and not testbed and max(wl.widths[1:-1], default=0) >= 48 and
+             min(wl.widths[:-1]) >= 20 and wl.widths[-1] >= 8)
+    peak = PEAK_SPLIT if split else PEAK_TFLOPS[precision]
     traffic, traffic_src = measured_traffic(workload_name, precision)
     es = 4 if precision == "fp32" else 2
     wide = workload_name == "mlp784-256-10"
-    testbed = getattr(wl, "net", None) is not None
     if testbed:   # every spark (the network input) once, the fixed parameters once
         alg_bytes = rows * wl.dim * 4 + wl.n_params * 4
-        kernel = "k_net_input / k_net_layer (explosion-spark fitness, fixed network)"
+        kernel = "k_net_narrow / k_net_layer (explosion-spark fitness, fixed network)"
     else:         # every spark's weights once (the wide kernel reads them packed in its
         # own precision), the samples once
         alg_bytes = rows * wl.dim * (es if wide else 4) + wl.n_samples * wl.widths[0] * es
-        kernel = ("k_fit_wide_pipe" if precision == "bf16" else "k_fit_wide32") if wide else "k_fit"
+        kernel = "k_fit_wide" if wide else "k_fit_split" if split else "k_fit"
         kernel += " (explosion-spark fitness)"
     return {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
             "frac": achieved / peak, "traffic": traffic, "traffic_source": traffic_src,
