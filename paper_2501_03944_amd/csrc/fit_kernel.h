@@ -813,7 +813,7 @@ __device__ __forceinline__ void fit_body(const FitArgs &a, int bid)
             }
         }
     }
-    loss.flush();
+    if (a.loss == 1) loss.flush();
     float lsum = loss.total;
     // fixed-order reduction: wavefront butterfly, then the wavefronts in order
 #pragma unroll

@@ -433,7 +433,7 @@ __device__ __forceinline__ void split_body(const FitArgs &a, int bid)
         if (threadIdx.x == 0) store_loss(a, r, c, t);
         return;
     }
-    loss.flush();
+    if (a.loss == 1) loss.flush();
     float lsum = loss.total;
     // fixed-order reduction: wavefront butterfly, then the wavefronts in order
 #pragma unroll
