@@ -1227,7 +1227,7 @@ void fill_plan_info(const mgfwa_ctx *c, const FitPlan &p, int rows, mgfwa_plan_i
         info->blocks_per_row = p.bpr;
         info->samples_per_block = p.spb;
         info->lds_bytes = p.lds_bytes;
-        for (int l = 0; l < MAXL; ++l) info->row_blocks[l] = p.lrows[l] / 16;
+        for (int l = 0; l < MAXL; ++l) info->row_blocks[l] = p.lay.lrows[l] / 16;
     }
 }
 

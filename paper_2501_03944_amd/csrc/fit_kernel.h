@@ -141,21 +141,21 @@ struct WView {
     const char *sp;      // LDS source (WL = true)
     int fi, fo, vec, pitch, n, gq;
 
-    __device__ __forceinline__ WView(const FitArgs &a, const float *w, const char *smem, int l,
-                                     int n_, int g_)
+    __device__ __forceinline__ WView(const FitArgs &a, const LdsLayout &y, const float *w,
+                                     const char *smem, int l, int n_, int g_)
     {
         n = n_;
         gq = g_;
         fi = a.fi[l];
         fo = a.fo[l];
         vec = a.vec[l];
-        pitch = a.lpitch[l];
+        pitch = y.lpitch[l];
         if constexpr (WL) {
             constexpr int es = BF ? 2 : 4;
             // FP32: 16-byte chunk c of row r is stored at chunk c ^ (r & 1) (see
             // stage_weights); the lane's chunk in every K block is 4kb + g
             const int gq = BF ? g_ : (g_ ^ (n & 1));
-            sp = smem + (size_t)(a.lw[l] + n * pitch + 4 * gq) * es;
+            sp = smem + (size_t)(y.lw[l] + n * pitch + 4 * gq) * es;
             gp = nullptr;
         } else {
             gp = w + a.woff[l] + (size_t)n * fi + 4 * g_;
@@ -223,16 +223,17 @@ __device__ __forceinline__ float spark_at(const FitArgs &a, const float *w, int 
     return regen_chunk(a.rg, r, j >> 2)[j & 3];
 }
 
-// Copy the spark's weights into LDS (zero-padded layout) and its biases into
+// Copy the spark's weights into LDS (layout y, zero-padded) and its biases into
 // the FP32 bias area; with a.rg.F the spark (row r) is regenerated instead of read.
 template <bool BF>
-__device__ __forceinline__ void stage_weights(const FitArgs &a, const float *w, int r, char *smem)
+__device__ __forceinline__ void stage_weights(const FitArgs &a, const LdsLayout &y, const float *w, int r,
+                                              char *smem)
 {
-    float *bias = reinterpret_cast<float *>(smem + a.lbias_byte);
+    float *bias = reinterpret_cast<float *>(smem + y.bias_byte);
     const bool regen = a.rg.F != nullptr;
     for (int l = 0; l < a.nl; ++l) {
-        const int fo = a.fo[l], fi = a.fi[l], rows = a.lrows[l], cols = a.lcols[l];
-        const int pitch = a.lpitch[l], base = a.lw[l];
+        const int fo = a.fo[l], fi = a.fi[l], rows = y.lrows[l], cols = y.lcols[l];
+        const int pitch = y.lpitch[l], base = y.lw[l];
         const float *src = w + a.woff[l];
         if (a.vec[l]) {
             // 16-byte loads, four in flight per thread (fi, cols and the row
@@ -268,7 +269,7 @@ __device__ __forceinline__ void stage_weights(const FitArgs &a, const float *w, 
                 }
             }
             for (int o = threadIdx.x; o < rows; o += blockDim.x)
-                bias[a.lb[l] + o] = o < fo ? spark_at(a, w, r, a.boff[l] + o) : 0.0f;
+                bias[y.lb[l] + o] = o < fo ? spark_at(a, w, r, a.boff[l] + o) : 0.0f;
             continue;
         }
         const int n = rows * cols;
@@ -282,7 +283,7 @@ __device__ __forceinline__ void stage_weights(const FitArgs &a, const float *w, 
                 reinterpret_cast<float *>(smem)[base + o * pitch + (k ^ ((o & 1) << 2))] = v;
         }
         for (int o = threadIdx.x; o < rows; o += blockDim.x)
-            bias[a.lb[l] + o] = o < fo ? spark_at(a, w, r, a.boff[l] + o) : 0.0f;
+            bias[y.lb[l] + o] = o < fo ? spark_at(a, w, r, a.boff[l] + o) : 0.0f;
     }
     __syncthreads();
 }
@@ -563,15 +564,15 @@ __device__ __forceinline__ void add_act(floatx4 (&h)[P][R], const floatx4 (&bb)[
 
 // This lane's biases of layer l (rows 16rb + 4g .. +3 of every output block).
 template <bool WL, int R>
-__device__ __forceinline__ void load_bias(const FitArgs &a, const float *w, const char *smem, int l,
-                                          int g, floatx4 (&bb)[R])
+__device__ __forceinline__ void load_bias(const FitArgs &a, const LdsLayout &y, const float *w,
+                                          const char *smem, int l, int g, floatx4 (&bb)[R])
 {
     const int fo = a.fo[l];
 #pragma unroll
     for (int rb = 0; rb < R; ++rb) {
         if constexpr (WL) {
-            bb[rb] = *reinterpret_cast<const floatx4 *>(smem + a.lbias_byte +
-                                                        (size_t)(a.lb[l] + 16 * rb + 4 * g) * 4);
+            bb[rb] = *reinterpret_cast<const floatx4 *>(smem + y.bias_byte +
+                                                        (size_t)(y.lb[l] + 16 * rb + 4 * g) * 4);
         } else {
             const float *bias = w + a.boff[l];
 #pragma unroll
@@ -585,12 +586,25 @@ __device__ __forceinline__ void load_bias(const FitArgs &a, const float *w, cons
 
 // Bias then activation of layer l.  ACT >= 0 fixes the hidden activation at
 // compile time; ACT < 0 dispatches once per call on the runtime code.
-template <int ACT, bool WL, int P, int R>
-__device__ __forceinline__ void bias_act(const FitArgs &a, const float *w, const char *smem, int l,
-                                         int g, bool apply_act, floatx4 (&h)[P][R])
+// MASK: units past the layer's width are zero whatever the inputs are (an infinite input
+// times their zero weights would be a NaN).
+template <int ACT, bool WL, bool MASK, int P, int R>
+__device__ __forceinline__ void bias_act(const FitArgs &a, const LdsLayout &y, const float *w,
+                                         const char *smem, int l, int g, bool apply_act,
+                                         floatx4 (&h)[P][R])
 {
     floatx4 bb[R];
-    load_bias<WL, R>(a, w, smem, l, g, bb);
+    load_bias<WL, R>(a, y, w, smem, l, g, bb);
+    if constexpr (MASK) {
+#pragma unroll
+        for (int rb = 0; rb < R; ++rb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (16 * rb + 4 * g + v >= a.fo[l]) {
+#pragma unroll
+                    for (int p = 0; p < P; ++p) h[p][rb][v] = 0.0f;
+                }
+    }
     if (!apply_act) {
         add_act<0, P, R>(h, bb);
         return;
@@ -747,75 +761,15 @@ __device__ __forceinline__ void store_loss(const FitArgs &a, int r, int c, float
     if (a.bpr == 1) a.out[a.map.index(r)] = canon_fitness((float)((double)t * (double)a.inv_norm));
 }
 
-// Block `bid` of a fitness launch: spark r = bid / bpr, sample range c = bid % bpr.
-template <bool BF, bool WL, int NW, int P, int ACT, int R1, int R2, int R3, int R4, int SCHED>
-__device__ __forceinline__ void fit_body(const FitArgs &a, int bid)
+// A block's wavefronts' losses, added in a fixed order: the wavefront's butterfly, then
+// the wavefronts in order.
+template <int NW>
+__device__ __forceinline__ void block_loss(const FitArgs &a, int r, int c, LossSum &loss)
 {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ float red[NW];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = lane & 15, g = lane >> 4;
-    const int r = bid / a.bpr, c = bid % a.bpr;
-    const float *w = a.W + (size_t)r * a.ld;
-    if constexpr (WL) stage_weights<BF>(a, w, r, smem);
-    const WView<BF, WL> w0(a, w, smem, 0, n, g), w1(a, w, smem, 1, n, g);
-    const WView<BF, WL> w2(a, w, smem, 2, n, g), w3(a, w, smem, 3, n, g);
-    const int s_begin = c * a.spb;
-    const int s_end = min(s_begin + a.spb, a.S_pad);
-    LossSum loss;
-    for (int s0 = s_begin + wave * 16 * P; s0 < s_end; s0 += NW * 16 * P) {
-        // The staged weights are re-read from LDS for every slab: without this
-        // fence the compiler hoists those reads out of the loop and, short of
-        // registers, spills the whole weight fragment set to scratch memory.
-        asm volatile("" ::: "memory");
-        // (ahead of the products where the registers allow it)
-        int lab[P];
-        if constexpr (WL) load_labels(a, s0, n, lab);
-        // FOLD (BF16, zero-addend instances, ReLU): each layer's bias is the
-        // addend of its first K block and the ReLU of a hidden layer is applied
-        // to its BF16-rounded values as the next layer converts them, so no
-        // per-value bias or activation pass runs.
-        constexpr bool FOLD = BF && (SCHED & 2) != 0 && ACT == 1;
-        floatx4 h1[P][R1], c1[R1];
-        if constexpr (FOLD) load_bias<WL, R1>(a, w, smem, 0, g, c1);
-        layer_x<BF, WL, P, R1, SCHED, FOLD>(a, w0, s0, n, g, h1, c1);
-        if constexpr (R2 == 0) {
-            if constexpr (!FOLD) bias_act<ACT, WL, P, R1>(a, w, smem, 0, g, false, h1);
-            if constexpr (!WL) load_labels(a, s0, n, lab);
-            slab_loss<P, R1>(a, 0, s0, n, g, h1, lab, loss);
-        } else {
-            if constexpr (!FOLD) bias_act<ACT, WL, P, R1>(a, w, smem, 0, g, true, h1);
-            floatx4 h2[P][R2], c2[R2];
-            if constexpr (FOLD) load_bias<WL, R2>(a, w, smem, 1, g, c2);
-            layer_h<BF, WL, P, R1, R2, SCHED, FOLD>(w1, h1, h2, c2);
-            if constexpr (R3 == 0) {
-                if constexpr (!FOLD) bias_act<ACT, WL, P, R2>(a, w, smem, 1, g, false, h2);
-                if constexpr (!WL) load_labels(a, s0, n, lab);
-                slab_loss<P, R2>(a, 1, s0, n, g, h2, lab, loss);
-            } else {
-                if constexpr (!FOLD) bias_act<ACT, WL, P, R2>(a, w, smem, 1, g, true, h2);
-                floatx4 h3[P][R3], c3[R3];
-                if constexpr (FOLD) load_bias<WL, R3>(a, w, smem, 2, g, c3);
-                layer_h<BF, WL, P, R2, R3, SCHED, FOLD>(w2, h2, h3, c3);
-                if constexpr (R4 == 0) {
-                    if constexpr (!FOLD) bias_act<ACT, WL, P, R3>(a, w, smem, 2, g, false, h3);
-                    if constexpr (!WL) load_labels(a, s0, n, lab);
-                    slab_loss<P, R3>(a, 2, s0, n, g, h3, lab, loss);
-                } else {
-                    if constexpr (!FOLD) bias_act<ACT, WL, P, R3>(a, w, smem, 2, g, true, h3);
-                    floatx4 h4[P][R4], c4[R4];
-                    if constexpr (FOLD) load_bias<WL, R4>(a, w, smem, 3, g, c4);
-                    layer_h<BF, WL, P, R3, R4, SCHED, FOLD>(w3, h3, h4, c4);
-                    if constexpr (!FOLD) bias_act<ACT, WL, P, R4>(a, w, smem, 3, g, false, h4);
-                    if constexpr (!WL) load_labels(a, s0, n, lab);
-                    slab_loss<P, R4>(a, 3, s0, n, g, h4, lab, loss);
-                }
-            }
-        }
-    }
     if (a.loss == 1) loss.flush();
     float lsum = loss.total;
-    // fixed-order reduction: wavefront butterfly, then the wavefronts in order
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) lsum += __shfl_xor(lsum, off);
     if (lane == 0) red[wave] = lsum;
@@ -826,6 +780,84 @@ __device__ __forceinline__ void fit_body(const FitArgs &a, int bid)
         for (int i = 1; i < NW; ++i) t += red[i];
         store_loss(a, r, c, t);
     }
+}
+
+// The losses of one slab group: samples s0 .. s0 + 16 P - 1 of the spark whose weights
+// the views read (layout y).
+template <bool BF, bool WL, int P, int ACT, int R1, int R2, int R3, int R4, int SCHED, bool MASK = false>
+__device__ __forceinline__ void slab_group(const FitArgs &a, const LdsLayout &y, const float *w,
+                                           const char *smem, const WView<BF, WL> &w0,
+                                           const WView<BF, WL> &w1, const WView<BF, WL> &w2,
+                                           const WView<BF, WL> &w3, int s0, int n, int g, LossSum &loss)
+{
+    // The staged weights are re-read from LDS for every slab: without this
+    // fence the compiler hoists those reads out of the loop and, short of
+    // registers, spills the whole weight fragment set to scratch memory.
+    asm volatile("" ::: "memory");
+    // (ahead of the products where the registers allow it)
+    int lab[P];
+    if constexpr (WL) load_labels(a, s0, n, lab);
+    // FOLD (BF16, zero-addend instances, ReLU): each layer's bias is the
+    // addend of its first K block and the ReLU of a hidden layer is applied
+    // to its BF16-rounded values as the next layer converts them, so no
+    // per-value bias or activation pass runs.
+    constexpr bool FOLD = BF && (SCHED & 2) != 0 && ACT == 1;
+    floatx4 h1[P][R1], c1[R1];
+    if constexpr (FOLD) load_bias<WL, R1>(a, y, w, smem, 0, g, c1);
+    layer_x<BF, WL, P, R1, SCHED, FOLD>(a, w0, s0, n, g, h1, c1);
+    if constexpr (R2 == 0) {
+        if constexpr (!FOLD) bias_act<ACT, WL, MASK, P, R1>(a, y, w, smem, 0, g, false, h1);
+        if constexpr (!WL) load_labels(a, s0, n, lab);
+        slab_loss<P, R1>(a, 0, s0, n, g, h1, lab, loss);
+    } else {
+        if constexpr (!FOLD) bias_act<ACT, WL, MASK, P, R1>(a, y, w, smem, 0, g, true, h1);
+        floatx4 h2[P][R2], c2[R2];
+        if constexpr (FOLD) load_bias<WL, R2>(a, y, w, smem, 1, g, c2);
+        layer_h<BF, WL, P, R1, R2, SCHED, FOLD>(w1, h1, h2, c2);
+        if constexpr (R3 == 0) {
+            if constexpr (!FOLD) bias_act<ACT, WL, MASK, P, R2>(a, y, w, smem, 1, g, false, h2);
+            if constexpr (!WL) load_labels(a, s0, n, lab);
+            slab_loss<P, R2>(a, 1, s0, n, g, h2, lab, loss);
+        } else {
+            if constexpr (!FOLD) bias_act<ACT, WL, MASK, P, R2>(a, y, w, smem, 1, g, true, h2);
+            floatx4 h3[P][R3], c3[R3];
+            if constexpr (FOLD) load_bias<WL, R3>(a, y, w, smem, 2, g, c3);
+            layer_h<BF, WL, P, R2, R3, SCHED, FOLD>(w2, h2, h3, c3);
+            if constexpr (R4 == 0) {
+                if constexpr (!FOLD) bias_act<ACT, WL, MASK, P, R3>(a, y, w, smem, 2, g, false, h3);
+                if constexpr (!WL) load_labels(a, s0, n, lab);
+                slab_loss<P, R3>(a, 2, s0, n, g, h3, lab, loss);
+            } else {
+                if constexpr (!FOLD) bias_act<ACT, WL, MASK, P, R3>(a, y, w, smem, 2, g, true, h3);
+                floatx4 h4[P][R4], c4[R4];
+                if constexpr (FOLD) load_bias<WL, R4>(a, y, w, smem, 3, g, c4);
+                layer_h<BF, WL, P, R3, R4, SCHED, FOLD>(w3, h3, h4, c4);
+                if constexpr (!FOLD) bias_act<ACT, WL, MASK, P, R4>(a, y, w, smem, 3, g, false, h4);
+                if constexpr (!WL) load_labels(a, s0, n, lab);
+                slab_loss<P, R4>(a, 3, s0, n, g, h4, lab, loss);
+            }
+        }
+    }
+}
+
+// Block `bid` of a fitness launch: spark r = bid / bpr, sample range c = bid % bpr.
+template <bool BF, bool WL, int NW, int P, int ACT, int R1, int R2, int R3, int R4, int SCHED>
+__device__ __forceinline__ void fit_body(const FitArgs &a, int bid)
+{
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = lane & 15, g = lane >> 4;
+    const int r = bid / a.bpr, c = bid % a.bpr;
+    const float *w = a.W + (size_t)r * a.ld;
+    if constexpr (WL) stage_weights<BF>(a, a.lay, w, r, smem);
+    const WView<BF, WL> w0(a, a.lay, w, smem, 0, n, g), w1(a, a.lay, w, smem, 1, n, g);
+    const WView<BF, WL> w2(a, a.lay, w, smem, 2, n, g), w3(a, a.lay, w, smem, 3, n, g);
+    const int s_begin = c * a.spb;
+    const int s_end = min(s_begin + a.spb, a.S_pad);
+    LossSum loss;
+    for (int s0 = s_begin + wave * 16 * P; s0 < s_end; s0 += NW * 16 * P)
+        slab_group<BF, WL, P, ACT, R1, R2, R3, R4, SCHED>(a, a.lay, w, smem, w0, w1, w2, w3, s0, n, g, loss);
+    block_loss<NW>(a, r, c, loss);
 }
 
 template <bool BF, bool WL, int NW, int P, int ACT, int R1, int R2, int R3, int R4, int SCHED = 1>

@@ -21,8 +21,11 @@
 // samples) 3,478 -> 1,350 us; 300 rows x 4,096 samples of it 574 -> 258 us, their error
 // against binary64 5.2e-8 -> 4.5e-8.
 //
-// Samples, weights or activations that are not finite, or whose exponents leave the
-// FP32 range, are scored by slow_losses in FP32 without parts.
+// Slab groups with a sample, a weight or an activation that is not finite, or whose
+// exponents leave the FP32 range, are marked and taken again by FP32 instructions
+// (fit_kernel.h's slab_group) once the block has been through its samples, with the
+// row's FP32 weights staged in place of the parts; values that are not finite thus go
+// the way that they go in the FP32 kernels.
 #pragma once
 
 #include "fit_kernel.h"
@@ -74,9 +77,9 @@ struct SplitView {
     int pitch, plane;
     __device__ __forceinline__ SplitView(const FitArgs &a, const char *smem, int l, int n, int g)
     {
-        pitch = a.lpitch[l];
-        plane = a.lrows[l] * pitch;
-        p = reinterpret_cast<const _Float16 *>(smem) + a.lw[l] + n * pitch + 8 * (g ^ (n & 1));
+        pitch = a.lay.lpitch[l];
+        plane = a.lay.lrows[l] * pitch;
+        p = reinterpret_cast<const _Float16 *>(smem) + a.lay.lw[l] + n * pitch + 8 * (g ^ (n & 1));
     }
     __device__ __forceinline__ void load(int rb, int kb, halfx8 &hi, halfx8 &lo) const
     {
@@ -89,13 +92,13 @@ struct SplitView {
 // The spark's weights as parts into LDS (zero-padded), biases into the FP32 area.
 __device__ __forceinline__ void stage_split(const FitArgs &a, const float *w, int r, char *smem, int wexp)
 {
-    float *bias = reinterpret_cast<float *>(smem + a.lbias_byte);
+    float *bias = reinterpret_cast<float *>(smem + a.lay.bias_byte);
     const bool regen = a.rg.F != nullptr;
     const int nt = blockDim.x;
     for (int l = 0; l < a.nl; ++l) {
-        const int fo = a.fo[l], fi = a.fi[l], rows = a.lrows[l], cols = a.lcols[l];
-        const int pitch = a.lpitch[l], plane = rows * pitch;
-        _Float16 *dst = reinterpret_cast<_Float16 *>(smem) + a.lw[l];
+        const int fo = a.fo[l], fi = a.fi[l], rows = a.lay.lrows[l], cols = a.lay.lcols[l];
+        const int pitch = a.lay.lpitch[l], plane = rows * pitch;
+        _Float16 *dst = reinterpret_cast<_Float16 *>(smem) + a.lay.lw[l];
         const float *src = w + a.woff[l];
         const int n4 = rows * cols / 4;
         const bool vec = a.vec[l] != 0;
@@ -135,18 +138,20 @@ __device__ __forceinline__ void stage_split(const FitArgs &a, const float *w, in
             }
         }
         for (int o = threadIdx.x; o < rows; o += nt)
-            bias[a.lb[l] + o] = o < fo ? spark_at(a, w, r, a.boff[l] + o) : 0.0f;
+            bias[a.lay.lb[l] + o] = o < fo ? spark_at(a, w, r, a.boff[l] + o) : 0.0f;
     }
     __syncthreads();
 }
 
-// The exponent of a row that need not lie in the box; *inf when it has an infinity.
-__device__ __forceinline__ int row_exp(const FitArgs &a, const float *w, bool *inf)
+// The exponent of a row that need not lie in the box; *bad when a value of it is not
+// finite (the same in every thread).
+__device__ __forceinline__ int row_exp(const FitArgs &a, const float *w, bool *bad)
 {
     __shared__ float sm[16];
     const int n = a.boff[a.nl - 1] + a.fo[a.nl - 1];
     float m = 0.0f;
-    const int n4 = n / 4, nt = blockDim.x;      // (NaN takes no part in the maximum)
+    bool inf = false;
+    const int n4 = n / 4, nt = blockDim.x;
     for (int i0 = threadIdx.x; i0 < n4; i0 += 4 * nt) {
         floatx4 v[4];
 #pragma unroll
@@ -155,15 +160,21 @@ __device__ __forceinline__ int row_exp(const FitArgs &a, const float *w, bool *i
 #pragma unroll
         for (int u = 0; u < 4; ++u)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) m = fmaxf(m, fabsf(v[u][e]));
+            for (int e = 0; e < 4; ++e) {
+                m = fmaxf(m, fabsf(v[u][e]));
+                inf |= !(fabsf(v[u][e]) <= 3.4028234e38f);
+            }
     }
-    if ((int)threadIdx.x < n - 4 * n4) m = fmaxf(m, fabsf(w[4 * n4 + threadIdx.x]));
+    if ((int)threadIdx.x < n - 4 * n4) {
+        const float v = fabsf(w[4 * n4 + threadIdx.x]);
+        m = fmaxf(m, v);
+        inf |= !(v <= 3.4028234e38f);
+    }
     for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
     if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = m;
-    __syncthreads();
+    *bad = __syncthreads_or(inf) != 0;
     m = sm[0];
     for (int i = 1; i < (int)(blockDim.x >> 6); ++i) m = fmaxf(m, sm[i]);
-    *inf = m > 3.4028234e38f;
     return split_exp(m);
 }
 
@@ -239,8 +250,8 @@ __device__ __forceinline__ void split_bias_act(const FitArgs &a, const char *sme
     for (int p = 0; p < P; ++p) m[p] = 0.0f;
 #pragma unroll
     for (int rb = 0; rb < R; ++rb) {
-        const floatx4 b = *reinterpret_cast<const floatx4 *>(smem + a.lbias_byte +
-                                                             (size_t)(a.lb[l] + 16 * rb + 4 * g) * 4);
+        const floatx4 b = *reinterpret_cast<const floatx4 *>(smem + a.lay.bias_byte +
+                                                             (size_t)(a.lay.lb[l] + 16 * rb + 4 * g) * 4);
 #pragma unroll
         for (int p = 0; p < P; ++p)
 #pragma unroll
@@ -312,8 +323,8 @@ __device__ __forceinline__ void split_out(const FitArgs &a, const char *smem, in
 {
 #pragma unroll
     for (int rb = 0; rb < R; ++rb) {
-        const floatx4 b = *reinterpret_cast<const floatx4 *>(smem + a.lbias_byte +
-                                                             (size_t)(a.lb[l] + 16 * rb + 4 * g) * 4);
+        const floatx4 b = *reinterpret_cast<const floatx4 *>(smem + a.lay.bias_byte +
+                                                             (size_t)(a.lay.lb[l] + 16 * rb + 4 * g) * 4);
 #pragma unroll
         for (int p = 0; p < P; ++p)
 #pragma unroll
@@ -321,137 +332,121 @@ __device__ __forceinline__ void split_out(const FitArgs &a, const char *smem, in
     }
 }
 
-// The losses of samples [s0, s1) of row r, in FP32 without parts, one sample after the
-// other, a thread per unit; thread 0 returns their sum.  buf: 2 x MAXW floats of LDS.
-__device__ __forceinline__ float slow_losses(const FitArgs &a, const float *w, int r, int s0, int s1, float *buf)
-{
-    float total = 0.0f;
-    for (int s = s0; s < s1 && s < a.S; ++s) {
-        for (int l = 0; l < a.nl; ++l) {
-            const float *in = l == 0 ? a.X + (size_t)s * a.in_pad : buf + (l & 1 ? 0 : MAXW);
-            float *out = buf + (l & 1 ? MAXW : 0);
-            __syncthreads();
-            for (int o = threadIdx.x; o < a.fo[l]; o += blockDim.x) {
-                float z = 0.0f;
-                for (int k = 0; k < a.fi[l]; ++k)
-                    z = __builtin_fmaf(spark_at(a, w, r, a.woff[l] + o * a.fi[l] + k), in[k], z);
-                z += spark_at(a, w, r, a.boff[l] + o);
-                if (l + 1 < a.nl)
-                    z = a.act[l] == 1   ? (z > 0.0f ? z : 0.0f)
-                        : a.act[l] == 2 ? act_c<2>(z)
-                        : a.act[l] == 3 ? act_c<3>(z)
-                                        : z;
-                out[o] = z;
-            }
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            const int fo = a.fo[a.nl - 1];
-            const float *z = buf + ((a.nl - 1) & 1 ? MAXW : 0);
-            float loss = 0.0f;
-            if (a.loss == 0) {
-                for (int o = 0; o < fo; ++o) {
-                    const float e = z[o] - a.Y[(size_t)s * fo + o];
-                    loss = __builtin_fmaf(e, e, loss);
-                }
-            } else {
-                const int label = a.lab[s];
-                float mx = z[0], se = 0.0f, rest = 0.0f;
-                for (int o = 1; o < fo; ++o) mx = z[o] > mx || z[o] != z[o] ? z[o] : mx;
-                for (int o = 0; o < fo; ++o) {
-                    const float e = expf(z[o] - mx);
-                    se += e;
-                    if (o != label) rest += e;
-                }
-                loss = z[label] == mx ? log1pf(rest) : (mx - z[label]) + logf(se);
-            }
-            total += loss;
-        }
-    }
-    return total;
-}
-
 // Layer l of a slab group and those behind it, from its raw products h (their scale
-// 2^-c): activation and the next layer, or the losses.
+// 2^-c): activation and the next layer, or the losses.  False, and no losses, when the
+// parts do not hold an activation of the group (the same in every lane).
 template <int ACT, int P, int R, int RN, int... RR>
-__device__ __forceinline__ void split_chain(const FitArgs &a, const char *smem, int l, int s0, int n, int g,
+__device__ __forceinline__ bool split_chain(const FitArgs &a, const char *smem, int l, int s0, int n, int g,
                                             int wexp, float (&c)[P], floatx4 (&h)[P][R],
-                                            const int (&lab)[P], LossSum &loss, bool &bad)
+                                            const int (&lab)[P], LossSum &loss, bool ok)
 {
     if constexpr (RN == 0) {
+        if (!__all(ok)) return false;
         split_out<P, R>(a, smem, l, g, c, h);
         slab_loss<P, R>(a, l, s0, n, g, h, lab, loss);
+        return true;
     } else {
         Parts x[(R + 1) / 2][P];
         int e[P];
-        bad |= !split_act<ACT, P, R>(a, smem, l, g, c, h, e, x);
+        ok &= split_act<ACT, P, R>(a, smem, l, g, c, h, e, x);
 #pragma unroll
         for (int p = 0; p < P; ++p) c[p] = __builtin_ldexpf(1.0f, -(e[p] + wexp));
         floatx4 out[P][RN];
         const SplitView wv(a, smem, l + 1, n, g);
         split_layer_h(wv, x, out);
-        split_chain<ACT, P, RN, RR..., 0>(a, smem, l + 1, s0, n, g, wexp, c, out, lab, loss, bad);
+        return split_chain<ACT, P, RN, RR..., 0>(a, smem, l + 1, s0, n, g, wexp, c, out, lab, loss, ok);
     }
+}
+
+// One slab group from its inputs on, as split_chain.
+template <int P, int ACT, int R1, int R2, int R3, int R4>
+__device__ __forceinline__ bool split_group(const FitArgs &a, const char *smem, const SplitView &w0, int s0,
+                                            int n, int g, int wexp, LossSum &loss)
+{
+    // re-read the staged weights for every slab (a hoisted fragment set spills)
+    asm volatile("" ::: "memory");
+    int lab[P];
+    load_labels(a, s0, n, lab);
+    bool ok = true;
+    float cx[P], cz[P];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int xe = a.Xe[s0 + 16 * p + n];
+        ok &= xe < XE_BAD / 2 && xe + wexp >= -SPLIT_EMAX;
+        cx[p] = __builtin_ldexpf(1.0f, xe);
+        cz[p] = __builtin_ldexpf(1.0f, -(xe + wexp));
+    }
+    if (!__all(ok)) return false;
+    floatx4 h1[P][R1];
+    split_layer_x<P, R1>(a, w0, s0, n, g, cx, h1);
+    return split_chain<ACT, P, R1, R2, R3, R4>(a, smem, 0, s0, n, g, wexp, cz, h1, lab, loss, true);
+}
+
+// The launch's arguments where they lie in memory.  The redo reads them there, behind an
+// opaque pointer: kept in registers for it, they would spill the slab loop's.
+typedef const __attribute__((address_space(4))) FitArgs *ArgsInMemory;
+
+// Slab groups of a wavefront that its products in parts left out: bit i the i-th, and
+// every one from `rest` on.
+struct Redo {
+    uint64_t marks = 0;
+    int rest = 0x7fffffff;
+    __device__ __forceinline__ bool any() const { return marks != 0 || rest != 0x7fffffff; }
+};
+
+// The losses of the marked slab groups of samples [s0, s_end) with FP32 instructions and
+// weights.
+template <int NW, int P, int ACT, int R1, int R2, int R3, int R4>
+__device__ __forceinline__ void redo_groups(ArgsInMemory k, char *smem, int r, int s0, int s_end,
+                                            const Redo &redo, LossSum &loss)
+{
+    asm volatile("" : "+s"(k));
+    const FitArgs &a = *(const FitArgs *)k;
+    const int n = threadIdx.x & 15, g = (threadIdx.x & 63) >> 4;
+    const float *w = a.W + (size_t)r * a.ld;
+    stage_weights<false>(a, a.lay32, w, r, smem);
+    const WView<false, true> v0(a, a.lay32, w, smem, 0, n, g), v1(a, a.lay32, w, smem, 1, n, g);
+    const WView<false, true> v2(a, a.lay32, w, smem, 2, n, g), v3(a, a.lay32, w, smem, 3, n, g);
+    for (int i = 0; s0 < s_end; s0 += NW * 16 * P, ++i)
+        if (i >= redo.rest || (i < 64 && redo.marks >> i & 1))
+            slab_group<false, true, P, ACT, R1, R2, R3, R4, 1, true>(a, a.lay32, w, smem, v0, v1, v2, v3, s0,
+                                                                     n, g, loss);
 }
 
 // Block `bid` of a fitness launch: spark r = bid / bpr, sample range c = bid % bpr.
 template <int NW, int P, int ACT, int R1, int R2, int R3, int R4>
-__device__ __forceinline__ void split_body(const FitArgs &a, int bid)
+__device__ __forceinline__ void split_body(const FitArgs &a, ArgsInMemory k, int bid)
 {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ float red[NW];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int n = lane & 15, g = lane >> 4;
     const int r = bid / a.bpr, c = bid % a.bpr;
     const float *w = a.W + (size_t)r * a.ld;
-    bool bad = false;
-    const int wexp = a.boxed ? a.wexp : row_exp(a, w, &bad);
+    bool row_bad = false;
+    const int wexp = a.boxed ? a.wexp : row_exp(a, w, &row_bad);
     stage_split(a, w, r, smem, wexp);
     const SplitView w0(a, smem, 0, n, g);
-    const int s_begin = c * a.spb;
-    const int s_end = min(s_begin + a.spb, a.S_pad);
+    const int s_begin = c * a.spb + wave * 16 * P;
+    const int s_end = min(c * a.spb + a.spb, a.S_pad);
     LossSum loss;
-    for (int s0 = s_begin + wave * 16 * P; s0 < s_end && !bad; s0 += NW * 16 * P) {
-        // re-read the staged weights for every slab (a hoisted fragment set spills)
-        asm volatile("" ::: "memory");
-        int lab[P];
-        load_labels(a, s0, n, lab);
-        float cx[P], cz[P];
-#pragma unroll
-        for (int p = 0; p < P; ++p) {
-            const int xe = a.Xe[s0 + 16 * p + n];
-            bad |= xe >= XE_INF / 2 || xe + wexp < -SPLIT_EMAX;
-            cx[p] = __builtin_ldexpf(1.0f, xe);
-            cz[p] = __builtin_ldexpf(1.0f, -(xe + wexp));
+    Redo redo;
+    if (row_bad) redo.rest = 0;
+    for (int s0 = s_begin, i = 0; s0 < s_end && i < redo.rest; s0 += NW * 16 * P, ++i)
+        if (!split_group<P, ACT, R1, R2, R3, R4>(a, smem, w0, s0, n, g, wexp, loss)) {
+            if (i < 64) redo.marks |= 1ull << i;
+            else redo.rest = i;
         }
-        floatx4 h1[P][R1];
-        split_layer_x<P, R1>(a, w0, s0, n, g, cx, h1);
-        split_chain<ACT, P, R1, R2, R3, R4>(a, smem, 0, s0, n, g, wexp, cz, h1, lab, loss, bad);
-    }
-    if (__syncthreads_or(bad)) {
-        const float t = slow_losses(a, w, r, s_begin, s_end, reinterpret_cast<float *>(smem));
-        if (threadIdx.x == 0) store_loss(a, r, c, t);
-        return;
-    }
-    if (a.loss == 1) loss.flush();
-    float lsum = loss.total;
-    // fixed-order reduction: wavefront butterfly, then the wavefronts in order
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) lsum += __shfl_xor(lsum, off);
-    if (lane == 0) red[wave] = lsum;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float t = red[0];
-#pragma unroll
-        for (int i = 1; i < NW; ++i) t += red[i];
-        store_loss(a, r, c, t);
-    }
+    if (__syncthreads_or(redo.any()))
+        redo_groups<NW, P, ACT, R1, R2, R3, R4>(k, smem, r, s_begin, s_end, redo, loss);
+    block_loss<NW>(a, r, c, loss);
 }
 
 template <int NW, int P, int ACT, int R1, int R2, int R3, int R4>
 __global__ __launch_bounds__(NW * 64) void k_fit_split(FitArgs a)
 {
-    split_body<NW, P, ACT, R1, R2, R3, R4>(a, xcd_remap(blockIdx.x, gridDim.x));
+    // (its only argument starts the kernel's argument segment)
+    split_body<NW, P, ACT, R1, R2, R3, R4>(a, (ArgsInMemory)__builtin_amdgcn_kernarg_segment_ptr(),
+                                           xcd_remap(blockIdx.x, gridDim.x));
 }
 
 template <int NW, int P, int ACT, int R1, int R2, int R3, int R4>
@@ -461,7 +456,7 @@ __global__ __launch_bounds__(NW * 64) void k_fit_split_group(GroupTable t, int w
     const int local = blockIdx.x - t.start[j], n = t.gx[j] * t.gy[j];
     if (local >= n) return;   // padding
     const FitArgs a = t.job[j]->fit[which].a;   // a private copy, as in k_fit_group
-    split_body<NW, P, ACT, R1, R2, R3, R4>(a, xcd_remap(local, n));
+    split_body<NW, P, ACT, R1, R2, R3, R4>(a, (ArgsInMemory)&t.job[j]->fit[which].a, xcd_remap(local, n));
 }
 
 #define FIT_ENTRY_SPLIT(NW, P, ACT, R1, R2, R3, R4)                                          \

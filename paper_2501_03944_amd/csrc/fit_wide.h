@@ -105,7 +105,7 @@ struct WideArgs {
     float *partial;        // [rows][ntn]
     int gs;                // sparks per XCD tile group
     int hid;               // hidden width
-    const int32_t *Xe;     // two FP16 parts: [S_pad] sample exponents (XE_INF: the sample has an infinity),
+    const int32_t *Xe;     // two FP16 parts: [S_pad] sample exponents (XE_BAD: a value is not finite),
                            // then whether any sample has one
 };
 
@@ -538,7 +538,7 @@ __device__ __forceinline__ float wave_sum_lane0(float v)
 
 constexpr int LABEL_SKIP = -2;     // the sample's loss is not taken here (k_wide_finalize adds it)
 
-__device__ __forceinline__ int sample_exp(int xe) { return xe >= XE_INF / 2 ? xe - XE_INF : xe; }
+__device__ __forceinline__ int sample_exp(int xe) { return xe >= XE_BAD / 2 ? xe - XE_BAD : xe; }
 
 // What the lane that scores sample s of spark row r in the epilogue needs, fetched
 // early (its load latency would otherwise sit in the epilogue): the label, and with
@@ -558,7 +558,7 @@ __device__ __forceinline__ LaneSample lane_sample(const WideArgs &a, int r, int 
         const int32_t *t = wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp);
         const int xe = a.Xe[s];
         ls.e = t[0] + sample_exp(xe);
-        if (t[1] || xe >= XE_INF / 2) ls.label = LABEL_SKIP;
+        if (t[1] || xe >= XE_BAD / 2) ls.label = LABEL_SKIP;
     }
     return ls;
 }
@@ -1062,7 +1062,7 @@ __global__ __launch_bounds__(256) void k_wide_finalize(WideArgs a, float inv_nor
             __shared__ float red[256];
             for (int s0 = 0; s0 < a.S; s0 += 256) {
                 const int s = s0 + threadIdx.x;
-                red[threadIdx.x] = s < a.S && (row_inf || a.Xe[s] >= XE_INF / 2) ? slow_loss<ACT>(a, r, s)
+                red[threadIdx.x] = s < a.S && (row_inf || a.Xe[s] >= XE_BAD / 2) ? slow_loss<ACT>(a, r, s)
                                                                           : 0.0f;
                 __syncthreads();
                 if (threadIdx.x == 0)

@@ -234,7 +234,7 @@ __global__ __launch_bounds__(TPB) void k_pack_wide_x_f16x2(const float *__restri
     float v = 0.0f;
     if (s < S) v = k < in ? x[(size_t)s * in + k] : (k == in ? 1.0f : 0.0f);
     const int xe = Xe[s];
-    const SplitF16 p = split_f16(v, xe >= XE_INF / 2 ? xe - XE_INF : xe);
+    const SplitF16 p = split_f16(v, xe >= XE_BAD / 2 ? xe - XE_BAD : xe);
     const size_t plane = (size_t)WT_N * Kp;
     _Float16 *hi = reinterpret_cast<_Float16 *>(Xw) + (size_t)(s / WT_N) * 2 * plane;
     const size_t at = ((size_t)(k / WT_K) * WT_N + s % WT_N) * WT_K + k % WT_K;

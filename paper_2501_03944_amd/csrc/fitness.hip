@@ -90,27 +90,27 @@ __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ x, const
 __global__ void k_clear_word(int32_t *p) { *p = 0; }
 
 // Exponent of every sample's inputs (and the constant 1 of a folded bias): one
-// wavefront per sample; a sample with an infinity is marked and raises the flag
-// behind the exponents.
+// wavefront per sample; a sample with a value that is not finite is marked and raises
+// the flag behind the exponents.
 __global__ __launch_bounds__(256) void k_sample_exp(const float *__restrict__ x, int S, int S_pad, int in,
                                                     int32_t *__restrict__ Xe)
 {
     const int s = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (s >= S_pad) return;
     float m = 1.0f;
-    int inf = 0;
+    int bad = 0;
     for (int k = lane; s < S && k < in; k += 64) {
         const float v = fabsf(x[(size_t)s * in + k]);
-        if (v <= 3.4028234e38f) m = fmaxf(m, v);   // finite (NaN takes no part)
-        else if (v == __builtin_huge_valf()) inf = 1;
+        if (v <= 3.4028234e38f) m = fmaxf(m, v);
+        else bad = 1;
     }
     for (int off = 32; off > 0; off >>= 1) {
         m = fmaxf(m, __shfl_xor(m, off));
-        inf |= __shfl_xor(inf, off);
+        bad |= __shfl_xor(bad, off);
     }
     if (lane != 0) return;
-    Xe[s] = split_exp(m) + (inf ? XE_INF : 0);
-    if (inf) atomicOr(&Xe[S_pad], 1);
+    Xe[s] = split_exp(m) + (bad ? XE_BAD : 0);
+    if (bad) atomicOr(&Xe[S_pad], 1);
 }
 
 const KernelEntry *(*const kTables[])(int *) = {
@@ -123,22 +123,23 @@ const KernelEntry *(*const kTables[])(int *) = {
 
 int fit_max_bpr() { return MAX_BPR; }
 
-// LDS layout of the staged weights for kernel entry e; returns the byte size.
-static int lds_layout(const Net &net, const KernelEntry &e, FitPlan *p)
+// LDS layout of the staged weights for kernel entry e (split: of its FP16 parts, or of
+// FP32 weights); returns the byte size.
+static int lds_layout(const Net &net, const KernelEntry &e, LdsLayout *p, bool split)
 {
-    const int es = e.bf16 || e.split ? 2 : 4;   // bytes per stored element (split: per part)
+    const int es = e.bf16 || split ? 2 : 4;   // bytes per stored element (split: per part)
     // pitch padding in elements: BF16 16 bytes; FP32 32 bytes (a pitch of 2 mod 8
     // 16-byte chunks, with the row-parity chunk swizzle of the kernel)
     // split: a pitch of 2 (mod 4) 16-byte chunks, with the same swizzle
-    const int unit = e.split ? 16 : 8;
+    const int unit = split ? 16 : 8;
     int off = 0, boff = 0;
     for (int l = 0; l < MAXL; ++l) {
         p->lw[l] = p->lpitch[l] = p->lrows[l] = p->lcols[l] = p->lb[l] = 0;
         if (l >= net.nl) continue;
         const int rows = 16 * e.R[l];
         int cols;
-        if (l == 0) cols = e.split ? (net.in_pad + 31) / 32 * 32 : net.in_pad;
-        else cols = e.bf16 || e.split ? 32 * ((e.R[l - 1] + 1) / 2) : 16 * e.R[l - 1];
+        if (l == 0) cols = split ? (net.in_pad + 31) / 32 * 32 : net.in_pad;
+        else cols = e.bf16 || split ? 32 * ((e.R[l - 1] + 1) / 2) : 16 * e.R[l - 1];
         const int pitch = cols + unit;
         off = (off + (16 / es) - 1) / (16 / es) * (16 / es);   // 16-byte aligned layer base
         p->lw[l] = off;
@@ -146,12 +147,29 @@ static int lds_layout(const Net &net, const KernelEntry &e, FitPlan *p)
         p->lrows[l] = rows;
         p->lcols[l] = cols;
         p->lb[l] = boff;
-        off += rows * pitch * (e.split ? 2 : 1);
+        off += rows * pitch * (split ? 2 : 1);
         boff += rows;
     }
-    p->lbias_byte = (off * es + 15) / 16 * 16;
-    p->lds_bytes = p->lbias_byte + boff * 4;
-    return p->lds_bytes;
+    p->bias_byte = (off * es + 15) / 16 * 16;
+    p->bytes = p->bias_byte + boff * 4;
+    return p->bytes;
+}
+
+// Both layouts of kernel entry e; returns the bytes that its blocks take.
+static int lds_layouts(const Net &net, const KernelEntry &e, LdsLayout *lay, LdsLayout *lay32)
+{
+    const int bytes = lds_layout(net, e, lay, e.split != 0);
+    if (!e.split) {
+        *lay32 = LdsLayout{};
+        return bytes;
+    }
+    return std::max(bytes, lds_layout(net, e, lay32, false));
+}
+
+static int lds_bytes(const Net &net, const KernelEntry &e)
+{
+    LdsLayout lay, lay32;
+    return lds_layouts(net, e, &lay, &lay32);
 }
 
 int resident_lds_bytes(const Net &net)
@@ -162,8 +180,7 @@ int resident_lds_bytes(const Net &net)
         e.R[l] = l < net.nl ? (net.fo[l] + 15) / 16 : 0;
         if (net.bf16 && l < net.nl - 1 && (e.R[l] & 1)) e.R[l] += 1;
     }
-    FitPlan p{};
-    return lds_layout(net, e, &p);
+    return lds_bytes(net, e);
 }
 
 // Whether the network may take the register chain in two FP16 parts.  Those (7e-8 of a
@@ -207,8 +224,7 @@ static bool entry_fits(const Net &net, const KernelEntry &e, double *cost, doubl
     }
     if (padded) *padded = c;
     if (e.wl) {
-        FitPlan tmp{};
-        if (lds_layout(net, e, &tmp) > net.lds_max) return false;
+        if (lds_bytes(net, e) > net.lds_max) return false;
         // staged weights beat global fragment loads; run-time activations with more row
         // blocks than twice the network's do not (12-45-1 in GELU, 156 sparks: 23 us a
         // generation from global memory in 4 row blocks, 29 us from LDS in 8)
@@ -233,8 +249,7 @@ static int default_bpr(const Net &net, const KernelEntry &e, int rows)
     const int group = e.nw * 16 * e.P;                    // samples per block pass
     const int max_bpr = (net.S_pad + group - 1) / group;
     if (e.wl) {
-        FitPlan tmp{};
-        const int fit = (160 * 1024) / std::max(1, lds_layout(net, e, &tmp));
+        const int fit = (160 * 1024) / std::max(1, lds_bytes(net, e));
         int best = 1, widest = 0;
         for (int l = 0; l < net.nl; ++l) widest = std::max(widest, net.fo[l]);
         const int waves = widest <= 32 ? 16 : 8;
@@ -275,7 +290,7 @@ static void make_plan(const Net &net, const KernelEntry &e, int rows, int bpr, F
     // sparks of 12-45-1 in GELU: 33 us a generation drawn in the kernel, 23 us stored).
     plan->regen = e.wl && e.act >= 0 && net.nl <= 3;
     plan->rows = rows;
-    lds_layout(net, e, plan);
+    plan->lds_bytes = lds_layouts(net, e, &plan->lay, &plan->lay32);
     if (!e.wl) plan->lds_bytes = 0;
     const int group = e.nw * 16 * e.P;
     int spb = (net.S_pad + bpr - 1) / bpr;
@@ -374,13 +389,9 @@ FitLaunch fit_launch_args(const Net &net, const FitPlan &plan, const DevState &d
         a.boff[l] = net.boff[l];
         a.act[l] = net.act[l];
         a.vec[l] = net.vec[l];
-        a.lw[l] = plan.lw[l];
-        a.lpitch[l] = plan.lpitch[l];
-        a.lrows[l] = plan.lrows[l];
-        a.lcols[l] = plan.lcols[l];
-        a.lb[l] = plan.lb[l];
     }
-    a.lbias_byte = plan.lbias_byte;
+    a.lay = plan.lay;
+    a.lay32 = plan.lay32;
     a.loss = net.loss;
     a.Y = d.Ypad;
     a.lab = d.Lpad;

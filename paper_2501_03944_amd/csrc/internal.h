@@ -40,7 +40,7 @@ struct DevState {
     int32_t *Lpad;     // [S_pad] CE labels (-1 padded)
     char *Wpack;       // packed spark rows for the wide-first-layer kernel
     char *Xw;          // [S_pad][Kp] samples with a ones column (wide kernel)
-    int32_t *Xe;       // [S_pad + 1] exponents of samples in two FP16 parts, any-infinity flag
+    int32_t *Xe;       // [S_pad + 1] exponents of samples in two FP16 parts, any-marked flag
     float *lo, *hi;    // [B][Dp] population ranges (range mapping)
     float *Pnet;       // packed parameters of a fixed network (input problems)
     float *H0, *H1;    // [partial_rows][hnp] activations between layers (input problems)
@@ -117,6 +117,14 @@ struct SparkRegen {
     int lam, N, D, Dp;
 };
 
+// Weights staged in LDS, per layer: weight offset and row pitch in elements of the
+// storage type, padded rows and columns, bias offset (floats); start of the FP32 bias
+// area; size.
+struct LdsLayout {
+    int lw[MAXL], lpitch[MAXL], lrows[MAXL], lcols[MAXL], lb[MAXL];
+    int bias_byte, bytes;
+};
+
 // Arguments of the register-chain fitness kernel (fit_kernel.h).
 struct FitArgs {
     const float *W;        // spark rows
@@ -127,10 +135,8 @@ struct FitArgs {
     int in_pad, S, S_pad;
     int nl;
     int fi[MAXL], fo[MAXL], woff[MAXL], boff[MAXL], act[MAXL], vec[MAXL];
-    // LDS layout (WL kernels), per layer: weight offset and row pitch in
-    // elements of the storage type, padded rows and columns, bias offset (floats)
-    int lw[MAXL], lpitch[MAXL], lrows[MAXL], lcols[MAXL], lb[MAXL];
-    int lbias_byte;        // start of the FP32 bias area
+    LdsLayout lay;         // WL kernels
+    LdsLayout lay32;       // FP32 in two FP16 parts: of the FP32 weights, for redone samples
     int loss;
     const float *Y;        // [S_pad][out]
     const int32_t *lab;    // [S_pad]
@@ -161,9 +167,8 @@ struct FitPlan {
     int bpr;              // blocks per spark row
     int spb;              // samples per block
     int rows;
-    // LDS layout of the staged weights (wl = 1)
-    int lw[MAXL], lpitch[MAXL], lrows[MAXL], lcols[MAXL], lb[MAXL];
-    int lbias_byte, lds_bytes;
+    LdsLayout lay, lay32; // of the staged weights (wl = 1; lay32: split = 1)
+    int lds_bytes;
     int net_shape = -1;   // input problems: NET_* kernel shape (-1 chosen per launch)
 };
 
@@ -410,8 +415,8 @@ dim3 fitness_grid(const FitLaunch &f);     // the job's own grid of the GEMM ker
 dim3 finalize_grid(const FitLaunch &f);
 hipError_t launch_pack_problem(const Net &net, const float *x, const float *y,
                                const int32_t *labels, const DevState &d, hipStream_t st);
-// The samples' exponents and any-infinity flag for FP16 parts, into d.Xe.
-constexpr int XE_INF = 1 << 20;    // Xe of a sample with an infinity: its exponent + XE_INF
+// The samples' exponents and any-marked flag for FP16 parts, into d.Xe.
+constexpr int XE_BAD = 1 << 20;    // Xe of a sample with a value that is not finite: its exponent + XE_BAD
 hipError_t launch_sample_exp(const Net &net, const float *x, int32_t *Xe, hipStream_t st);
 // largest partial-sum count per row any plan may use
 int fit_max_bpr();
