@@ -51,11 +51,14 @@ constexpr size_t ALIGN = 256;
 size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 int round_up(int v, int a) { return (v + a - 1) / a * a; }
 
+// Bytes of the samples in two FP16 parts (register chain).
+size_t split_bytes(const Net &net) { return (size_t)net.S_pad * round_up(net.in_pad, 32) * 4; }
+
 struct Layout {
     size_t F, SE, SG, A, Aexp, Y, Yprev, fresh, Yc, top, bottom, tie, cstar, improved, reinit, src;
     size_t best_x, best_y, best_f, best_gen, best_upd, ctrl, partial, Xp, Xb, Ypad, Lpad;
-    size_t Wpack, Xw, Xe, lo, hi, Pnet, H0, H1, Zero;
-    size_t Wstar, Ystar, Xp32, Wpack32, Xw32, Xe32;   // FP32 re-check of BF16 selection winners
+    size_t Wpack, Xw, Xs, Xe, lo, hi, Pnet, H0, H1, Zero;
+    size_t Wstar, Ystar, Xp32, Wpack32, Xw32, Xs32, Xe32;   // FP32 re-check of BF16 selection winners
     size_t desc;                                // the job's descriptor for grouped launches
     size_t total;
     int partial_rows;
@@ -232,6 +235,7 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
                    (c->fit_path == 2 ||
                     (c->fit_path == 0 && resident_lds_bytes(net) > 160 * 1024 - 512));
         net.wexp = split_exp(std::max(std::fabs(c->lb), std::fabs(c->ub)));
+        net.box_exp = part_exp(std::max(std::fabs(c->lb), std::fabs(c->ub)));
         if (net.wide && net.S_pad / 256 > fit_max_bpr())
             return fail(MGFWA_EUNSUPPORTED, "too many samples for the wide fitness kernel");
     }
@@ -291,6 +295,7 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
     L.Lpad = take(net.loss == MGFWA_LOSS_CE ? (size_t)net.S_pad * 4 : 0);
     L.Wpack = take(net.wide ? (size_t)L.partial_rows * wide_row_bytes(net) : 0);
     L.Xw = take(net.wide ? (size_t)net.S_pad * wide_kp(net) * (net.bf16 ? 2 : 4) : 0);
+    L.Xs = take(!input && chain_split(net) ? split_bytes(net) : 0);
     L.Xe = take(!input && !net.bf16 ? (size_t)(net.S_pad + 1) * 4 : 0);
     L.lo = take(s.map_range ? (size_t)s.B * Dp * 4 : 0);
     L.hi = take(s.map_range ? (size_t)s.B * Dp * 4 : 0);
@@ -304,6 +309,7 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
     L.Xp32 = take(s.recheck && !net.wide ? (size_t)net32.S_pad * net32.in_pad * 4 : 0);
     L.Wpack32 = take(s.recheck && net.wide ? BN * wide_row_bytes(net32) : 0);
     L.Xw32 = take(s.recheck && net.wide ? (size_t)net32.S_pad * wide_kp(net32) * 4 : 0);
+    L.Xs32 = take(s.recheck && chain_split(net32) ? split_bytes(net32) : 0);
     L.Xe32 = take(s.recheck ? (size_t)(net32.S_pad + 1) * 4 : 0);
     L.desc = take(sizeof(JobDesc));
     L.total = off;
@@ -428,7 +434,7 @@ mgfwa_status fit_rows(mgfwa_ctx *c, const FitPlan &plan, const float *W, size_t 
         STEP(launch_fitness_wide(c->net, c->d, W, ld, rows, map, out, st, boxed, mid, pre, prepacked),
              "fitness_wide");
     else
-        STEP(launch_fitness(c->net, plan, c->d, W, ld, rows, map, out, st, boxed, mid, rg), "fitness");
+        STEP(launch_fitness(c->net, plan, c->d, W, ld, rows, map, out, st, mid, rg), "fitness");
     return MGFWA_OK;
 }
 
@@ -440,7 +446,7 @@ mgfwa_status fit_check(mgfwa_ctx *c, const float *W, int rows, float *out, hipSt
         STEP(launch_fitness_wide(c->net32, c->d32, W, c->s.Dp, rows, kFlat, out, st, true),
              "fitness_check_wide");
     else
-        STEP(launch_fitness(c->net32, c->plan_check, c->d32, W, c->s.Dp, rows, kFlat, out, st, true),
+        STEP(launch_fitness(c->net32, c->plan_check, c->d32, W, c->s.Dp, rows, kFlat, out, st),
              "fitness_check");
     return MGFWA_OK;
 }
@@ -676,6 +682,7 @@ mgfwa_status mgfwa_init(mgfwa_ctx **out, const mgfwa_config *config, const mgfwa
     d.Lpad = c->net.loss == MGFWA_LOSS_CE ? at<int32_t>(b, L.Lpad) : nullptr;
     d.Wpack = c->net.wide ? at<char>(b, L.Wpack) : nullptr;
     d.Xw = c->net.wide ? at<char>(b, L.Xw) : nullptr;
+    d.Xs = !c->input && chain_split(c->net) ? at<_Float16>(b, L.Xs) : nullptr;
     d.Xe = !c->input && !c->net.bf16 ? at<int32_t>(b, L.Xe) : nullptr;
     d.lo = c->s.map_range ? at<float>(b, L.lo) : nullptr;
     d.hi = c->s.map_range ? at<float>(b, L.hi) : nullptr;
@@ -693,6 +700,7 @@ mgfwa_status mgfwa_init(mgfwa_ctx **out, const mgfwa_config *config, const mgfwa
         c->d32.Xp = c->net32.wide ? nullptr : at<float>(b, L.Xp32);
         c->d32.Wpack = c->net32.wide ? at<char>(b, L.Wpack32) : nullptr;
         c->d32.Xw = c->net32.wide ? at<char>(b, L.Xw32) : nullptr;
+        c->d32.Xs = chain_split(c->net32) ? at<_Float16>(b, L.Xs32) : nullptr;
         c->d32.Xe = at<int32_t>(b, L.Xe32);
     }
 
@@ -1058,8 +1066,8 @@ extern "C" mgfwa_status mgfwa_evaluate_noalloc(const mgfwa_problem *problem, int
     cfg.n_sparks = 2;
     cfg.sigma = 0.5f;
     cfg.boost = cfg.amp_up = cfg.amp_down = 1.0f;
-    cfg.lb = -1.0f;
-    cfg.ub = 1.0f;
+    cfg.lb = -8.0f;   // (the exponent that rows in parts are tried with first)
+    cfg.ub = 8.0f;
     cfg.max_generations = 1;
     cfg.precision = precision;
     Derived dv;
@@ -1091,10 +1099,15 @@ extern "C" mgfwa_status mgfwa_evaluate_noalloc(const mgfwa_problem *problem, int
     const size_t oXw = take(net.wide ? (size_t)net.S_pad * wide_kp(net) * es : 0);
     const size_t oY = take(net.loss == MGFWA_LOSS_MSE ? (size_t)net.S_pad * outw * 4 : 0);
     const size_t oL = take(net.loss == MGFWA_LOSS_CE ? (size_t)net.S_pad * 4 : 0);
+    const size_t cap = MGFWA_NOALLOC_SCRATCH_BYTES;
+    // (the register chain's samples in parts as well, where they leave room for as many
+    // rows as a launch takes)
+    net.no_parts = !chain_split(net) ||
+                   off + split_bytes(net) + 1024 * (size_t)fit_max_bpr() * 4 + 4 * ALIGN > cap;
+    const size_t oXs = take(net.no_parts ? 0 : split_bytes(net));
     const size_t fixed = off;
     const size_t per_row = net.wide ? wide_row_bytes(net) + (size_t)(net.S_pad / 256) * 4
                                     : (size_t)fit_max_bpr() * 4;
-    const size_t cap = MGFWA_NOALLOC_SCRATCH_BYTES;
     if (fixed + per_row + 2 * ALIGN > cap)
         return fail(MGFWA_EINVAL, "problem too large for the %zu-byte no-allocation scratch "
                                   "(packed samples need %zu bytes, one row %zu)", cap, fixed, per_row);
@@ -1121,6 +1134,7 @@ extern "C" mgfwa_status mgfwa_evaluate_noalloc(const mgfwa_problem *problem, int
     d.Lpad = net.loss == MGFWA_LOSS_CE ? at<int32_t>(base, oL) : nullptr;
     d.partial = at<float>(base, oP);
     d.Wpack = net.wide ? at<char>(base, oW) : nullptr;
+    d.Xs = !net.no_parts ? at<_Float16>(base, oXs) : nullptr;
     d.Xe = !net.bf16 ? at<int32_t>(base, MGFWA_NOALLOC_SCRATCH_BYTES) : nullptr;
     hipStream_t st = static_cast<hipStream_t>(hip_stream);
     // the array keeps the previous call's contents: every byte a launch reads is
@@ -1138,7 +1152,7 @@ extern "C" mgfwa_status mgfwa_evaluate_noalloc(const mgfwa_problem *problem, int
             if (!fit_select(net, nr, &plan))
                 return fail(MGFWA_EUNSUPPORTED, "no compiled fitness kernel covers this MLP shape");
             HIP_TRY(fit_prepare(plan));
-            HIP_TRY(launch_fitness(net, plan, d, wr, (size_t)ld, nr, kFlat, out + r0, st, false));
+            HIP_TRY(launch_fitness(net, plan, d, wr, (size_t)ld, nr, kFlat, out + r0, st));
         }
     }
     return MGFWA_OK;
@@ -1268,7 +1282,7 @@ mgfwa_status tune_plan(mgfwa_ctx *c, int rows, const float *W, OutMap map, int r
             if (e == hipSuccess)
                 e = c->input ? launch_net_input(c->in, cand[i].net_shape, c->d.Pnet, W, c->s.Dp, rows,
                                                 map, c->d.Yc, c->d.H0, c->d.H1, c->d.zero, c->stream)
-                             : launch_fitness(net, cand[i], dv, W, c->s.Dp, rows, map, res, c->stream, true);
+                             : launch_fitness(net, cand[i], dv, W, c->s.Dp, rows, map, res, c->stream);
         }
         if (e == hipSuccess) e = hipEventRecord(e1, c->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
@@ -1367,12 +1381,12 @@ JobDesc job_desc(const mgfwa_ctx *c)
     j.d = c->d;
     const SparkRegen rg = spark_regen(c);
     j.fit[0] = fit_launch_args(c->net, c->plan_expl, c->d, c->d.SE, s.Dp, s.BN * s.lam, expl_map(s),
-                               c->d.Yc, true, s.regen ? &rg : nullptr);
+                               c->d.Yc, s.regen ? &rg : nullptr);
     j.fit[1] = fit_launch_args(c->net, c->plan_guide, c->d, c->d.SG, s.Dp, s.BN * s.G,
-                               OutMap{s.G, s.C, s.lam}, c->d.Yc, true);
+                               OutMap{s.G, s.C, s.lam}, c->d.Yc);
     if (s.recheck)
         j.fit[2] = fit_launch_args(c->net32, c->plan_check, c->d32, c->d.Wstar, s.Dp, s.BN, kFlat,
-                                   c->d.Ystar, true);
+                                   c->d.Ystar);
     return j;
 }
 

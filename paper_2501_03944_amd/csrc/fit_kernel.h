@@ -673,9 +673,11 @@ __device__ __forceinline__ float exp_neg(float x)
 // of the label's logit from the largest one and q the sum of the other classes'
 // exponentials; its four lanes (g = 0..3) hold the same d and q, so the logarithms of
 // four slabs are taken together, lane group g keeping slab g's pair until then (a
-// logarithm per slab was a third of the vector work of a narrow BF16 network).
+// logarithm per slab was a third of the vector work of a narrow BF16 network).  The sum is
+// in binary64: in FP32 its rounding was most of an FP32 fitness' error.
 struct LossSum {
-    float total = 0.0f, d = 0.0f, q = 0.0f;
+    double total = 0.0;
+    float d = 0.0f, q = 0.0f;
     int slot = 0;
     __device__ __forceinline__ void flush()
     {
@@ -766,19 +768,19 @@ __device__ __forceinline__ void store_loss(const FitArgs &a, int r, int c, float
 template <int NW>
 __device__ __forceinline__ void block_loss(const FitArgs &a, int r, int c, LossSum &loss)
 {
-    __shared__ float red[NW];
+    __shared__ double red[NW];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (a.loss == 1) loss.flush();
-    float lsum = loss.total;
+    double lsum = loss.total;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) lsum += __shfl_xor(lsum, off);
     if (lane == 0) red[wave] = lsum;
     __syncthreads();
     if (threadIdx.x == 0) {
-        float t = red[0];
+        double t = red[0];
 #pragma unroll
         for (int i = 1; i < NW; ++i) t += red[i];
-        store_loss(a, r, c, t);
+        store_loss(a, r, c, (float)t);
     }
 }
 

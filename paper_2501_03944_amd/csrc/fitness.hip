@@ -113,6 +113,23 @@ __global__ __launch_bounds__(256) void k_sample_exp(const float *__restrict__ x,
     if (bad) atomicOr(&Xe[S_pad], 1);
 }
 
+// Samples in two FP16 parts (exponents Xe): the hi plane, then the lo plane, every row's
+// 32-column blocks in the order that the lanes read them.  A sample whose inputs the
+// parts do not hold was marked in Xe: its parts are not read.
+__global__ __launch_bounds__(256) void k_pack_split(const float *__restrict__ x, int S, int S_pad, int in,
+                                                    int pitch, const int32_t *__restrict__ Xe,
+                                                    _Float16 *__restrict__ Xs)
+{
+    const size_t tid = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (tid >= (size_t)S_pad * pitch) return;
+    const int s = (int)(tid / pitch), k = (int)(tid % pitch);
+    const float v = s < S && k < in ? x[(size_t)s * in + k] : 0.0f;
+    const size_t at = (size_t)s * pitch + split_pos(k);
+    const ChainParts p = chain_parts(__builtin_ldexpf(v, Xe[s]));
+    Xs[at] = p.hi;
+    Xs[(size_t)S_pad * pitch + at] = p.lo;
+}
+
 const KernelEntry *(*const kTables[])(int *) = {
     table_std,         table_l1,          table_l2,       table_l2_wide,     table_l3,
     table_l3_wide_f32, table_l3_wide_bf16, table_l4_f32,  table_l4_bf16,     table_l4_wide_f32,
@@ -129,9 +146,7 @@ static int lds_layout(const Net &net, const KernelEntry &e, LdsLayout *p, bool s
 {
     const int es = e.bf16 || split ? 2 : 4;   // bytes per stored element (split: per part)
     // pitch padding in elements: BF16 16 bytes; FP32 32 bytes (a pitch of 2 mod 8
-    // 16-byte chunks, with the row-parity chunk swizzle of the kernel)
-    // split: a pitch of 2 (mod 4) 16-byte chunks, with the same swizzle
-    const int unit = split ? 16 : 8;
+    // 16-byte chunks, with the row-parity chunk swizzle of the kernel); split: likewise
     int off = 0, boff = 0;
     for (int l = 0; l < MAXL; ++l) {
         p->lw[l] = p->lpitch[l] = p->lrows[l] = p->lcols[l] = p->lb[l] = 0;
@@ -140,14 +155,14 @@ static int lds_layout(const Net &net, const KernelEntry &e, LdsLayout *p, bool s
         int cols;
         if (l == 0) cols = split ? (net.in_pad + 31) / 32 * 32 : net.in_pad;
         else cols = e.bf16 || split ? 32 * ((e.R[l - 1] + 1) / 2) : 16 * e.R[l - 1];
-        const int pitch = cols + unit;
+        const int pitch = split ? split_pitch(cols) : cols + 8;
         off = (off + (16 / es) - 1) / (16 / es) * (16 / es);   // 16-byte aligned layer base
         p->lw[l] = off;
         p->lpitch[l] = pitch;
         p->lrows[l] = rows;
         p->lcols[l] = cols;
         p->lb[l] = boff;
-        off += rows * pitch * (split ? 2 : 1);
+        off += rows * pitch;
         boff += rows;
     }
     p->bias_byte = (off * es + 15) / 16 * 16;
@@ -190,14 +205,14 @@ int resident_lds_bytes(const Net &net)
 // at 3-58-1, where the first layer's few products are all but exact in FP32, and with few
 // outputs, where fewer logits average it out (5.9e-8 -> 6.2e-8 at 32-128-2, 5.6e-8 ->
 // 6.8e-8 at 20-48-48-3; 5.9e-8 -> 5.8e-8 at 30-96-96-10, 5.3e-8 -> 4.0e-8 at 32-64-10).
-static bool chain_split(const Net &net)
+bool chain_split(const Net &net)
 {
     int widest = 0, narrowest = net.fi[0];
     for (int l = 0; l + 1 < net.nl; ++l) {
         widest = std::max(widest, net.fo[l]);
         narrowest = std::min(narrowest, net.fo[l]);
     }
-    return !net.bf16 && !net.wide && widest >= 48 && narrowest >= 20 && net.fo[net.nl - 1] >= 8;
+    return !net.no_parts && !net.bf16 && !net.wide && widest >= 48 && narrowest >= 20 && net.fo[net.nl - 1] >= 8;
 }
 
 // Whether kernel entry e covers the network; *cost is the model cost used to
@@ -224,7 +239,8 @@ static bool entry_fits(const Net &net, const KernelEntry &e, double *cost, doubl
     }
     if (padded) *padded = c;
     if (e.wl) {
-        if (lds_bytes(net, e) > net.lds_max) return false;
+        // (the parts' kernels hold up to 400 bytes of their own; lds_max leaves 256)
+        if (lds_bytes(net, e) + (e.split ? 256 : 0) > net.lds_max) return false;
         // staged weights beat global fragment loads; run-time activations with more row
         // blocks than twice the network's do not (12-45-1 in GELU, 156 sparks: 23 us a
         // generation from global memory in 4 row blocks, 29 us from LDS in 8)
@@ -368,7 +384,7 @@ hipError_t fit_prepare(const FitPlan &plan)
 }
 
 FitLaunch fit_launch_args(const Net &net, const FitPlan &plan, const DevState &d, const float *W,
-                          size_t ld, int rows, OutMap map, float *out, bool boxed, const SparkRegen *rg)
+                          size_t ld, int rows, OutMap map, float *out, const SparkRegen *rg)
 {
     FitLaunch f;
     FitArgs &a = f.a;
@@ -398,9 +414,9 @@ FitLaunch fit_launch_args(const Net &net, const FitPlan &plan, const DevState &d
     a.bpr = plan.bpr;
     a.spb = plan.spb;
     a.partial = d.partial;
+    a.Xs = d.Xs;
     a.Xe = d.Xe;
-    a.boxed = boxed ? 1 : 0;
-    a.wexp = net.wexp;
+    a.wexp = net.box_exp;
     a.inv_norm = net.inv_norm;
     a.map = map;
     a.out = out;
@@ -411,12 +427,12 @@ dim3 fitness_grid(const FitLaunch &f) { return dim3((unsigned)(f.a.rows * f.a.bp
 dim3 finalize_grid(const FitLaunch &f) { return dim3((unsigned)((f.a.rows + 255) / 256)); }
 
 hipError_t launch_fitness(const Net &net, const FitPlan &plan, const DevState &d, const float *W,
-                          size_t ld, int rows, OutMap map, float *out, hipStream_t st, bool boxed,
+                          size_t ld, int rows, OutMap map, float *out, hipStream_t st,
                           hipEvent_t mid, const SparkRegen *rg)
 {
     if (rows <= 0) return hipSuccess;
     if (rg && !plan.regen) return hipErrorInvalidValue;   // only the staging regenerates
-    FitLaunch f = fit_launch_args(net, plan, d, W, ld, rows, map, out, boxed, rg);
+    FitLaunch f = fit_launch_args(net, plan, d, W, ld, rows, map, out, rg);
     FitArgs &a = f.a;
     void *args[] = {&a};
     hipError_t e = hipLaunchKernel(plan.kernel, dim3((unsigned)(rows * plan.bpr)),
@@ -466,9 +482,13 @@ hipError_t launch_sample_exp(const Net &net, const float *x, int32_t *Xe, hipStr
 hipError_t launch_pack_problem(const Net &net, const float *x, const float *y,
                                const int32_t *labels, const DevState &d, hipStream_t st)
 {
-    if (d.Xe && chain_split(net)) {   // (the wide kernel packs its samples itself)
+    if (d.Xs && chain_split(net)) {   // (the wide kernel packs its samples itself)
         const hipError_t e = launch_sample_exp(net, x, d.Xe, st);
         if (e != hipSuccess) return e;
+        const int pitch = (net.in_pad + 31) / 32 * 32;
+        const size_t blocks = ((size_t)net.S_pad * pitch + 255) / 256;
+        hipLaunchKernelGGL(k_pack_split, dim3((unsigned)blocks), dim3(256), 0, st, x, net.S, net.S_pad,
+                           net.fi[0], pitch, d.Xe, d.Xs);
     }
     const int out = net.fo[net.nl - 1];
     size_t n = (size_t)net.S_pad * net.in_pad;

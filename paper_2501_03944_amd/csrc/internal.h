@@ -40,6 +40,7 @@ struct DevState {
     int32_t *Lpad;     // [S_pad] CE labels (-1 padded)
     char *Wpack;       // packed spark rows for the wide-first-layer kernel
     char *Xw;          // [S_pad][Kp] samples with a ones column (wide kernel)
+    _Float16 *Xs;      // [2][S_pad][in_pad to 32] samples in two FP16 parts (register chain)
     int32_t *Xe;       // [S_pad + 1] exponents of samples in two FP16 parts, any-marked flag
     float *lo, *hi;    // [B][Dp] population ranges (range mapping)
     float *Pnet;       // packed parameters of a fixed network (input problems)
@@ -79,7 +80,9 @@ struct Net {
     float inv_norm;                    // 1/(S*out) for MSE, 1/S for CE
     int lds_max;                       // LDS bytes a block may use (0: weights stay in global)
     int wide;                          // first layer streamed through LDS (two-layer nets)
-    int wexp;                          // FP16 parts: the exponent of weights in the search box
+    int wexp;                          // FP16 parts: the exponent of weights in the search box (wide kernel)
+    int box_exp;                       // the same of the register chain
+    int no_parts;                      // FP32 takes FP32 instructions only
     int num_cu;                        // compute units (persistent grid size)
 };
 
@@ -146,10 +149,11 @@ struct FitArgs {
     float inv_norm;
     OutMap map;
     float *out;
-    // FP32 in two FP16 parts: the samples' exponents; whether the sparks lie in the
-    // search box, and then the exponent of their weights
+    // FP32 in two FP16 parts: the samples so, and their exponents; the exponent that a
+    // row's weights are tried with first, the search box's
+    const _Float16 *Xs;
     const int32_t *Xe;
-    int boxed, wexp;
+    int wexp;
     // Explosion sparks regenerated while staging (rg.F non-null, LDS-staged
     // kernels only); W is then not read.
     SparkRegen rg;
@@ -207,6 +211,49 @@ __host__ __device__ __forceinline__ int split_exp(float bound)
     (void)frexpf(bound, &e);          // bound < 2^e
     return 15 - e;
 }
+
+// Exponent that brings values of up to m in magnitude below 2^15 (15 for zero), within
+// +-PART_EMAX: beyond, they are not held.
+constexpr int PART_EMAX = 60;
+__host__ __device__ __forceinline__ int part_exp(float m)
+{
+    int e = 0;
+    if (m > 3.4028234e38f) return -PART_EMAX;
+    if (m > 0.0f) (void)frexpf(m, &e);          // m < 2^e
+    e = 15 - e;
+    return e > PART_EMAX ? PART_EMAX : e < -PART_EMAX ? -PART_EMAX : e;
+}
+
+// The scale of the lo parts against the hi parts (register chain).
+constexpr float SPLIT_LO_UP = 4096.0f, SPLIT_LO_DOWN = 1.0f / 4096.0f;
+
+// FP16 parts of x: hi + lo / 4096; held: to 2^-23 of x (not so, among others, a value
+// that is not finite, or beyond FP16).
+struct ChainParts {
+    _Float16 hi, lo;
+    bool held;
+};
+__device__ __forceinline__ ChainParts chain_parts(float x)
+{
+    ChainParts p;
+    p.hi = (_Float16)x;
+    const float rest = __builtin_fmaf((float)p.hi, -1.0f, x);
+    p.lo = (_Float16)(rest * SPLIT_LO_UP);
+    p.held = fabsf(__builtin_fmaf((float)p.lo, -SPLIT_LO_DOWN, rest)) <= fabsf(x) * 0x1p-23f;
+    return p;
+}
+
+// Position of element k (of a 32-column block) of an operand in parts, in the order that
+// the chain's lanes read: lane group g takes columns 4g..4g+3 and 16+4g..16+4g+3 as eight
+// consecutive elements.
+__device__ __forceinline__ int split_pos(int k)
+{
+    return (k & ~31) + ((k & 12) << 1) + ((k & 16) >> 2) + (k & 3);
+}
+
+// Row pitch (elements) of weights in parts, hi and lo, of so many padded columns: 2 (mod 8)
+// 16-byte chunks, so that the fragment reads served together hit distinct bank groups.
+__host__ __device__ constexpr int split_pitch(int cols) { return 2 * cols + 16; }
 
 // FP16 parts of v 2^e: hi + lo has 23 of its 24 bits.  An infinity is all hi.
 struct SplitF16 {
@@ -394,15 +441,14 @@ hipError_t fit_prepare(const FitPlan &plan);
 // per (row, block); the finalisation sums them in order.  `mid` (optional) is
 // recorded between the two launches.
 // rg (LDS-staged plans only): the sparks are regenerated, W is not read.
-// boxed: every row lies in the search box.
 hipError_t launch_fitness(const Net &net, const FitPlan &plan, const DevState &d,
                           const float *W, size_t ld, int rows, OutMap map, float *out,
-                          hipStream_t st, bool boxed, hipEvent_t mid = nullptr,
+                          hipStream_t st, hipEvent_t mid = nullptr,
                           const SparkRegen *rg = nullptr);
 // The kernel arguments and finalisation of one fitness launch (what
 // launch_fitness passes), for a grouped launch's job descriptor.
 FitLaunch fit_launch_args(const Net &net, const FitPlan &plan, const DevState &d, const float *W,
-                          size_t ld, int rows, OutMap map, float *out, bool boxed,
+                          size_t ld, int rows, OutMap map, float *out,
                           const SparkRegen *rg = nullptr);
 // Fitness launch `which` of every job of t, all on the same kernel instance
 // (gkernel, nw wavefronts, lds_bytes of dynamic LDS: the most any of them needs;
@@ -420,6 +466,8 @@ constexpr int XE_BAD = 1 << 20;    // Xe of a sample with a value that is not fi
 hipError_t launch_sample_exp(const Net &net, const float *x, int32_t *Xe, hipStream_t st);
 // largest partial-sum count per row any plan may use
 int fit_max_bpr();
+// whether the network may take the register chain in two FP16 parts
+bool chain_split(const Net &net);
 // LDS bytes the resident-weights kernel would need for this network
 int resident_lds_bytes(const Net &net);
 

@@ -7,14 +7,14 @@ namespace fit {
 
 namespace {
 const KernelEntry kEntries[] = {
-    FIT_ENTRY_SPLIT(4, 2, 1, 4, 4, 4, 1),
+    FIT_ENTRY_SPLIT(8, 1, 1, 4, 4, 4, 1),
     FIT_ENTRY_SPLIT(8, 2, 1, 6, 6, 6, 1),
-    FIT_ENTRY_SPLIT(4, 2, -1, 4, 1, 0, 0),
+    FIT_ENTRY_SPLIT(4, 1, -1, 4, 1, 0, 0),
     FIT_ENTRY_SPLIT(8, 1, -1, 8, 1, 0, 0),
     FIT_ENTRY_SPLIT(8, 1, -1, 16, 1, 0, 0),
-    FIT_ENTRY_SPLIT(4, 2, -1, 4, 4, 1, 0),
+    FIT_ENTRY_SPLIT(4, 1, -1, 4, 4, 1, 0),
     FIT_ENTRY_SPLIT(8, 1, -1, 8, 8, 1, 0),
-    FIT_ENTRY_SPLIT(4, 2, -1, 4, 4, 4, 1),
+    FIT_ENTRY_SPLIT(4, 1, -1, 4, 4, 4, 1),
 };
 }  // namespace
 
