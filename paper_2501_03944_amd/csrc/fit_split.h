@@ -507,7 +507,7 @@ __device__ __forceinline__ bool split_group(const FitArgs &a, const char *smem, 
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         const int xe = a.Xe[s0 + 16 * p + n];
-        ok &= xe <= PART_EMAX && xe >= -PART_EMAX;
+        ok &= xe < XE_BAD;
         cz[p] = __builtin_ldexpf(1.0f, -(xe + wexp[0]));
     }
     if (!__all(ok)) return false;

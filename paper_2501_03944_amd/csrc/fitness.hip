@@ -113,6 +113,25 @@ __global__ __launch_bounds__(256) void k_sample_exp(const float *__restrict__ x,
     if (bad) atomicOr(&Xe[S_pad], 1);
 }
 
+// Exponent of every sample's inputs for the register chain, or XE_BAD where the parts do
+// not hold one of them: one wavefront per sample, the largest magnitude, then every value.
+__global__ __launch_bounds__(256) void k_split_exp(const float *__restrict__ x, int S, int S_pad, int in,
+                                                   int32_t *__restrict__ Xe)
+{
+    const int s = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (s >= S_pad) return;
+    const float *row = x + (size_t)s * in;
+    const int n = s < S ? in : 0;
+    float m = 0.0f;
+    for (int k = lane; k < n; k += 64) m = fmaxf(m, fabsf(row[k]));
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off));
+    const int e = part_exp(m);
+    bool held = true;
+    for (int k = lane; k < n; k += 64) held &= chain_parts(__builtin_ldexpf(row[k], e)).held;
+    held = __all(held);
+    if (lane == 0) Xe[s] = held ? e : XE_BAD;
+}
+
 // Samples in two FP16 parts (exponents Xe): the hi plane, then the lo plane, every row's
 // 32-column blocks in the order that the lanes read them.  A sample whose inputs the
 // parts do not hold was marked in Xe: its parts are not read.
@@ -472,8 +491,7 @@ hipError_t launch_finalize_group(const GroupTable &t, int which, hipStream_t st)
 
 hipError_t launch_sample_exp(const Net &net, const float *x, int32_t *Xe, hipStream_t st)
 {
-    if (net.wide)   // (the chain reads the samples' marks only)
-        hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, st, Xe + net.S_pad);
+    hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, st, Xe + net.S_pad);
     hipLaunchKernelGGL(k_sample_exp, dim3((unsigned)((net.S_pad + 3) / 4)), dim3(256), 0, st, x, net.S,
                        net.S_pad, net.fi[0], Xe);
     return hipGetLastError();
@@ -483,8 +501,8 @@ hipError_t launch_pack_problem(const Net &net, const float *x, const float *y,
                                const int32_t *labels, const DevState &d, hipStream_t st)
 {
     if (d.Xs && chain_split(net)) {   // (the wide kernel packs its samples itself)
-        const hipError_t e = launch_sample_exp(net, x, d.Xe, st);
-        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_split_exp, dim3((unsigned)((net.S_pad + 3) / 4)), dim3(256), 0, st, x, net.S,
+                           net.S_pad, net.fi[0], d.Xe);
         const int pitch = (net.in_pad + 31) / 32 * 32;
         const size_t blocks = ((size_t)net.S_pad * pitch + 255) / 256;
         hipLaunchKernelGGL(k_pack_split, dim3((unsigned)blocks), dim3(256), 0, st, x, net.S, net.S_pad,

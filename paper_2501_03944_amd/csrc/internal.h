@@ -462,7 +462,7 @@ dim3 finalize_grid(const FitLaunch &f);
 hipError_t launch_pack_problem(const Net &net, const float *x, const float *y,
                                const int32_t *labels, const DevState &d, hipStream_t st);
 // The samples' exponents and any-marked flag for FP16 parts, into d.Xe.
-constexpr int XE_BAD = 1 << 20;    // Xe of a sample with a value that is not finite: its exponent + XE_BAD
+constexpr int XE_BAD = 1 << 20;    // Xe of a sample that its parts do not hold (wide kernel: + its exponent)
 hipError_t launch_sample_exp(const Net &net, const float *x, int32_t *Xe, hipStream_t st);
 // largest partial-sum count per row any plan may use
 int fit_max_bpr();

@@ -129,3 +129,34 @@ def test_weights_beyond_the_scales():
             w *= np.float32(2.0 ** 80 if l == big else 2.0 ** -40)
             b *= np.float32(2.0 ** -40 if l == 0 else 1.0)
     check(wl, W, "beyond")
+
+
+@pytest.mark.parametrize("widths,act", CHAIN)
+def test_small_inputs(widths, act):
+    """Inputs of s with first-layer weights of 1 / s; and, where the activation commutes
+    with it, everything behind them at the scale of s too."""
+    for s in (1e-3, 1e-6, 1e-8, 1e-10, 1e-12, 1e-25):
+        wl, W = base(widths, act, "mse", rows=2, S=300, x_scale=s)
+        w = next(layers(wl, W[0]))[0]
+        w *= np.float32(1.0 / s)
+        if act != "tanh" and s > 1e-15:
+            wl.y *= np.float32(s)
+            for _, b in layers(wl, W[1]):
+                b *= np.float32(s)
+        check(wl, W, f"inputs of {s}")
+
+
+@pytest.mark.parametrize("widths,act", CHAIN)
+@pytest.mark.parametrize("loss", ["ce", "mse"])
+def test_inputs_of_different_scale(widths, act, loss):
+    """Features of scales far apart, the weights on them as far the other way; and samples
+    that have only their small features."""
+    for s in (1e2, 1e5, 1e9, 1e12):
+        wl, W = base(widths, act, loss, rows=2, S=300)
+        scale = np.ones(widths[0], np.float32)
+        scale[1::3], scale[2::3] = s, 1.0 / s
+        wl.x *= scale
+        for row in W:
+            next(layers(wl, row))[0][:] /= scale
+        wl.x[5::7, 1::3] = 0.0
+        check(wl, W, f"features {s}")
