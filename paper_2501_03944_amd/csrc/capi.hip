@@ -234,7 +234,6 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
         net.wide = need_data && wide_applicable(net) &&
                    (c->fit_path == 2 ||
                     (c->fit_path == 0 && resident_lds_bytes(net) > 160 * 1024 - 512));
-        net.wexp = split_exp(std::max(std::fabs(c->lb), std::fabs(c->ub)));
         net.box_exp = part_exp(std::max(std::fabs(c->lb), std::fabs(c->ub)));
         if (net.wide && net.S_pad / 256 > fit_max_bpr())
             return fail(MGFWA_EUNSUPPORTED, "too many samples for the wide fitness kernel");
@@ -296,7 +295,7 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
     L.Wpack = take(net.wide ? (size_t)L.partial_rows * wide_row_bytes(net) : 0);
     L.Xw = take(net.wide ? (size_t)net.S_pad * wide_kp(net) * (net.bf16 ? 2 : 4) : 0);
     L.Xs = take(!input && chain_split(net) ? split_bytes(net) : 0);
-    L.Xe = take(!input && !net.bf16 ? (size_t)(net.S_pad + 1) * 4 : 0);
+    L.Xe = take(!input && !net.bf16 ? (size_t)(net.S_pad + net.S_pad / 256) * 4 : 0);
     L.lo = take(s.map_range ? (size_t)s.B * Dp * 4 : 0);
     L.hi = take(s.map_range ? (size_t)s.B * Dp * 4 : 0);
     L.Pnet = take(input && need_data ? (size_t)in.n_packed * (in.frag ? 8 : 4) : 0);
@@ -310,7 +309,7 @@ mgfwa_status derive(const mgfwa_config *c, const mgfwa_problem *p, Derived *out)
     L.Wpack32 = take(s.recheck && net.wide ? BN * wide_row_bytes(net32) : 0);
     L.Xw32 = take(s.recheck && net.wide ? (size_t)net32.S_pad * wide_kp(net32) * 4 : 0);
     L.Xs32 = take(s.recheck && chain_split(net32) ? split_bytes(net32) : 0);
-    L.Xe32 = take(s.recheck ? (size_t)(net32.S_pad + 1) * 4 : 0);
+    L.Xe32 = take(s.recheck ? (size_t)(net32.S_pad + net32.S_pad / 256) * 4 : 0);
     L.desc = take(sizeof(JobDesc));
     L.total = off;
     if (s.lag && L.SG != L.SE + BN * s.lam * Dp * 4)
@@ -422,8 +421,7 @@ SparkRegen spark_regen(const mgfwa_ctx *c)
 
 mgfwa_status fit_rows(mgfwa_ctx *c, const FitPlan &plan, const float *W, size_t ld, int rows,
                       OutMap map, float *out, hipStream_t st, hipEvent_t mid = nullptr,
-                      hipEvent_t pre = nullptr, int prepacked = 0, const SparkRegen *rg = nullptr,
-                      bool boxed = true)
+                      hipEvent_t pre = nullptr, int prepacked = 0, const SparkRegen *rg = nullptr)
 {
     if (c->input) {
         STEP(launch_net_input(c->in, plan.net_shape, c->d.Pnet, W, ld, rows, map, out, c->d.H0,
@@ -431,7 +429,7 @@ mgfwa_status fit_rows(mgfwa_ctx *c, const FitPlan &plan, const float *W, size_t 
              "fitness_input");
         if (mid) STEP(hipEventRecord(mid, st), "event");
     } else if (c->net.wide)
-        STEP(launch_fitness_wide(c->net, c->d, W, ld, rows, map, out, st, boxed, mid, pre, prepacked),
+        STEP(launch_fitness_wide(c->net, c->d, W, ld, rows, map, out, st, mid, pre, prepacked),
              "fitness_wide");
     else
         STEP(launch_fitness(c->net, plan, c->d, W, ld, rows, map, out, st, mid, rg), "fitness");
@@ -443,7 +441,7 @@ mgfwa_status fit_rows(mgfwa_ctx *c, const FitPlan &plan, const float *W, size_t 
 mgfwa_status fit_check(mgfwa_ctx *c, const float *W, int rows, float *out, hipStream_t st)
 {
     if (c->net32.wide)
-        STEP(launch_fitness_wide(c->net32, c->d32, W, c->s.Dp, rows, kFlat, out, st, true),
+        STEP(launch_fitness_wide(c->net32, c->d32, W, c->s.Dp, rows, kFlat, out, st),
              "fitness_check_wide");
     else
         STEP(launch_fitness(c->net32, c->plan_check, c->d32, W, c->s.Dp, rows, kFlat, out, st),
@@ -905,7 +903,7 @@ mgfwa_status mgfwa_evaluate(mgfwa_ctx *c, const float *w, int rows, int ld, floa
             HIP_TRY(fit_prepare(plan));
         }
         mgfwa_status r = fit_rows(c, plan, w + (size_t)r0 * ld, (size_t)ld, nr, kFlat, out + r0,
-                                  c->stream, nullptr, nullptr, 0, nullptr, false);
+                                  c->stream);
         if (r) return r;
     }
     return MGFWA_OK;
@@ -1146,7 +1144,7 @@ extern "C" mgfwa_status mgfwa_evaluate_noalloc(const mgfwa_problem *problem, int
         const int nr = std::min(chunk, rows - r0);
         const float *wr = w + (size_t)r0 * ld;
         if (net.wide) {
-            HIP_TRY(launch_fitness_wide(net, d, wr, (size_t)ld, nr, kFlat, out + r0, st, false));
+            HIP_TRY(launch_fitness_wide(net, d, wr, (size_t)ld, nr, kFlat, out + r0, st));
         } else {
             FitPlan plan{};
             if (!fit_select(net, nr, &plan))

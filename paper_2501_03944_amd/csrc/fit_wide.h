@@ -25,24 +25,36 @@
 //             ahead and the last row block reads the next step's first fragments.
 //             Past the last tile the look-ahead re-loads the last step (16-bit: so
 //             its wait counts are constants);
-//  * FP32 from 128 columns on: every operand is split into two FP16 parts,
-//             v 2^e = hi + lo (an exponent e per spark row and per sample,
-//             split_exp), and a tile runs k_fit_wide's loop over its K once per
-//             product of two parts, the small products first: W_lo X_hi, W_hi X_lo,
-//             W_hi X_hi.  The FP32 matrix rate (157 TFLOP/s) bounds a direct FP32
-//             product (k_fit_wide32 reached 0.91 of it); FP16 runs 16x faster, so
-//             three passes have a bound of 833 TFLOP/s.  Precision: two parts hold
-//             23 bits, and the dropped lo-lo product is below 2^-24 of its term
-//             (together 7e-8 rms of a pre-activation); but the running sum at its
-//             full size is rounded once per 32 columns instead of once per few
-//             columns, which from 128 columns on makes the error no larger than
-//             with FP32 instructions (rms at 800 columns, 20 % dense and dense
-//             inputs: 1.4e-7 against 2.3e-7 and 5.1e-7).  A generation of 784-256-10
-//             with 4,096 sparks x 8,192 samples takes 31.4 ms so, 98.4 ms with FP32
-//             instructions; the fitness' error against binary64 9e-8 -> 3e-8.  Below 128 columns it would
-//             be larger, and k_fit_wide32 stays (networks that narrow come here
-//             only by fit_path).  Infinite inputs or weights (the products of their
-//             parts cancel to NaN) are left to the finalisation (slow_loss);
+//  * FP32 from 128 columns on: every operand is two FP16 parts of the value times a
+//             power of two, v 2^e = hi + lo 2^-12 (e: one exponent for a spark's W1 and b1,
+//             one for a sample's inputs and the constant 1), and a tile runs k_fit_wide's
+//             loop over its K once per product of two parts: W_lo X_hi and W_hi X_lo, then
+//             the accumulators are brought down by 2^12, then W_hi X_hi.  The FP32 matrix
+//             rate (157 TFLOP/s) bounds a direct FP32 product (k_fit_wide32 reaches 0.91 of
+//             it); FP16 runs 16x faster, so three passes have a bound of 833 TFLOP/s.
+//             Precision: a value is held to a last bit of FP32 (2^-23) and the dropped
+//             lo-lo product is below 2^-24 of its term; but the running sum at its full
+//             size is rounded once per 32 columns instead of once per few columns, which
+//             from 128 columns on makes the error no larger than with FP32 instructions
+//             (rms at 800 columns, 20 % dense and dense inputs: 1.4e-7 against 2.3e-7 and
+//             5.1e-7).  Below 128 columns it would be larger, and k_fit_wide32 stays
+//             (networks that narrow come here only by fit_path).
+//  * range:   values that share an exponent are held so over 2^29 (without the scale of the
+//             lo parts it would be 2^17, less than the weights of one spark span).  A spark
+//             or a sample with a value further below its largest, an infinity or a NaN is
+//             never rounded: its row, or its tile of 256 samples, is `raw`, the planes being
+//             the halves of its FP32 values (zeros are zeros in both forms, so the padding
+//             serves both).  k_fit_wide leaves out the tiles of raw operands, and a second
+//             launch, k_fit_wide32 on planes, takes them with FP32 instructions, joining the
+//             values in the shadow of the multiplies.  Explosion sparks, whose parts are on
+//             the box's exponent, are looked at again when that fails (k_explode_fix).
+//             Of uniform weights in the box about one spark of 784-256-10 in two thousand
+//             is raw.
+//             Measured at 784-256-10: a generation of 4,096 sparks x 8,192 samples 31.9 ms
+//             (98.4 ms with FP32 instructions; 31.2 ms with the lo parts on the scale of the
+//             hi parts, right over 2^17 only), the fitness' error against binary64 9e-8 ->
+//             3e-8.  512 rows x 8,192 samples 4.5 ms; with one raw row 4.8, one raw sample
+//             5.0, all raw 14.2 (the same with FP32 operands 12.1).
 //  * swizzle: a 16-byte chunk c of tile row r lives at chunk c ^ s(r), with
 //             s(r) = (r >> 1) & 3 for 64-byte rows (16-bit) and r & 7 for
 //             128-byte rows (FP32).  A 16-byte LDS read serves eight lanes at a time,
@@ -73,9 +85,9 @@
 //   [.., + 16*256*es)       W2[16][256] (FP32, or BF16 with each 32-column block
 //                           stored in the order the MFMA lanes consume it)
 //   [.., + 16*4)            b2[16] (FP32)
-//   [.., + 2*4)             two FP16 parts: the row's exponent, 1 if W1aug has an infinity
-// Packed samples: [S_pad/256] tiles of [Kp/32][256][32] (two FP16 parts: the hi plane,
-// then the lo plane of each tile), with a ones column `in`.
+//   [.., + 2*4)             two planes: the row's exponent, whether it is raw
+// Packed samples: [S_pad/256] tiles of [Kp/32][256][32] (two planes: the hi plane, then the
+// lo plane of each tile), with a ones column `in`.
 #pragma once
 
 #include "fit_kernel.h"
@@ -89,7 +101,6 @@ constexpr int WT_K = 32;    // input columns per K step
 constexpr int WT_NW = 4;    // wavefronts per block
 
 typedef __attribute__((address_space(3))) void lds_void_t;
-typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
 
 struct WideArgs {
     const char *Wp;        // packed spark rows
@@ -105,8 +116,7 @@ struct WideArgs {
     float *partial;        // [rows][ntn]
     int gs;                // sparks per XCD tile group
     int hid;               // hidden width
-    const int32_t *Xe;     // two FP16 parts: [S_pad] sample exponents (XE_BAD: a value is not finite),
-                           // then whether any sample has one
+    const int32_t *Xe;     // two planes: [S_pad] sample exponents, [ntn] whether a tile is raw
 };
 
 constexpr int ZP = 20;      // LDS pitch (floats) of a sample's logits in the loss exchange
@@ -163,7 +173,9 @@ __device__ __forceinline__ int x_tile(const WideArgs &a, int v)
 struct TileIter {
     int xcd, j, bx, gs, ntn, rows;
     int cj, ngx, cw;           // tiles per group for this block, groups here, cols per round
-    __device__ __forceinline__ void setup()
+    __device__ __forceinline__ explicit TileIter(const WideArgs &a)
+        : xcd(blockIdx.x % 8), j(blockIdx.x / 8), bx((gridDim.x - xcd + 7) / 8), gs(a.gs), ntn(a.ntn),
+          rows(a.rows)
     {
         const int t = gs * ntn;
         cj = j < t ? (t - 1 - j) / bx + 1 : 0;
@@ -186,6 +198,56 @@ struct TileIter {
         const int sp = rem / cw;
         *r = grp * gs + sp;
         *col = cb * cw + (rem - sp * cw);
+    }
+};
+
+// All tiles in turn, spark by spark, the sample tiles of a spark turned by one from each
+// round of the blocks to the next: whether the tiles to be taken are those of a few sparks
+// or of one sample tile, they are spread over the blocks.
+struct SpreadIter {
+    int first, blocks, ntn, ntiles;
+    __device__ __forceinline__ explicit SpreadIter(const WideArgs &a)
+        : first(xcd_remap(blockIdx.x, gridDim.x)), blocks(gridDim.x), ntn(a.ntn), ntiles(a.rows * a.ntn)
+    {
+    }
+    __device__ __forceinline__ int count() const
+    {
+        return first < ntiles ? (ntiles - 1 - first) / blocks + 1 : 0;
+    }
+    __device__ __forceinline__ void tile(int i, int *r, int *col) const
+    {
+        const int t = first + i * blocks, row = t / ntn;
+        *r = row;
+        *col = (t - row * ntn + row * ntn / blocks) % ntn;
+    }
+};
+
+// The block's tiles in turn; of two planes (FILTER), those where the row or the sample
+// tile is raw (RAW) or those where neither is, looked up 64 at a time.
+template <bool FILTER, bool RAW>
+struct TileScan {
+    uint64_t mask = 0;     // tiles at - 64 .. at - 1 still to come
+    int at = 0;
+    template <class Iter>
+    __device__ __forceinline__ int next(const WideArgs &a, const Iter &it, int ntiles)
+    {
+        if constexpr (!FILTER) return at < ntiles ? at++ : ntiles;
+        while (!mask) {
+            if (at >= ntiles) return ntiles;
+            const int i = at + (threadIdx.x & 63);
+            bool mine = false;
+            if (i < ntiles) {
+                int r, col;
+                it.tile(i, &r, &col);
+                const bool raw = (wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp)[1] | a.Xe[a.S_pad + col]) != 0;
+                mine = raw == RAW;
+            }
+            mask = __ballot(mine);
+            at += 64;
+        }
+        const int i = at - 64 + __builtin_ctzll(mask);
+        mask &= mask - 1;
+        return __builtin_amdgcn_readfirstlane(i);
     }
 };
 
@@ -245,24 +307,26 @@ struct Look {
     int nmask;        // -1 while a next tile exists, else 0
 };
 
-template <int KIND>
-__device__ __forceinline__ void look_set(const WideArgs &a, const TileIter &it, int i, int ntiles,
+template <int KIND, bool PLANES32 = false, class Iter>
+__device__ __forceinline__ void look_set(const WideArgs &a, const Iter &it, int i, int inext, int ntiles,
                                          Look &lk)
 {
-    constexpr int TILEB = KIND == WIDE_F32 ? Cfg32::TILEB : PipeCfg::TILEB;
-    const size_t xpitch = (size_t)a.nk * (KIND == WIDE_F16X2 ? 2 : 1) * TILEB;
+    constexpr int TILEB = KIND == WIDE_F32 && !PLANES32 ? Cfg32::TILEB : PipeCfg::TILEB;
+    const size_t xpitch = (size_t)a.nk * (KIND == WIDE_F16X2 || PLANES32 ? 2 : 1) * TILEB;
+    const int wlast = PLANES32 ? a.nk - 1 : w_tile<KIND>(a, a.nv - 1);
+    const int xlast = PLANES32 ? a.nk - 1 : x_tile<KIND>(a, a.nv - 1);
     int r, col;
     it.tile(i, &r, &col);
     lk.wcur = a.Wp + (size_t)r * a.pr;
     lk.xcur = a.Xw + (size_t)col * xpitch;
-    if (i + 1 < ntiles) {
-        it.tile(i + 1, &r, &col);
+    if (inext < ntiles) {
+        it.tile(inext, &r, &col);
         lk.wnext = a.Wp + (size_t)r * a.pr;
         lk.xnext = a.Xw + (size_t)col * xpitch;
         lk.nmask = -1;
     } else {
-        lk.wnext = lk.wcur + (size_t)w_tile<KIND>(a, a.nv - 1) * TILEB;
-        lk.xnext = lk.xcur + (size_t)x_tile<KIND>(a, a.nv - 1) * TILEB;
+        lk.wnext = lk.wcur + (size_t)wlast * TILEB;
+        lk.xnext = lk.xcur + (size_t)xlast * TILEB;
         lk.nmask = 0;
     }
 }
@@ -415,6 +479,23 @@ __device__ __forceinline__ void pipe_step(const WideArgs &a, char *smem, const L
     lgkm_wait_all(fa[1 - P], fb[1 - P]);
 }
 
+// All accumulators times c, between multiplies of mfma_step.
+__device__ __forceinline__ void acc_scale(floatx4 (&acc)[8][8], float c)
+{
+    mfma_acc_sync(acc);
+#pragma unroll
+    for (int rb = 0; rb < 8; ++rb) {
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[rb][cb][v] *= c;
+            asm volatile("" : "+a"(acc[rb][cb]));
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    mfma_acc_sync(acc);
+}
+
 // The K steps of one tile whose first step (global step qbase) uses register
 // set P0: step kt uses set (P0 + kt) & 1, i.e. the parity of its global step,
 // so an odd step count per tile just alternates P0 from tile to tile.
@@ -425,6 +506,18 @@ __device__ __forceinline__ void pipe_tile(const WideArgs &a, char *smem, const L
 {
     pipe_step<KIND, P0, true>(a, smem, lk, 0, qbase, L, acc, fa, fb);
     int kt = 1;
+    if constexpr (KIND == WIDE_F16X2) {
+        // the passes with a lo part (an even count of steps), then their sum onto the
+        // scale of the third
+        pipe_step<KIND, 1 - P0>(a, smem, lk, 1, qbase + 1, L, acc, fa, fb);
+        for (kt = 2; kt < 2 * a.nk; kt += 2) {
+            pipe_step<KIND, P0>(a, smem, lk, kt, qbase + kt, L, acc, fa, fb);
+            pipe_step<KIND, 1 - P0>(a, smem, lk, kt + 1, qbase + kt + 1, L, acc, fa, fb);
+        }
+        acc_scale(acc, SPLIT_LO_DOWN);
+        pipe_step<KIND, P0>(a, smem, lk, kt, qbase + kt, L, acc, fa, fb);
+        ++kt;
+    }
     for (; kt + 1 < a.nv; kt += 2) {
         pipe_step<KIND, 1 - P0>(a, smem, lk, kt, qbase + kt, L, acc, fa, fb);
         pipe_step<KIND, P0>(a, smem, lk, kt + 1, qbase + kt + 1, L, acc, fa, fb);
@@ -536,10 +629,6 @@ __device__ __forceinline__ float wave_sum_lane0(float v)
     return (v + r1) + (r2 + r3);
 }
 
-constexpr int LABEL_SKIP = -2;     // the sample's loss is not taken here (k_wide_finalize adds it)
-
-__device__ __forceinline__ int sample_exp(int xe) { return xe >= XE_BAD / 2 ? xe - XE_BAD : xe; }
-
 // What the lane that scores sample s of spark row r in the epilogue needs, fetched
 // early (its load latency would otherwise sit in the epilogue): the label, and with
 // two FP16 parts the exponent e of the pre-activations' scale 2^e.
@@ -555,15 +644,14 @@ __device__ __forceinline__ LaneSample lane_sample(const WideArgs &a, int r, int 
     ls.label = (a.loss == 1 && s < a.S) ? a.lab[s] : 0;
     ls.e = 0;
     if constexpr (KIND == WIDE_F16X2) {
-        const int32_t *t = wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp);
-        const int xe = a.Xe[s];
-        ls.e = t[0] + sample_exp(xe);
-        if (t[1] || xe >= XE_BAD / 2) ls.label = LABEL_SKIP;
+        ls.e = wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp)[0] + a.Xe[s];
     }
     return ls;
 }
 
-template <int KIND, int ACT, bool BF = KIND == WIDE_BF16>
+// PLANES: FP32 values of raw operands, where infinities may meet the zero weights of units
+// past the hidden width.
+template <int KIND, int ACT, bool PLANES = false, bool BF = KIND == WIDE_BF16>
 __device__ void wide_epilogue(const WideArgs &a, char *smem, int r, int col, int wave, int lane,
                               floatx4 (&acc)[8][8], const W2Frag<BF> &w2, float *red,
                               const LaneSample &own)
@@ -600,7 +688,7 @@ __device__ void wide_epilogue(const WideArgs &a, char *smem, int r, int col, int
             const int re = wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp)[0];
 #pragma unroll
             for (int cb = 0; cb < 8; ++cb)
-                e[cb] = re + sample_exp(a.Xe[(size_t)col * WT_N + 128 * sh + 16 * cb + n]);
+                e[cb] = re + a.Xe[(size_t)col * WT_N + 128 * sh + 16 * cb + n];
         }
 #pragma unroll
         for (int cb = 0; cb < 8; ++cb) {
@@ -615,6 +703,10 @@ __device__ void wide_epilogue(const WideArgs &a, char *smem, int r, int col, int
                     for (int v = 0; v < 4; ++v) h[v] = __builtin_ldexpf(h[v], -e[cb]);
                 }
                 h = act4<ACT>(h);
+                if constexpr (PLANES) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) h[v] = 128 * nh + 16 * rb + 4 * g + v < a.hid ? h[v] : 0.0f;
+                }
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
                     floatx4 &t = zv[SPLIT ? v : 0];
@@ -667,7 +759,7 @@ __device__ void wide_epilogue(const WideArgs &a, char *smem, int r, int col, int
     const int sl = 64 * wave + lane;                // sample within the tile
     const int s = col * WT_N + sl;
     float ls = 0.0f;
-    if (s < a.S && own.label != LABEL_SKIP) {
+    if (s < a.S) {
         float zz[16];
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
@@ -708,11 +800,26 @@ struct Lane32 {
     int woff;            // byte offset of this wave's first 8-row block of a tile (uniform)
 };
 
+template <bool PL>
 __device__ __forceinline__ Lane32 lane32(int wave, int lane, int nh, int sh)
 {
     using C = Cfg32;
     static_assert(C::NCH == 8 && C::RPL == 8, "128-byte rows, 8 rows per wave load");
     const int n = lane & 15, g = lane >> 4;
+    if constexpr (PL) {
+        // columns 16 kk + 4 g .. + 3 of a 64-byte row: half a 16-byte chunk of each plane
+        const PipeLane p = pipe_lane(wave, lane, nh, sh);
+        Lane32 L;
+        L.goff = p.goff;
+        L.woff = p.woff;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk) {
+            const uint32_t at = (uint32_t)(n * PipeCfg::ROWB + (((2 * kk + (g >> 1)) ^ ((n >> 1) & 3)) << 4) + 8 * (g & 1));
+            L.aoff[kk] = (uint32_t)(128 * nh * PipeCfg::ROWB) + at;
+            L.boff[kk] = (uint32_t)(C::TILEB + 128 * sh * PipeCfg::ROWB) + at;
+        }
+        return L;
+    }
     const int lr = lane / C::NCH, pc = lane % C::NCH;
     Lane32 L;
     // a wave load covers rows r0..r0+7 with r0 a multiple of 8, so the swizzle
@@ -732,28 +839,93 @@ __device__ __forceinline__ Lane32 lane32(int wave, int lane, int nh, int sh)
 // blocks of the W tile, 8-15 those of the X tile.  Blocks 0-3 and 4-7 of an
 // operand each share one address and one LDS base, the block being the
 // instruction's immediate offset (which must stay below 4 KiB).
-template <int T>
-__device__ __forceinline__ void issue32(const char *wsrc, const char *xsrc, char *stage, const Lane32 &L)
+// Two planes (`plane` bytes apart): four blocks of each plane of W, then of X.
+template <bool PL, int T>
+__device__ __forceinline__ void issue32(const char *wsrc, const char *xsrc, size_t plane, char *stage,
+                                        const Lane32 &L)
 {
     using C = Cfg32;
     constexpr int half = T >> 3, blk = T & 7;
-    constexpr int hi = (blk >> 2) * 4096, lo = (blk & 3) * 1024;
-    const char *src = (half ? xsrc : wsrc) + L.woff + hi + L.goff;
+    constexpr int hi = (blk >> 2) * (PL ? PipeCfg::TILEB : 4096), lo = (blk & 3) * 1024;
+    const char *src = (half ? xsrc : wsrc) + L.woff + (PL ? (blk >> 2) * plane : hi) + L.goff;
     char *dst = stage + half * C::TILEB + L.woff + hi;
     __builtin_amdgcn_global_load_lds(src, (lds_void_t *)dst, 16, lo, 0);
 }
 
-template <int OFF>
+// All 16 wave loads of a K step.
+template <bool PL, int T = 0>
+__device__ __forceinline__ void issue32_all(const char *wsrc, const char *xsrc, size_t plane, char *stage,
+                                            const Lane32 &L)
+{
+    issue32<PL, T>(wsrc, xsrc, plane, stage, L);
+    if constexpr (T + 1 < Cfg32::LOADS) issue32_all<PL, T + 1>(wsrc, xsrc, plane, stage, L);
+}
+
+// The fragment of row block RB at a lane's address: four values; of two planes, two words
+// of one and two of the other.
+template <bool PL, int RB>
 __device__ __forceinline__ floatx4 lds_read4_at(uint32_t addr)
 {
     floatx4 v;
-    asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(OFF));
+    if constexpr (PL) {
+        constexpr int at = RB * 16 * PipeCfg::ROWB / 512;   // (units of 64 8-byte words)
+        asm volatile("ds_read2st64_b64 %0, %1 offset0:%2 offset1:%3"
+                     : "=v"(v) : "v"(addr), "i"(at), "i"(at + PipeCfg::TILEB / 512));
+    } else {
+        asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(v) : "v"(addr), "i"(RB * 16 * Cfg32::ROWB));
+    }
     return v;
 }
+
+// How a tile's operands are staged: FP32 values, or two planes that are the halves of such
+// values (raw) or parts, of W and of X.
+enum Form32 : int { PLAIN = 0, RAW_W = 1, RAW_X = 2, RAW_WX = 3 };
+
+// Powers of two that parts are brought to their values by.
+struct Scale32 {
+    float w, x[8];     // of the row; of this lane's sample in each column block
+};
+
+__device__ __forceinline__ Scale32 scale32(const WideArgs &a, int r, int col, int n, int sh)
+{
+    Scale32 s;
+    s.w = __builtin_ldexpf(1.0f, -wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp)[0]);
+#pragma unroll
+    for (int cb = 0; cb < 8; ++cb) s.x[cb] = __builtin_ldexpf(1.0f, -a.Xe[col * WT_N + 128 * sh + 16 * cb + n]);
+    return s;
+}
+
+// Value E of a fragment from its words (HI: the first two registers are the hi plane's).
+template <bool HI, bool RAW>
+__device__ __forceinline__ float join_word(const floatx4 &f, int E, float c)
+{
+    typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
+    const float fh = HI ? f[E >> 1] : f[2 + (E >> 1)], fl = HI ? f[2 + (E >> 1)] : f[E >> 1];
+    const uint32_t h = __float_as_uint(fh), l = __float_as_uint(fl);
+    if constexpr (RAW) return __uint_as_float(E & 1 ? (h & 0xffff0000u) | l >> 16 : h << 16 | (l & 0xffffu));
+    return __builtin_fmaf((float)__builtin_bit_cast(halfx2, l)[E & 1], c * SPLIT_LO_DOWN,
+                          (float)__builtin_bit_cast(halfx2, h)[E & 1] * c);
+}
+
+template <bool HI, bool RAW>
+__device__ __forceinline__ floatx4 join_words(const floatx4 &f, float c)
+{
+    return floatx4{join_word<HI, RAW>(f, 0, c), join_word<HI, RAW>(f, 1, c), join_word<HI, RAW>(f, 2, c),
+                   join_word<HI, RAW>(f, 3, c)};
+}
+
+// An operand that vector instructions wrote, before multiplies written as inline assembly
+// (which need two wait states behind them) read it.
+__device__ __forceinline__ void operand_wait(floatx4 &a) { asm volatile("s_nop 1" : "+v"(a)); }
 
 // This wave's LDS reads have completed; the fragments passed through are tied
 // to the wait so that nothing uses them earlier.
 __device__ __forceinline__ void lgkm_wait1(floatx4 &a) { asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a)); }
+
+__device__ __forceinline__ void lgkm_wait3(floatx4 &a, floatx4 &b, floatx4 &c)
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" : "+v"(a), "+v"(b), "+v"(c));
+}
 
 __device__ __forceinline__ void lgkm_wait9(floatx4 &a, floatx4 (&b)[8])
 {
@@ -762,11 +934,11 @@ __device__ __forceinline__ void lgkm_wait9(floatx4 &a, floatx4 (&b)[8])
                    "+v"(b[6]), "+v"(b[7]));
 }
 
-template <int CB>
+template <bool PL, int CB = 0>
 __device__ __forceinline__ void read_b32(uint32_t addr, floatx4 (&b)[8])
 {
-    b[CB] = lds_read4_at<CB * 16 * Cfg32::ROWB>(addr);
-    if constexpr (CB + 1 < 8) read_b32<CB + 1>(addr, b);
+    b[CB] = lds_read4_at<PL, CB>(addr);
+    if constexpr (CB + 1 < 8) read_b32<PL, CB + 1>(addr, b);
 }
 
 template <bool FIRST>
@@ -798,40 +970,81 @@ __device__ __forceinline__ void stage_barrier()
 // multiplies just issued read: the matrix core reads its A and B operands at
 // issue; only its accumulator input has a write-after-read hazard, and
 // accumulators live in AGPRs nothing else writes.)
-template <int KK, int RB, bool FIRST>
-__device__ __forceinline__ void rb32(uint32_t st, uint32_t stn, const char *wsrc, const char *xsrc,
-                                     char *fill, const Lane32 &L, floatx4 (&acc)[8][8],
-                                     floatx4 (&fa)[2], floatx4 (&b0)[8], floatx4 (&b1)[8])
+// Two planes: fragments are joined from their words as they arrive, in the shadow of the
+// multiplies, but for a step's first ones, whose scale is known in their own step only.
+template <int FORM, int KK, int RB, bool FIRST>
+__device__ __forceinline__ void rb32(uint32_t st, uint32_t stn, const char *wsrc, const char *xsrc, size_t plane,
+                                     char *fill, const Lane32 &L, const Scale32 &sc, floatx4 (&acc)[8][8],
+                                     floatx4 (&fa)[2], floatx4 &aj, floatx4 (&b0)[8], floatx4 (&b1)[8])
 {
-    using C = Cfg32;
+    constexpr bool PL = FORM != PLAIN, WRAW = FORM & RAW_W, XRAW = FORM & RAW_X;
     constexpr int RB1 = RB + 1 < 8 ? RB + 1 : 0;
     constexpr int J = 8 * KK + RB;              // A fragment J of the step lives in fa[J % 2]
-    if constexpr (J < 15)
-        fa[(J + 1) % 2] = lds_read4_at<RB1 * 16 * C::ROWB>(st + L.aoff[RB + 1 < 8 ? KK : 1]);
+    if constexpr (J < 15) fa[(J + 1) % 2] = lds_read4_at<PL, RB1>(st + L.aoff[RB + 1 < 8 ? KK : 1]);
     if constexpr (KK == 0 && RB >= 4) {
         constexpr int c0 = 2 * (RB - 4);
-        b1[c0] = lds_read4_at<c0 * 16 * C::ROWB>(st + L.boff[1]);
-        b1[c0 + 1] = lds_read4_at<(c0 + 1) * 16 * C::ROWB>(st + L.boff[1]);
+        b1[c0] = lds_read4_at<PL, c0>(st + L.boff[1]);
+        b1[c0 + 1] = lds_read4_at<PL, c0 + 1>(st + L.boff[1]);
     }
     if constexpr (KK == 0 && RB < 4) {
-        issue32<4 * RB>(wsrc, xsrc, fill, L);
-        issue32<4 * RB + 1>(wsrc, xsrc, fill, L);
-        issue32<4 * RB + 2>(wsrc, xsrc, fill, L);
-        issue32<4 * RB + 3>(wsrc, xsrc, fill, L);
+        issue32<PL, 4 * RB>(wsrc, xsrc, plane, fill, L);
+        issue32<PL, 4 * RB + 1>(wsrc, xsrc, plane, fill, L);
+        issue32<PL, 4 * RB + 2>(wsrc, xsrc, plane, fill, L);
+        issue32<PL, 4 * RB + 3>(wsrc, xsrc, plane, fill, L);
     }
     if constexpr (J == 15) {
-        read_b32<0>(stn + L.boff[0], b0);
-        fa[0] = lds_read4_at<0>(stn + L.aoff[0]);
+        read_b32<PL>(stn + L.boff[0], b0);
+        fa[0] = lds_read4_at<PL, 0>(stn + L.aoff[0]);
     }
     __builtin_amdgcn_sched_barrier(0);
-    const floatx4 a = fa[J % 2];
     floatx4 (&bk)[8] = KK == 0 ? b0 : b1;
+    if constexpr (PL) {
+        constexpr bool B1 = KK == 0 && RB >= 4;
+        constexpr int c0 = B1 ? 2 * (RB - 4) : 0;
+        if constexpr (J == 0) {
+            aj = join_words<false, WRAW>(fa[0], sc.w);
+            operand_wait(aj);
+        }
+        const floatx4 a = aj;
 #pragma unroll
-    for (int cb = 0; cb < 8; ++cb) mfma32<FIRST && KK == 0>(acc[RB][cb], a[0], bk[cb][0]);
+        for (int cb = 0; cb < 8; ++cb) {
+            if constexpr (J == 0) {
+                b0[cb] = join_words<true, XRAW>(b0[cb], sc.x[cb]);
+                operand_wait(b0[cb]);
+            }
+            mfma32<FIRST && KK == 0>(acc[RB][cb], a[0], bk[cb][0]);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (J < 15) {
+            if constexpr (B1) lgkm_wait3(fa[(J + 1) % 2], b1[c0], b1[c0 + 1]);
+            else lgkm_wait1(fa[(J + 1) % 2]);
+        }
+        floatx4 n0 = zero4(), n1 = zero4();
 #pragma unroll
-    for (int v = 1; v < 4; ++v)
+        for (int v = 1; v < 4; ++v)
 #pragma unroll
-        for (int cb = 0; cb < 8; ++cb) mfma32<false>(acc[RB][cb], a[v], bk[cb][v]);
+            for (int cb = 0; cb < 8; ++cb) {
+                // (a value in the shadow of each multiply)
+                mfma32<false>(acc[RB][cb], a[v], bk[cb][v]);
+                const int i = 8 * (v - 1) + cb;
+                if (J < 15 && i < 4) aj[i] = join_word<false, WRAW>(fa[(J + 1) % 2], i, sc.w);
+                if (B1 && i >= 4 && i < 8) n0[i - 4] = join_word<true, XRAW>(b1[c0], i - 4, sc.x[c0]);
+                if (B1 && i >= 8 && i < 12) n1[i - 8] = join_word<true, XRAW>(b1[c0 + 1], i - 8, sc.x[c0 + 1]);
+                if (i < 12) __builtin_amdgcn_sched_barrier(0);
+            }
+        if constexpr (B1) {
+            b1[c0] = n0;
+            b1[c0 + 1] = n1;
+        }
+    } else {
+        const floatx4 a = fa[J % 2];
+#pragma unroll
+        for (int cb = 0; cb < 8; ++cb) mfma32<FIRST && KK == 0>(acc[RB][cb], a[0], bk[cb][0]);
+#pragma unroll
+        for (int v = 1; v < 4; ++v)
+#pragma unroll
+            for (int cb = 0; cb < 8; ++cb) mfma32<false>(acc[RB][cb], a[v], bk[cb][v]);
+    }
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (J == 7) {
         lgkm_wait9(fa[0], b1);
@@ -843,7 +1056,8 @@ __device__ __forceinline__ void rb32(uint32_t st, uint32_t stn, const char *wsrc
     } else {
         lgkm_wait1(fa[(J + 1) % 2]);
     }
-    if constexpr (RB + 1 < 8) rb32<KK, RB + 1, FIRST>(st, stn, wsrc, xsrc, fill, L, acc, fa, b0, b1);
+    if constexpr (RB + 1 < 8)
+        rb32<FORM, KK, RB + 1, FIRST>(st, stn, wsrc, xsrc, plane, fill, L, sc, acc, fa, aj, b0, b1);
 }
 
 // K step kt of a tile, global step q of the block (stage q & 1: a tile with an
@@ -851,84 +1065,94 @@ __device__ __forceinline__ void rb32(uint32_t st, uint32_t stn, const char *wsrc
 // stage is complete for every wavefront and its first fragments are in b0 and
 // fa[0]; on exit the same holds for the next step (the next tile's first step
 // after a tile's last).
-template <bool FIRST>
+template <int FORM, bool FIRST>
 __device__ __forceinline__ void step32(const WideArgs &a, char *smem, const Look &lk, int kt, int q,
-                                       const Lane32 &L, floatx4 (&acc)[8][8], floatx4 (&fa)[2],
-                                       floatx4 (&b0)[8], floatx4 (&b1)[8])
+                                       const Lane32 &L, const Scale32 &sc, floatx4 (&acc)[8][8],
+                                       floatx4 (&fa)[2], floatx4 (&b0)[8], floatx4 (&b1)[8])
 {
     using C = Cfg32;
+    constexpr int TILEB = FORM != PLAIN ? PipeCfg::TILEB : C::TILEB;
+    const size_t plane = (size_t)a.nk * PipeCfg::TILEB;
     const bool wrap = kt + 1 >= a.nk;
-    const char *wsrc = wrap ? lk.wnext : lk.wcur + (size_t)(kt + 1) * C::TILEB;
-    const char *xsrc = wrap ? lk.xnext : lk.xcur + (size_t)(kt + 1) * C::TILEB;
+    const char *wsrc = wrap ? lk.wnext : lk.wcur + (size_t)(kt + 1) * TILEB;
+    const char *xsrc = wrap ? lk.xnext : lk.xcur + (size_t)(kt + 1) * TILEB;
     char *fill = smem + ((q + 1) & 1) * C::STAGEB;
     const uint32_t st = (uint32_t)(uintptr_t)(lds_void_t *)(smem + (q & 1) * C::STAGEB);
     const uint32_t stn = (uint32_t)(uintptr_t)(lds_void_t *)fill;
-    rb32<0, 0, FIRST>(st, stn, wsrc, xsrc, fill, L, acc, fa, b0, b1);
-    rb32<1, 0, FIRST>(st, stn, wsrc, xsrc, fill, L, acc, fa, b0, b1);
+    floatx4 aj = zero4();   // PL: the A fragment being multiplied
+    rb32<FORM, 0, 0, FIRST>(st, stn, wsrc, xsrc, plane, fill, L, sc, acc, fa, aj, b0, b1);
+    rb32<FORM, 1, 0, FIRST>(st, stn, wsrc, xsrc, plane, fill, L, sc, acc, fa, aj, b0, b1);
 }
 
-template <int ACT>
+// The K steps of a tile, and the epilogue's global inputs, fetched meanwhile (after its
+// first step: the next step's wait covers them).
+template <int FORM>
+__device__ __forceinline__ void tile32(const WideArgs &a, char *smem, const Look &lk, int r, int col, int qbase,
+                                       const Lane32 &L, const Scale32 &sc, int wave, int lane,
+                                       floatx4 (&acc)[8][8], floatx4 (&fa)[2], floatx4 (&b0)[8],
+                                       floatx4 (&b1)[8], W2Frag<false> &w2, LaneSample &own)
+{
+    step32<FORM, true>(a, smem, lk, 0, qbase, L, sc, acc, fa, b0, b1);
+    w2_load<WIDE_F32>(a, r, wave & 1, lane & 15, lane >> 4, w2);
+    own = lane_sample<WIDE_F32>(a, r, col, wave, lane);
+    for (int kt = 1; kt < a.nk; ++kt) step32<FORM, false>(a, smem, lk, kt, qbase + kt, L, sc, acc, fa, b0, b1);
+    mfma_acc_sync(acc);
+}
+
+// PL: the tiles of two planes that k_fit_wide leaves out, their values joined from the
+// planes on the true scale.
+template <bool PL, int ACT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void k_fit_wide32(WideArgs a)
 {
-    using C = Cfg32;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     __shared__ float red[4];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform
-    const int n = lane & 15, g = lane >> 4, nh = wave & 1, sh = wave >> 1;
-    TileIter it;
-    it.xcd = blockIdx.x % 8;
-    it.j = blockIdx.x / 8;
-    it.bx = (gridDim.x - it.xcd + 7) / 8;
-    it.gs = a.gs;
-    it.ntn = a.ntn;
-    it.rows = a.rows;
-    it.setup();
+    const int n = lane & 15, nh = wave & 1, sh = wave >> 1;
+    const std::conditional_t<PL, SpreadIter, TileIter> it(a);
     const int ntiles = it.count();
-    if (ntiles == 0) return;
-    const Lane32 L = lane32(wave, lane, nh, sh);
+    TileScan<PL, true> scan;
+    int i = scan.next(a, it, ntiles);
+    if (i >= ntiles) return;
+    int inext = scan.next(a, it, ntiles);
+    const Lane32 L = lane32<PL>(wave, lane, nh, sh);
     Look lk;
-    look_set<WIDE_F32>(a, it, 0, ntiles, lk);
-    // prologue: step 0 of tile 0 into stage 0
-    issue32<0>(lk.wcur, lk.xcur, smem, L);
-    issue32<1>(lk.wcur, lk.xcur, smem, L);
-    issue32<2>(lk.wcur, lk.xcur, smem, L);
-    issue32<3>(lk.wcur, lk.xcur, smem, L);
-    issue32<4>(lk.wcur, lk.xcur, smem, L);
-    issue32<5>(lk.wcur, lk.xcur, smem, L);
-    issue32<6>(lk.wcur, lk.xcur, smem, L);
-    issue32<7>(lk.wcur, lk.xcur, smem, L);
-    issue32<8>(lk.wcur, lk.xcur, smem, L);
-    issue32<9>(lk.wcur, lk.xcur, smem, L);
-    issue32<10>(lk.wcur, lk.xcur, smem, L);
-    issue32<11>(lk.wcur, lk.xcur, smem, L);
-    issue32<12>(lk.wcur, lk.xcur, smem, L);
-    issue32<13>(lk.wcur, lk.xcur, smem, L);
-    issue32<14>(lk.wcur, lk.xcur, smem, L);
-    issue32<15>(lk.wcur, lk.xcur, smem, L);
+    look_set<WIDE_F32, PL>(a, it, i, inext, ntiles, lk);
+    // prologue: step 0 of the first tile into stage 0
+    issue32_all<PL>(lk.wcur, lk.xcur, (size_t)a.nk * PipeCfg::TILEB, smem, L);
     stage_barrier();
     floatx4 fa[2], b0[8], b1[8];
     {
         const uint32_t st0 = (uint32_t)(uintptr_t)(lds_void_t *)smem;
-        read_b32<0>(st0 + L.boff[0], b0);
-        fa[0] = lds_read4_at<0>(st0 + L.aoff[0]);
+        read_b32<PL>(st0 + L.boff[0], b0);
+        fa[0] = lds_read4_at<PL, 0>(st0 + L.aoff[0]);
         lgkm_wait9(fa[0], b0);
     }
-    for (int i = 0; i < ntiles; ++i) {
+    for (int qbase = 0;; qbase += a.nk) {
         int r, col;
         it.tile(i, &r, &col);
-        if (i > 0) look_set<WIDE_F32>(a, it, i, ntiles, lk);
+        if (qbase > 0) look_set<WIDE_F32, PL>(a, it, i, inext, ntiles, lk);
         floatx4 acc[8][8];
-        const int qbase = i * a.nk;
-        step32<true>(a, smem, lk, 0, qbase, L, acc, fa, b0, b1);
-        // the epilogue's global inputs, fetched while the tile's K loop runs
-        // (after its first step: the next step's wait covers them)
         W2Frag<false> w2;
-        w2_load<WIDE_F32>(a, r, nh, n, g, w2);
-        const LaneSample own = lane_sample<WIDE_F32>(a, r, col, wave, lane);
-        for (int kt = 1; kt < a.nk; ++kt) step32<false>(a, smem, lk, kt, qbase + kt, L, acc, fa, b0, b1);
-        mfma_acc_sync(acc);
-        wide_epilogue<WIDE_F32, ACT>(a, smem, r, col, wave, lane, acc, w2, red, own);
+        LaneSample own;
+        auto run = [&](auto form, const Scale32 &sc) {
+            tile32<decltype(form)::value>(a, smem, lk, r, col, qbase, L, sc, wave, lane, acc, fa, b0, b1, w2, own);
+        };
+        if constexpr (PL) {
+            const Scale32 sc = scale32(a, r, col, n, sh);
+            if (wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp)[1] == 0)
+                run(std::integral_constant<int, RAW_X>{}, sc);
+            else if (a.Xe[a.S_pad + col] == 0)
+                run(std::integral_constant<int, RAW_W>{}, sc);
+            else
+                run(std::integral_constant<int, RAW_WX>{}, sc);
+        } else {
+            run(std::integral_constant<int, PLAIN>{}, Scale32{});
+        }
+        wide_epilogue<WIDE_F32, ACT, PL>(a, smem, r, col, wave, lane, acc, w2, red, own);
+        if (inext >= ntiles) break;
+        i = inext;
+        inext = scan.next(a, it, ntiles);
     }
     __builtin_amdgcn_s_waitcnt(0);
 }
@@ -944,22 +1168,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform
     const int n = lane & 15, g = lane >> 4, nh = wave & 1, sh = wave >> 1;
-    TileIter it;
-    it.xcd = blockIdx.x % 8;
-    it.j = blockIdx.x / 8;
-    it.bx = (gridDim.x - it.xcd + 7) / 8;
-    it.gs = a.gs;
-    it.ntn = a.ntn;
-    it.rows = a.rows;
-    it.setup();
+    const TileIter it(a);
     const int ntiles = it.count();
-    if (ntiles == 0) return;
+    TileScan<KIND == WIDE_F16X2, false> scan;
+    int t = scan.next(a, it, ntiles);
+    if (t >= ntiles) return;
+    int tnext = scan.next(a, it, ntiles);
     // K steps per tile: at least STAGES, so the look-ahead of a step lies in its
     // own tile or the next one
     const PipeLane L = pipe_lane(wave, lane, nh, sh);
     Look lk;
-    look_set<KIND>(a, it, 0, ntiles, lk);
-    // prologue: steps 0..3 of tile 0 into stages 0..3, then the fragments of step 0
+    look_set<KIND>(a, it, t, tnext, ntiles, lk);
+    // prologue: steps 0..3 of the first tile into stages 0..3, then the fragments of step 0
 #pragma unroll
     for (int s = 0; s < PipeCfg::STAGES; ++s)
         pipe_issue_all(lk.wcur + (size_t)w_tile<KIND>(a, s) * C::TILEB,
@@ -973,10 +1193,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     }
     bf16x8 fa[2][8], fb[2][8];
     pipe_first<0>(smem, 0, L, fa, fb);
-    for (int i = 0; i < ntiles; ++i) {
+    for (int qbase = 0;; qbase += a.nv) {
         int r, col;
-        it.tile(i, &r, &col);
-        if (i > 0) look_set<KIND>(a, it, i, ntiles, lk);
+        it.tile(t, &r, &col);
+        if (qbase > 0) look_set<KIND>(a, it, t, tnext, ntiles, lk);
         floatx4 acc[8][8];
         // the epilogue's global inputs are fetched at the start of the tile;
         // then every load in flight (the tile's first look-ahead steps
@@ -992,7 +1212,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         if constexpr (EARLY) w2_load<KIND>(a, r, nh, n, g, w2);
         const LaneSample own = lane_sample<KIND>(a, r, col, wave, lane);
         __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));   // vmcnt(0)
-        const int qbase = i * a.nv;
         if (qbase & 1) {
             if constexpr (!EARLY) pipe_first<1>(smem, qbase, L, fa, fb);
             pipe_tile<KIND, 1>(a, smem, lk, qbase, L, acc, fa, fb);
@@ -1003,75 +1222,23 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         mfma_acc_sync(acc);
         if constexpr (!EARLY) w2_load<KIND>(a, r, nh, n, g, w2);
         wide_epilogue<KIND, ACT>(a, smem, r, col, wave, lane, acc, w2, red, own);
+        if (tnext >= ntiles) break;
+        t = tnext;
+        tnext = scan.next(a, it, ntiles);
     }
     __builtin_amdgcn_s_waitcnt(0);
 }
 
-// Loss of sample s of spark row r, column by column from the FP16 parts in FP32: for
-// samples and rows with an infinity, which the products of its parts (the lo part is
-// zero) would turn into a NaN.  Serial and slow; nothing else takes it.
-template <int ACT>
-__device__ float slow_loss(const WideArgs &a, int r, int s)
-{
-    const char *row = a.Wp + (size_t)r * a.pr;
-    const size_t plane = (size_t)WT_M * a.Kp;          // elements of a plane (of W, and of a sample tile)
-    const _Float16 *wlo = reinterpret_cast<const _Float16 *>(row), *whi = wlo + plane;
-    const _Float16 *xhi = reinterpret_cast<const _Float16 *>(a.Xw) + (size_t)(s / WT_N) * 2 * plane +
-                          (size_t)(s % WT_N) * WT_K;
-    const _Float16 *xlo = xhi + plane;
-    const float *w2 = reinterpret_cast<const float *>(row + plane * 4);
-    const int e = wide_row_exp(row, a.Kp)[0] + sample_exp(a.Xe[s]);
-    float zz[16];
-#pragma unroll
-    for (int j = 0; j < 16; ++j) zz[j] = w2[16 * WT_M + j];
-    for (int o = 0; o < a.hid; ++o) {
-        float h = 0.0f;
-        for (int k = 0; k < a.Kp; ++k) {
-            const size_t ks = (size_t)(k / WT_K) * WT_M * WT_K + k % WT_K, wk = ks + (size_t)o * WT_K;
-            h = __builtin_fmaf((float)whi[wk] + (float)wlo[wk], (float)xhi[ks] + (float)xlo[ks], h);
-        }
-        h = act_c<ACT>(ldexpf(h, -e));
-#pragma unroll
-        for (int j = 0; j < 16; ++j) zz[j] = __builtin_fmaf(w2[j * WT_M + o], h, zz[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < 16; ++j)
-        if (a.loss == 1 && j >= a.fo1) zz[j] = -__builtin_huge_valf();
-    return sample_loss<false>(a, s, a.loss == 1 ? a.lab[s] : 0, zz);
-}
-
 // Sum of a row's partials in order, scaled to the mean, NaN -> +inf, scattered: one
-// thread per row; with two FP16 parts one block per row, which first adds the losses
-// of the samples that k_fit_wide left out, and the sum is taken in binary64 (the
-// rounding of this sum was most of the error of an FP32 fitness: 9e-8 of 8,192
-// samples' mean).
-template <int KIND, int ACT>
-__global__ __launch_bounds__(256) void k_wide_finalize(WideArgs a, float inv_norm, OutMap map,
-                                                       float *__restrict__ out)
+// thread per row.  Two planes: the sum is taken in binary64 (the rounding of this sum was
+// most of the error of an FP32 fitness: 9e-8 of 8,192 samples' mean).
+template <typename Sum>
+__global__ __launch_bounds__(64) void k_wide_finalize(WideArgs a, float inv_norm, OutMap map,
+                                                      float *__restrict__ out)
 {
-    int r;
-    using Sum = std::conditional_t<KIND == WIDE_F16X2, double, float>;
+    const int r = blockIdx.x * 64 + threadIdx.x;
+    if (r >= a.rows) return;
     Sum t = 0;
-    if constexpr (KIND != WIDE_F16X2) {
-        r = blockIdx.x * 256 + threadIdx.x;
-        if (r >= a.rows) return;
-    } else {
-        r = blockIdx.x;
-        const bool row_inf = wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp)[1] != 0;
-        if (row_inf || a.Xe[a.S_pad]) {
-            __shared__ float red[256];
-            for (int s0 = 0; s0 < a.S; s0 += 256) {
-                const int s = s0 + threadIdx.x;
-                red[threadIdx.x] = s < a.S && (row_inf || a.Xe[s] >= XE_BAD / 2) ? slow_loss<ACT>(a, r, s)
-                                                                          : 0.0f;
-                __syncthreads();
-                if (threadIdx.x == 0)
-                    for (int i = 0; i < 256; ++i) t += red[i];
-                __syncthreads();
-            }
-        }
-        if (threadIdx.x != 0) return;
-    }
     for (int c = 0; c < a.ntn; ++c) t += a.partial[(size_t)r * a.ntn + c];
     out[map.index(r)] = canon_fitness((float)(t * (Sum)inv_norm));
 }

@@ -32,7 +32,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b)
 
 template <int KIND>
 __device__ __forceinline__ void pack_chunk(const float *__restrict__ w, char *__restrict__ wp,
-                                           int chunk, int c1, int c2, const WidePack &p, int wexp)
+                                           int chunk, int c1, int c2, const WidePack &p, float c, bool raw)
 {
     constexpr bool BF = KIND == WIDE_BF16;
     if (chunk < c1) {
@@ -67,15 +67,15 @@ __device__ __forceinline__ void pack_chunk(const float *__restrict__ w, char *__
                 make_uint4(pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3]), pack_bf16(v[4], v[5]),
                            pack_bf16(v[6], v[7]));
         } else if constexpr (KIND == WIDE_F16X2) {
-            halfx8 hi, lo;
+            uint32_t h[4], l[4];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-                const SplitF16 s = split_f16(v[e], wexp);
-                hi[e] = s.hi;
-                lo[e] = s.lo;
+            for (int e = 0; e < 8; e += 2) {
+                const Words a = wide_words(v[e], c, raw), b = wide_words(v[e + 1], c, raw);
+                h[e / 2] = a.hi | (uint32_t)b.hi << 16;
+                l[e / 2] = a.lo | (uint32_t)b.lo << 16;
             }
-            reinterpret_cast<halfx8 *>(wp)[chunk] = lo;
-            reinterpret_cast<halfx8 *>(wp)[c1 + chunk] = hi;
+            reinterpret_cast<uint4 *>(wp)[chunk] = make_uint4(l[0], l[1], l[2], l[3]);
+            reinterpret_cast<uint4 *>(wp)[c1 + chunk] = make_uint4(h[0], h[1], h[2], h[3]);
         } else {
             reinterpret_cast<float4 *>(wp)[2 * chunk] = make_float4(v[0], v[1], v[2], v[3]);
             reinterpret_cast<float4 *>(wp)[2 * chunk + 1] = make_float4(v[4], v[5], v[6], v[7]);
@@ -112,11 +112,10 @@ __device__ __forceinline__ void pack_chunk(const float *__restrict__ w, char *__
 }
 
 // A block packs PACK_RPB rows x (PACK_CPT * TPB) chunks: fat blocks, so the
-// dispatcher is not what bounds the pass.  boxed: FP16 parts take the box's
-// exponent (and store it), otherwise the one k_wide_row_exp stored.
+// dispatcher is not what bounds the pass.  Two planes: in the form k_wide_row_exp stored.
 template <int KIND>
 __global__ __launch_bounds__(TPB) void k_pack_wide_rows(const float *__restrict__ W, size_t ld,
-                                                        int rows, WidePack p, int boxed)
+                                                        int rows, WidePack p)
 {
     const int c1 = WT_M * p.Kp / 8;                  // chunks of W1aug
     const int c2 = 16 * WT_M / (KIND == WIDE_BF16 ? 8 : 4);         // chunks of W2
@@ -127,46 +126,44 @@ __global__ __launch_bounds__(TPB) void k_pack_wide_rows(const float *__restrict_
         for (int r = r0; r < rend; ++r) {
             const float *w = W + (size_t)r * ld;
             char *wp = p.Wp + (size_t)r * p.pr;
-            int wexp = p.wexp;
+            float c = 1.0f;
+            bool raw = false;
             if constexpr (KIND == WIDE_F16X2) {
-                int32_t *t = wide_row_exp(wp, p.Kp);
-                if (!boxed) {
-                    wexp = t[0];
-                } else if (cfirst == 0) {
-                    t[0] = wexp;
-                    t[1] = 0;
-                }
+                const int32_t *t = wide_row_exp(wp, p.Kp);
+                c = __builtin_ldexpf(1.0f, t[0]);
+                raw = t[1] != 0;
             }
 #pragma unroll
             for (int i = 0; i < PACK_CPT; ++i) {
                 const int chunk = cfirst + i * TPB;
-                if (chunk < nchunk) pack_chunk<KIND>(w, wp, chunk, c1, c2, p, wexp);
+                if (chunk < nchunk) pack_chunk<KIND>(w, wp, chunk, c1, c2, p, c, raw);
             }
         }
     }
 }
 
-__device__ __forceinline__ void max_inf(float v, float &m, int &inf)
-{
-    const float a = fabsf(v);
-    if (a <= 3.4028234e38f) m = fmaxf(m, a);   // finite (NaN takes no part)
-    else if (a == __builtin_huge_valf()) inf = 1;
-}
-
-// Exponent and infinity flag of rows that need not lie in the box: one block per
-// row, over W1 and b1 (adjacent, at the start of the spark, which is 16-byte
-// aligned).  A few rows leave most of the chip idle, so a block keeps as many loads
-// in flight as it can: 1024 threads x 4 x 16 bytes.
+// The form (row_form) of rows that the explosion did not pack: one block per row, over W1
+// and b1 (adjacent, at the start of the spark, which is 16-byte aligned), whose values the
+// parts hold or not, and W2, which must not be too large for their scale.  A few rows leave
+// most of the chip idle, so a block keeps as many loads in flight as it can: 1024 threads
+// x 4 x 16 bytes.
 constexpr int ROW_EXP_TPB = 1024;
 __global__ __launch_bounds__(ROW_EXP_TPB) void k_wide_row_exp(const float *__restrict__ W, size_t ld,
                                                               WidePack p)
 {
-    __shared__ float sm[ROW_EXP_TPB / 64];
-    __shared__ int si[ROW_EXP_TPB / 64];
+    __shared__ uint32_t most, least, w2most;
+    if (threadIdx.x == 0) {
+        most = w2most = 0;
+        least = 0xffffffffu;
+    }
+    __syncthreads();
     const float *w = W + (size_t)blockIdx.x * ld + p.woff1;
     const int n = p.hid * (p.in + 1), n4 = n / 4;
-    float m = 0.0f;
-    int inf = 0;
+    uint32_t m = 0, l = 0xffffffffu, m2 = 0;   // (magnitudes are ordered as their bits are)
+    auto take = [&](float v) {
+        m = max(m, __float_as_uint(fabsf(v)));
+        l = least_bits(l, v);
+    };
     for (int i0 = threadIdx.x; i0 < n4; i0 += 4 * ROW_EXP_TPB) {
         float4 v[4];
 #pragma unroll
@@ -176,30 +173,32 @@ __global__ __launch_bounds__(ROW_EXP_TPB) void k_wide_row_exp(const float *__res
         }
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            max_inf(v[u].x, m, inf);
-            max_inf(v[u].y, m, inf);
-            max_inf(v[u].z, m, inf);
-            max_inf(v[u].w, m, inf);
+            take(v[u].x);
+            take(v[u].y);
+            take(v[u].z);
+            take(v[u].w);
         }
     }
-    if ((int)threadIdx.x < n - 4 * n4) max_inf(w[4 * n4 + threadIdx.x], m, inf);
+    if ((int)threadIdx.x < n - 4 * n4) take(w[4 * n4 + threadIdx.x]);
+    for (int i = threadIdx.x; i < p.out * p.hid; i += ROW_EXP_TPB)
+        m2 = max(m2, __float_as_uint(fabsf(w[p.woff2 - p.woff1 + i])));
     for (int off = 32; off > 0; off >>= 1) {
-        m = fmaxf(m, __shfl_xor(m, off));
-        inf |= __shfl_xor(inf, off);
+        m = max(m, (uint32_t)__shfl_xor((int)m, off));
+        l = min(l, (uint32_t)__shfl_xor((int)l, off));
+        m2 = max(m2, (uint32_t)__shfl_xor((int)m2, off));
     }
     if ((threadIdx.x & 63) == 0) {
-        sm[threadIdx.x >> 6] = m;
-        si[threadIdx.x >> 6] = inf;
+        atomicMax(&most, m);
+        atomicMin(&least, l);
+        atomicMax(&w2most, m2);
     }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int i = 1; i < ROW_EXP_TPB / 64; ++i) {
-            m = fmaxf(m, sm[i]);
-            inf |= si[i];
-        }
+        RowForm form = row_form(most, least);
+        if (w2most >= __float_as_uint(WIDE_W2_MAX)) form = RowForm{0, 1};
         int32_t *t = wide_row_exp(p.Wp + (size_t)blockIdx.x * p.pr, p.Kp);
-        t[0] = split_exp(m);
-        t[1] = inf;
+        t[0] = form.e;
+        t[1] = form.raw;
     }
 }
 
@@ -222,21 +221,48 @@ __global__ __launch_bounds__(TPB) void k_pack_wide_x(const float *__restrict__ x
     else reinterpret_cast<float *>(Xw)[dst] = v;
 }
 
-// Samples in two FP16 parts (exponents Xe): a tile's hi plane, then its lo plane, each
-// K-blocked as above.
-__global__ __launch_bounds__(TPB) void k_pack_wide_x_f16x2(const float *__restrict__ x, int S, int S_pad,
-                                                           int in, int Kp, char *__restrict__ Xw,
-                                                           const int32_t *__restrict__ Xe)
+__global__ void k_clear_marks(int32_t *p, int n)
+{
+    if ((int)threadIdx.x < n) p[threadIdx.x] = 0;
+}
+
+// Exponent of every sample's inputs and of the constant 1 (Xe), a wavefront per sample; a
+// tile of 256 with a sample that the parts do not hold is marked (behind the exponents) and
+// packed raw.
+__global__ __launch_bounds__(TPB) void k_wide_sample_exp(const float *__restrict__ x, int S, int S_pad, int in,
+                                                         int32_t *__restrict__ Xe)
+{
+    const int s = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (s >= S_pad) return;
+    uint32_t m = __float_as_uint(1.0f), l = least_bits(0xffffffffu, 1.0f);
+    for (int k = lane; s < S && k < in; k += 64) {
+        const float v = x[(size_t)s * in + k];
+        m = max(m, __float_as_uint(fabsf(v)));
+        l = least_bits(l, v);
+    }
+    for (int off = 32; off > 0; off >>= 1) {
+        m = max(m, (uint32_t)__shfl_xor((int)m, off));
+        l = min(l, (uint32_t)__shfl_xor((int)l, off));
+    }
+    if (lane != 0) return;
+    const RowForm form = row_form(m, l);
+    Xe[s] = form.e;
+    if (form.raw) atomicOr(&Xe[S_pad + s / WT_N], 1);
+}
+
+// Samples in two planes: a tile's hi plane, then its lo plane, each K-blocked as above.
+__global__ __launch_bounds__(TPB) void k_pack_wide_x_planes(const float *__restrict__ x, int S, int S_pad,
+                                                            int in, int Kp, char *__restrict__ Xw,
+                                                            const int32_t *__restrict__ Xe)
 {
     const size_t tid = (size_t)blockIdx.x * TPB + threadIdx.x;
     if (tid >= (size_t)S_pad * Kp) return;
     const int s = (int)(tid / Kp), k = (int)(tid % Kp);
     float v = 0.0f;
     if (s < S) v = k < in ? x[(size_t)s * in + k] : (k == in ? 1.0f : 0.0f);
-    const int xe = Xe[s];
-    const SplitF16 p = split_f16(v, xe >= XE_BAD / 2 ? xe - XE_BAD : xe);
+    const Words p = wide_words(v, __builtin_ldexpf(1.0f, Xe[s]), Xe[S_pad + s / WT_N] != 0);
     const size_t plane = (size_t)WT_N * Kp;
-    _Float16 *hi = reinterpret_cast<_Float16 *>(Xw) + (size_t)(s / WT_N) * 2 * plane;
+    uint16_t *hi = reinterpret_cast<uint16_t *>(Xw) + (size_t)(s / WT_N) * 2 * plane;
     const size_t at = ((size_t)(k / WT_K) * WT_N + s % WT_N) * WT_K + k % WT_K;
     hi[at] = p.hi;
     hi[plane + at] = p.lo;
@@ -245,18 +271,19 @@ __global__ __launch_bounds__(TPB) void k_pack_wide_x_f16x2(const float *__restri
 // One instance per (precision, hidden activation): a run-time activation
 // switch over the 256 accumulators would push them out of registers.
 typedef void (*WideFn)(WideArgs);
-typedef void (*WideFin)(WideArgs, float, OutMap, float *);
 struct WideKernels {
     WideFn fit;
-    WideFin finalize;
+    WideFn raw;    // two planes: the tiles that fit leaves out
 };
-#define WIDE_KIND(K, FIT)                                                                       \
-    {{&FIT 0>, &k_wide_finalize<K, 0>}, {&FIT 1>, &k_wide_finalize<K, 1>},                      \
-     {&FIT 2>, &k_wide_finalize<K, 2>}, {&FIT 3>, &k_wide_finalize<K, 3>}}
+#define WIDE_KIND(FIT, RAW)                                                                         \
+    {{&FIT 0>, RAW 0>}, {&FIT 1>, RAW 1>}, {&FIT 2>, RAW 2>}, {&FIT 3>, RAW 3>}}
 #define COMMA ,
-const WideKernels kWide[3][4] = {WIDE_KIND(WIDE_F32, k_fit_wide32<),
-                                 WIDE_KIND(WIDE_BF16, k_fit_wide<WIDE_BF16 COMMA),
-                                 WIDE_KIND(WIDE_F16X2, k_fit_wide<WIDE_F16X2 COMMA)};
+template <int ACT>
+constexpr WideFn NO_RAW = nullptr;
+const WideKernels kWide[3][4] = {
+    WIDE_KIND(k_fit_wide32<false COMMA, NO_RAW<),
+    WIDE_KIND(k_fit_wide<WIDE_BF16 COMMA, NO_RAW<),
+    WIDE_KIND(k_fit_wide<WIDE_F16X2 COMMA, &k_fit_wide32<true COMMA)};
 #undef COMMA
 #undef WIDE_KIND
 
@@ -307,10 +334,11 @@ int wide_kp(const Net &net)
 }
 
 // FP32 takes two FP16 parts from 128 columns on, where their products are at least as
-// accurate as FP32 instructions (fit_wide.h has the figures)
+// accurate as FP32 instructions (fit_wide.h has the figures), in boxes whose weights they
+// take
 WideKind wide_kind(const Net &net)
 {
-    return net.bf16 ? WIDE_BF16 : wide_kp(net) >= 128 ? WIDE_F16X2 : WIDE_F32;
+    return net.bf16 ? WIDE_BF16 : wide_kp(net) >= 128 && net.box_exp >= WIDE_EMIN ? WIDE_F16X2 : WIDE_F32;
 }
 
 size_t wide_row_bytes(const Net &net)
@@ -320,12 +348,19 @@ size_t wide_row_bytes(const Net &net)
     return (b + 255) / 256 * 256;
 }
 
-int wide_lds_bytes(const Net &net) { return wide_kind(net) == WIDE_F32 ? Cfg32::LDS : PipeCfg::LDS; }
+int wide_lds_bytes(const Net &net) { return wide_kind(net) == WIDE_BF16 ? PipeCfg::LDS : Cfg32::LDS; }
 
 hipError_t wide_prepare(const Net &net)
 {
-    return hipFuncSetAttribute(reinterpret_cast<const void *>(wide_kernels(net).fit), hipFuncAttributeMaxDynamicSharedMemorySize,
-                               wide_lds_bytes(net));
+    static_assert(PipeCfg::LDS <= Cfg32::LDS, "wide_lds_bytes holds for both kernels of two planes");
+    for (const WideFn fn : {wide_kernels(net).fit, wide_kernels(net).raw}) {
+        if (!fn) continue;
+        const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(fn),
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 wide_lds_bytes(net));
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_pack_wide_x(const Net &net, const float *x, const DevState &d, hipStream_t st)
@@ -334,9 +369,10 @@ hipError_t launch_pack_wide_x(const Net &net, const float *x, const DevState &d,
     const size_t n = (size_t)net.S_pad * Kp;
     const dim3 grid((unsigned)((n + TPB - 1) / TPB));
     if (wide_kind(net) == WIDE_F16X2) {
-        const hipError_t e = launch_sample_exp(net, x, d.Xe, st);
-        if (e != hipSuccess) return e;
-        hipLaunchKernelGGL(k_pack_wide_x_f16x2, grid, dim3(TPB), 0, st, x, net.S, net.S_pad, net.fi[0], Kp,
+        hipLaunchKernelGGL(k_clear_marks, dim3(1), dim3(TPB), 0, st, d.Xe + net.S_pad, net.S_pad / WT_N);
+        hipLaunchKernelGGL(k_wide_sample_exp, dim3((unsigned)((net.S_pad + 3) / 4)), dim3(TPB), 0, st, x,
+                           net.S, net.S_pad, net.fi[0], d.Xe);
+        hipLaunchKernelGGL(k_pack_wide_x_planes, grid, dim3(TPB), 0, st, x, net.S, net.S_pad, net.fi[0], Kp,
                            d.Xw, d.Xe);
     } else {
         hipLaunchKernelGGL(net.bf16 ? &k_pack_wide_x<true> : &k_pack_wide_x<false>, grid, dim3(TPB), 0, st, x,
@@ -356,7 +392,7 @@ WidePack wide_pack_geometry(const Net &net, const DevState &d)
     p.out = net.fo[1];
     p.Kp = wide_kp(net);
     p.kind = wide_kind(net);
-    p.wexp = net.wexp;
+    p.wexp = net.box_exp;
     p.woff1 = net.woff[0];
     p.boff1 = net.boff[0];
     p.woff2 = net.woff[1];
@@ -365,7 +401,7 @@ WidePack wide_pack_geometry(const Net &net, const DevState &d)
 }
 
 hipError_t launch_fitness_wide(const Net &net, const DevState &d, const float *W, size_t ld,
-                               int rows, OutMap map, float *out, hipStream_t st, bool boxed,
+                               int rows, OutMap map, float *out, hipStream_t st,
                                hipEvent_t mid, hipEvent_t pre, int prepacked)
 {
     if (rows <= 0) return hipSuccess;
@@ -381,12 +417,12 @@ hipError_t launch_fitness_wide(const Net &net, const DevState &d, const float *W
         const float *Wsrc = W + (size_t)prepacked * ld;
         WidePack p = wide_pack_geometry(net, d);
         p.Wp += (size_t)prepacked * pr;
-        if (p.kind == WIDE_F16X2 && !boxed)
+        if (p.kind == WIDE_F16X2)
             hipLaunchKernelGGL(k_wide_row_exp, dim3(npack), dim3(ROW_EXP_TPB), 0, st, Wsrc, ld, p);
         auto *k = p.kind == WIDE_BF16    ? &k_pack_wide_rows<WIDE_BF16>
                   : p.kind == WIDE_F16X2 ? &k_pack_wide_rows<WIDE_F16X2>
                                          : &k_pack_wide_rows<WIDE_F32>;
-        hipLaunchKernelGGL(k, pg, dim3(TPB), 0, st, Wsrc, ld, npack, p, boxed ? 1 : 0);
+        hipLaunchKernelGGL(k, pg, dim3(TPB), 0, st, Wsrc, ld, npack, p);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -417,14 +453,16 @@ hipError_t launch_fitness_wide(const Net &net, const DevState &d, const float *W
     a.gs = wide_group(net, rows, a.ntn);
     const WideKernels &k = wide_kernels(net);
     hipLaunchKernelGGL(k.fit, dim3((unsigned)net.num_cu), dim3(TPB), (size_t)wide_lds_bytes(net), st, a);
+    if (k.raw)
+        hipLaunchKernelGGL(k.raw, dim3((unsigned)net.num_cu), dim3(TPB), (size_t)wide_lds_bytes(net), st, a);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (mid) {
         e = hipEventRecord(mid, st);
         if (e != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(k.finalize, dim3((unsigned)(f16x2 ? rows : (rows + 255) / 256)), dim3(256), 0, st,
-                       a, net.inv_norm, map, out);
+    hipLaunchKernelGGL(f16x2 ? &k_wide_finalize<double> : &k_wide_finalize<float>,
+                       dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, st, a, net.inv_norm, map, out);
     return hipGetLastError();
 }
 

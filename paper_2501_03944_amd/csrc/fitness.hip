@@ -87,32 +87,6 @@ __global__ __launch_bounds__(256) void k_pack(const float *__restrict__ x, const
     if (tid < (size_t)S_pad && Lp) Lp[tid] = (tid < (size_t)S && lab) ? lab[tid] : -1;
 }
 
-__global__ void k_clear_word(int32_t *p) { *p = 0; }
-
-// Exponent of every sample's inputs (and the constant 1 of a folded bias): one
-// wavefront per sample; a sample with a value that is not finite is marked and raises
-// the flag behind the exponents.
-__global__ __launch_bounds__(256) void k_sample_exp(const float *__restrict__ x, int S, int S_pad, int in,
-                                                    int32_t *__restrict__ Xe)
-{
-    const int s = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (s >= S_pad) return;
-    float m = 1.0f;
-    int bad = 0;
-    for (int k = lane; s < S && k < in; k += 64) {
-        const float v = fabsf(x[(size_t)s * in + k]);
-        if (v <= 3.4028234e38f) m = fmaxf(m, v);
-        else bad = 1;
-    }
-    for (int off = 32; off > 0; off >>= 1) {
-        m = fmaxf(m, __shfl_xor(m, off));
-        bad |= __shfl_xor(bad, off);
-    }
-    if (lane != 0) return;
-    Xe[s] = split_exp(m) + (bad ? XE_BAD : 0);
-    if (bad) atomicOr(&Xe[S_pad], 1);
-}
-
 // Exponent of every sample's inputs for the register chain, or XE_BAD where the parts do
 // not hold one of them: one wavefront per sample, the largest magnitude, then every value.
 __global__ __launch_bounds__(256) void k_split_exp(const float *__restrict__ x, int S, int S_pad, int in,
@@ -486,14 +460,6 @@ hipError_t launch_finalize_group(const GroupTable &t, int which, hipStream_t st)
 {
     hipLaunchKernelGGL(k_fit_finalize_group, dim3((unsigned)t.start[t.njobs]), dim3(256), 0, st, t,
                        which);
-    return hipGetLastError();
-}
-
-hipError_t launch_sample_exp(const Net &net, const float *x, int32_t *Xe, hipStream_t st)
-{
-    hipLaunchKernelGGL(k_clear_word, dim3(1), dim3(1), 0, st, Xe + net.S_pad);
-    hipLaunchKernelGGL(k_sample_exp, dim3((unsigned)((net.S_pad + 3) / 4)), dim3(256), 0, st, x, net.S,
-                       net.S_pad, net.fi[0], Xe);
     return hipGetLastError();
 }
 

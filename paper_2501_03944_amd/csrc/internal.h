@@ -41,7 +41,8 @@ struct DevState {
     char *Wpack;       // packed spark rows for the wide-first-layer kernel
     char *Xw;          // [S_pad][Kp] samples with a ones column (wide kernel)
     _Float16 *Xs;      // [2][S_pad][in_pad to 32] samples in two FP16 parts (register chain)
-    int32_t *Xe;       // [S_pad + 1] exponents of samples in two FP16 parts, any-marked flag
+    int32_t *Xe;       // [S_pad] exponents of samples in two FP16 parts, [S_pad / 256] sample
+                       // tiles of the wide kernel that hold their values in two halves
     float *lo, *hi;    // [B][Dp] population ranges (range mapping)
     float *Pnet;       // packed parameters of a fixed network (input problems)
     float *H0, *H1;    // [partial_rows][hnp] activations between layers (input problems)
@@ -80,8 +81,7 @@ struct Net {
     float inv_norm;                    // 1/(S*out) for MSE, 1/S for CE
     int lds_max;                       // LDS bytes a block may use (0: weights stay in global)
     int wide;                          // first layer streamed through LDS (two-layer nets)
-    int wexp;                          // FP16 parts: the exponent of weights in the search box (wide kernel)
-    int box_exp;                       // the same of the register chain
+    int box_exp;                       // FP16 parts: the exponent of weights in the search box
     int no_parts;                      // FP32 takes FP32 instructions only
     int num_cu;                        // compute units (persistent grid size)
 };
@@ -183,8 +183,8 @@ enum WideKind : int { WIDE_F32 = 0, WIDE_BF16 = 1, WIDE_F16X2 = 2 };
 // write each spark there as well (the fitness launch then skips packing them).
 // Row layout (fit_wide.h): W1 with b1 as column `in`, K-blocked as
 // [Kp/32][256][32] (two FP16 parts: lo plane, hi plane); W2 [16][256] (BF16: each 32-column
-// block in MFMA lane order); b2 [16] FP32; two FP16 parts: the row's exponent and infinity
-// flag.  Padding stays zero from initialisation.
+// block in MFMA lane order); b2 [16] FP32; two FP16 parts: the row's exponent and whether
+// it is raw.  Padding stays zero from initialisation.
 struct WidePack {
     char *Wp;                           // packed rows
     size_t pr;                          // row pitch (bytes)
@@ -199,19 +199,6 @@ __host__ __device__ __forceinline__ size_t wide_w1_offset(int o, int k)
     return ((size_t)(k >> 5) * 256 + o) * 32 + (k & 31);
 }
 
-// Exponent that brings values up to `bound` in magnitude below 2^15 (a bound of
-// 0 or less, or not finite, gives that of 1).  The same for every bound in
-// (2^-3, 2^3], so that ordinary rows get the same parts, bit for bit, whether the
-// bound is their own maximum or the search box's: at 12, an FP16 pair keeps its
-// full precision down to 2^-14.
-__host__ __device__ __forceinline__ int split_exp(float bound)
-{
-    if (!(bound > 0.0f) || bound > 3.4028234e38f || (bound > 0.125f && bound <= 8.0f)) return 12;
-    int e;
-    (void)frexpf(bound, &e);          // bound < 2^e
-    return 15 - e;
-}
-
 // Exponent that brings values of up to m in magnitude below 2^15 (15 for zero), within
 // +-PART_EMAX: beyond, they are not held.
 constexpr int PART_EMAX = 60;
@@ -224,7 +211,7 @@ __host__ __device__ __forceinline__ int part_exp(float m)
     return e > PART_EMAX ? PART_EMAX : e < -PART_EMAX ? -PART_EMAX : e;
 }
 
-// The scale of the lo parts against the hi parts (register chain).
+// The scale of the lo parts against the hi parts.
 constexpr float SPLIT_LO_UP = 4096.0f, SPLIT_LO_DOWN = 1.0f / 4096.0f;
 
 // FP16 parts of x: hi + lo / 4096; held: to 2^-23 of x (not so, among others, a value
@@ -243,6 +230,55 @@ __device__ __forceinline__ ChainParts chain_parts(float x)
     return p;
 }
 
+// The wide kernel's exponents stay at or above this: no pre-activation of values in parts
+// overflows then, on its own scale or the true one.
+constexpr int WIDE_EMIN = -40;
+// Its second layer's weights are FP32, and may be applied to pre-activations on the parts'
+// scale: below this, their products do not overflow there.
+constexpr float WIDE_W2_MAX = 0x1p64f;
+
+// Bits of the least magnitude but zero, doubled, less one: of what was seen and x.
+__device__ __forceinline__ uint32_t least_bits(uint32_t least, float x)
+{
+    const uint32_t u = (__float_as_uint(x) << 1) - 1u;
+    return u < least ? u : least;
+}
+// Whether parts hold all values whose least_bits on their exponent's scale are these and
+// that do not exceed FP16: from 2^-14 on, hi is a normal FP16 value and the last bit of lo
+// is at most 2^-22 of it.
+__device__ __forceinline__ bool parts_hold(uint32_t least) { return least >= (113u << 24) - 1u; }
+
+// How values of these largest magnitude (its bits) and least_bits are kept: as parts on
+// the exponent e, or raw (e is 0 then).  Infinities and NaNs are raw.
+struct RowForm {
+    int e;
+    int raw;
+};
+__device__ __forceinline__ RowForm row_form(uint32_t most, uint32_t least)
+{
+    if (most >= 0x7f800000u) return RowForm{0, 1};
+    const int e = part_exp(__uint_as_float(most));
+    if (least == 0xffffffffu) return RowForm{e, 0};   // all zero
+    const float low = __uint_as_float((least + 1u) >> 1);
+    const bool held = e >= WIDE_EMIN && low * __builtin_ldexpf(1.0f, e) >= 0x1p-14f;
+    return held ? RowForm{e, 0} : RowForm{0, 1};
+}
+
+// The 16-bit words of a value in the planes of a packed operand: FP16 parts of x c (c a
+// power of two), or, raw, the halves of its FP32 bits.  Zero is zero in both.
+struct Words {
+    uint16_t hi, lo;
+};
+__device__ __forceinline__ Words wide_words(float x, float c, bool raw)
+{
+    const uint32_t u = __float_as_uint(x);
+    const float v = x * c;
+    const _Float16 h = (_Float16)v;
+    const _Float16 l = (_Float16)__builtin_fmaf((float)h, -SPLIT_LO_UP, v * SPLIT_LO_UP);
+    return raw ? Words{(uint16_t)(u >> 16), (uint16_t)u}
+               : Words{__builtin_bit_cast(uint16_t, h), __builtin_bit_cast(uint16_t, l)};
+}
+
 // Position of element k (of a 32-column block) of an operand in parts, in the order that
 // the chain's lanes read: lane group g takes columns 4g..4g+3 and 16+4g..16+4g+3 as eight
 // consecutive elements.
@@ -255,21 +291,10 @@ __device__ __forceinline__ int split_pos(int k)
 // 16-byte chunks, so that the fragment reads served together hit distinct bank groups.
 __host__ __device__ constexpr int split_pitch(int cols) { return 2 * cols + 16; }
 
-// FP16 parts of v 2^e: hi + lo has 23 of its 24 bits.  An infinity is all hi.
-struct SplitF16 {
-    _Float16 hi, lo;
-};
-__device__ __forceinline__ SplitF16 split_f16(float v, int e)
-{
-    const float x = __builtin_ldexpf(v, e);
-    SplitF16 p;
-    p.hi = (_Float16)x;
-    p.lo = __builtin_isinf(x) ? (_Float16)0.0f : (_Float16)(x - (float)p.hi);
-    return p;
-}
-
-// Store spark coordinate j (< D) in its packed row at dst, in the row's precision.
-__device__ __forceinline__ void wide_store(const WidePack &p, char *dst, int j, float v)
+// Store spark coordinate j (< D) in its packed row at dst, in the row's precision (FP16
+// parts: of v c, or raw).
+__device__ __forceinline__ void wide_store(const WidePack &p, char *dst, int j, float v, float c = 1.0f,
+                                           bool raw = false)
 {
     const size_t plane = (size_t)256 * p.Kp;   // elements of a W1aug plane
     char *w2 = dst + plane * (p.kind == WIDE_BF16 ? 2 : 4);
@@ -299,15 +324,16 @@ __device__ __forceinline__ void wide_store(const WidePack &p, char *dst, int j, 
     if (p.kind == WIDE_BF16) {
         reinterpret_cast<__bf16 *>(dst)[at] = (__bf16)v;
     } else if (p.kind == WIDE_F16X2) {
-        const SplitF16 s = split_f16(v, p.wexp);
-        reinterpret_cast<_Float16 *>(dst)[at] = s.lo;
-        reinterpret_cast<_Float16 *>(dst)[plane + at] = s.hi;
+        const Words s = wide_words(v, c, raw);
+        reinterpret_cast<uint16_t *>(dst)[at] = s.lo;
+        reinterpret_cast<uint16_t *>(dst)[plane + at] = s.hi;
     } else {
         reinterpret_cast<float *>(dst)[at] = v;
     }
 }
 
-// The exponent and infinity flag at the end of a packed row of two FP16 parts.
+// At the end of a packed row of two planes: the exponent of its parts, and whether it is
+// raw (its planes are the halves of its FP32 values, exponent 0).
 __device__ __forceinline__ int32_t *wide_row_exp(char *row, int Kp)
 {
     return reinterpret_cast<int32_t *>(row + (size_t)256 * Kp * 4 + 16 * 256 * 4 + 64);
@@ -462,8 +488,7 @@ dim3 finalize_grid(const FitLaunch &f);
 hipError_t launch_pack_problem(const Net &net, const float *x, const float *y,
                                const int32_t *labels, const DevState &d, hipStream_t st);
 // The samples' exponents and any-marked flag for FP16 parts, into d.Xe.
-constexpr int XE_BAD = 1 << 20;    // Xe of a sample that its parts do not hold (wide kernel: + its exponent)
-hipError_t launch_sample_exp(const Net &net, const float *x, int32_t *Xe, hipStream_t st);
+constexpr int XE_BAD = 1 << 20;    // Xe of a sample that its parts do not hold (register chain)
 // largest partial-sum count per row any plan may use
 int fit_max_bpr();
 // whether the network may take the register chain in two FP16 parts
@@ -499,12 +524,9 @@ hipError_t wide_prepare(const Net &net);
 // Packed samples into d.Xw (two FP16 parts: their exponents into d.Xe).
 hipError_t launch_pack_wide_x(const Net &net, const float *x, const DevState &d, hipStream_t st);
 // prepacked: the first rows are already in d.Wpack (written by the explosion).
-// boxed: every row lies in the search box (FP16 parts take the box's exponent);
-// otherwise each row's exponent comes from its own largest weight.
 hipError_t launch_fitness_wide(const Net &net, const DevState &d, const float *W, size_t ld,
                                int rows, OutMap map, float *out, hipStream_t st,
-                               bool boxed, hipEvent_t mid = nullptr, hipEvent_t pre = nullptr,
-                               int prepacked = 0);
+                               hipEvent_t mid = nullptr, hipEvent_t pre = nullptr, int prepacked = 0);
 WidePack wide_pack_geometry(const Net &net, const DevState &d);
 
 // Record the message returned by mgfwa_last_error (printf format) and return code.

@@ -84,13 +84,13 @@ __global__ __launch_bounds__(TPB) void k_pop_range_group(GroupTable t)
 // layout (row `row` of wp.Wp): four coordinates of one W1 row inside one
 // 32-column block (the common case) as one store (one per FP16 part), others one
 // by one.
-typedef _Float16 halfx4 __attribute__((ext_vector_type(4)));
-typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
-
+// FP16 parts: times 2^wexp, and false when those do not hold a coordinate of W1 and b1.
 template <int KIND>
-__device__ __forceinline__ void pack_four(const WidePack &wp, int row, int j0, int D,
+__device__ __forceinline__ bool pack_four(const WidePack &wp, int row, int j0, int D,
                                           const float (&s)[4])
 {
+    const float c = __builtin_ldexpf(1.0f, wp.wexp);
+    uint32_t least = 0xffffffffu;
     char *dst = wp.Wp + (size_t)row * wp.pr;
     int o = -1, k = 0;
     if (j0 >= wp.woff1 && j0 + 3 < wp.woff1 + wp.hid * wp.in) {
@@ -108,33 +108,45 @@ __device__ __forceinline__ void pack_four(const WidePack &wp, int row, int j0, i
                                 ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)s[3]) << 16);
             *reinterpret_cast<uint2 *>(dst + at * 2) = make_uint2(lo, hi);
         } else if constexpr (KIND == WIDE_F16X2) {
-            halfx4 hi, lo;
+            uint32_t hi[2], lo[2];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const SplitF16 p = split_f16(s[e], wp.wexp);
-                hi[e] = p.hi;
-                lo[e] = p.lo;
+            for (int e = 0; e < 4; e += 2) {
+                const Words p = wide_words(s[e], c, false), q = wide_words(s[e + 1], c, false);
+                hi[e / 2] = p.hi | (uint32_t)q.hi << 16;
+                lo[e / 2] = p.lo | (uint32_t)q.lo << 16;
+                least = least_bits(least_bits(least, s[e] * c), s[e + 1] * c);
             }
-            *reinterpret_cast<halfx4 *>(dst + at * 2) = lo;
-            *reinterpret_cast<halfx4 *>(dst + ((size_t)256 * wp.Kp + at) * 2) = hi;
+            *reinterpret_cast<uint2 *>(dst + at * 2) = make_uint2(lo[0], lo[1]);
+            *reinterpret_cast<uint2 *>(dst + ((size_t)256 * wp.Kp + at) * 2) = make_uint2(hi[0], hi[1]);
         } else {
             *reinterpret_cast<float4 *>(dst + at * 4) = make_float4(s[0], s[1], s[2], s[3]);
         }
-        return;
+        return parts_hold(least);
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         if (j0 + e >= D) break;
-        wide_store(wp, dst, j0 + e, s[e]);
+        wide_store(wp, dst, j0 + e, s[e], c);
+        if (KIND == WIDE_F16X2 && j0 + e < wp.boff1 + wp.hid) least = least_bits(least, s[e] * c);
     }
+    return parts_hold(least);
 }
 
-// The exponent of an explosion spark's packed row (its weights lie in the box).
-__device__ __forceinline__ void pack_row_exp(const WidePack &wp, int row)
+// An explosion spark's packed row of two planes is one of parts, on the exponent of the
+// box that its weights lie in, unless the explosion meets a value that those do not hold
+// (mark_row) ...
+__global__ __launch_bounds__(TPB) void k_clear_rows(WidePack wp, int rows, const int32_t *__restrict__ ctrl)
 {
+    const int row = blockIdx.x * TPB + threadIdx.x;
+    if (row >= rows || ctrl[CTRL_DONE]) return;   // (a finished job keeps its sparks)
     int32_t *t = wide_row_exp(wp.Wp + (size_t)row * wp.pr, wp.Kp);
     t[0] = wp.wexp;
     t[1] = 0;
+}
+
+__device__ __forceinline__ void mark_row(const WidePack &wp, char *dst)
+{
+    atomicOr(&wide_row_exp(dst, wp.Kp)[1], 1);
 }
 
 // SE null: the FP32 rows are not stored (the packed rows are the only copy the
@@ -164,9 +176,8 @@ __device__ __forceinline__ void explode_body(const float *__restrict__ F, const 
         if (SE)
             reinterpret_cast<float4 *>(SE + (size_t)row * Dp)[chunk] = make_float4(s[0], s[1], s[2], s[3]);
         if constexpr (PACK >= 0)
-            if (4 * chunk < D) pack_four<PACK>(wp, row, 4 * chunk, D, s);
-        if constexpr (PACK == WIDE_F16X2)
-            if (chunk == 0) pack_row_exp(wp, row);
+            if (4 * chunk < D && !pack_four<PACK>(wp, row, 4 * chunk, D, s))
+                mark_row(wp, wp.Wp + (size_t)row * wp.pr);
     }
 }
 
@@ -226,6 +237,7 @@ __global__ __launch_bounds__(TPB) void k_explode_packed(const float *__restrict_
     // W1 columns k..k+7 of a row start on a 4-coordinate chunk of the spark
     const bool aligned = (wp.in & 3) == 0 && (wp.woff1 & 3) == 0;
     const int woff2 = wp.boff1 + wp.hid;                      // W2, then b2, up to D
+    const float c2e = KIND == WIDE_F16X2 ? __builtin_ldexpf(1.0f, wp.wexp) : 1.0f;
     for (int row = blockIdx.y; row < rows; row += gridDim.y) {
         const int gf = row / lam;
         const float amp = A[gf];
@@ -260,15 +272,17 @@ __global__ __launch_bounds__(TPB) void k_explode_packed(const float *__restrict_
                                ((uint32_t)__builtin_bit_cast(uint16_t, (__bf16)v[2 * e + 1]) << 16);
                     *reinterpret_cast<uint4 *>(p) = make_uint4(h[0], h[1], h[2], h[3]);
                 } else if constexpr (KIND == WIDE_F16X2) {
-                    halfx8 hi, lo;
+                    uint32_t h[4], l[4], least = 0xffffffffu;
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) {
-                        const SplitF16 sp = split_f16(v[e], wp.wexp);
-                        hi[e] = sp.hi;
-                        lo[e] = sp.lo;
+                    for (int e = 0; e < 8; e += 2) {
+                        const Words a = wide_words(v[e], c2e, false), b = wide_words(v[e + 1], c2e, false);
+                        h[e / 2] = a.hi | (uint32_t)b.hi << 16;
+                        l[e / 2] = a.lo | (uint32_t)b.lo << 16;
+                        least = least_bits(least_bits(least, v[e] * c2e), v[e + 1] * c2e);
                     }
-                    *reinterpret_cast<halfx8 *>(p) = lo;
-                    *reinterpret_cast<halfx8 *>(ph) = hi;
+                    *reinterpret_cast<uint4 *>(p) = make_uint4(l[0], l[1], l[2], l[3]);
+                    *reinterpret_cast<uint4 *>(ph) = make_uint4(h[0], h[1], h[2], h[3]);
+                    if (!parts_hold(least)) mark_row(wp, dst);
                 } else {
                     reinterpret_cast<float4 *>(p)[0] = make_float4(v[0], v[1], v[2], v[3]);
                     reinterpret_cast<float4 *>(p)[1] = make_float4(v[4], v[5], v[6], v[7]);
@@ -296,9 +310,10 @@ __global__ __launch_bounds__(TPB) void k_explode_packed(const float *__restrict_
                     if constexpr (KIND == WIDE_BF16) {
                         reinterpret_cast<uint16_t *>(p)[e] = __builtin_bit_cast(uint16_t, (__bf16)val);
                     } else if constexpr (KIND == WIDE_F16X2) {
-                        const SplitF16 sp = split_f16(val, wp.wexp);
-                        reinterpret_cast<_Float16 *>(p)[e] = sp.lo;
-                        reinterpret_cast<_Float16 *>(ph)[e] = sp.hi;
+                        const Words a = wide_words(val, c2e, false);
+                        reinterpret_cast<uint16_t *>(p)[e] = a.lo;
+                        reinterpret_cast<uint16_t *>(ph)[e] = a.hi;
+                        if (!parts_hold(least_bits(0xffffffffu, val * c2e))) mark_row(wp, dst);
                     } else {
                         reinterpret_cast<float *>(p)[e] = val;
                     }
@@ -308,8 +323,6 @@ __global__ __launch_bounds__(TPB) void k_explode_packed(const float *__restrict_
             // W2 and b2: chunk c covers coordinates 4c..4c+3; those below woff2 (b1)
             // belong to the W1aug blocks
             const int c = (woff2 >> 2) + ((int)blockIdx.x - units) * TPB + threadIdx.x;
-            if constexpr (KIND == WIDE_F16X2)
-                if (c == (woff2 >> 2)) pack_row_exp(wp, row);
             if (4 * c >= D) continue;
             const float4 x4 = xrow[c];
             const float x[4] = {x4.x, x4.y, x4.z, x4.w};
@@ -322,6 +335,65 @@ __global__ __launch_bounds__(TPB) void k_explode_packed(const float *__restrict_
                 wide_store(wp, dst, j, e == 0 ? s4[0] : e == 1 ? s4[1] : e == 2 ? s4[2] : s4[3]);
             }
         }
+    }
+}
+
+// ... then W1 and b1 are written again: as parts on the row's own exponent, or where that
+// does not hold them either, raw.  A block per row; ordinary rows (of weights uniform in
+// the box, one in a thousand of 784-256-10 has a value below 2^-28 of it) leave at once.
+constexpr int FIX_TPB = 1024;
+__global__ __launch_bounds__(FIX_TPB) void k_explode_fix(const float *__restrict__ F,
+                                                         const float *__restrict__ A, int lam, int rows,
+                                                         int D, int Dp, uint2 key, Box box,
+                                                         const int32_t *__restrict__ ctrl, int N,
+                                                         const float *__restrict__ lo,
+                                                         const float *__restrict__ hi, WidePack wp)
+{
+    if (ctrl[CTRL_DONE]) return;
+    const uint32_t tn = (uint32_t)ctrl[CTRL_GEN] + 1u;
+    __shared__ uint32_t most, least;
+    for (int row = blockIdx.x; row < rows; row += gridDim.x) {
+        char *dst = wp.Wp + (size_t)row * wp.pr;
+        int32_t *t = wide_row_exp(dst, wp.Kp);
+        if (t[1] == 0) continue;
+        const int gf = row / lam;
+        const float4 *xrow = reinterpret_cast<const float4 *>(F + (size_t)gf * Dp);
+        const size_t pb = (size_t)(gf / N) * Dp;
+        const int j0 = wp.woff1, j1 = wp.boff1 + wp.hid;
+        // f(j, value) over the row's W1 and b1
+        auto each = [&](auto &&f) {
+            for (int c = (j0 >> 2) + threadIdx.x; 4 * c < j1; c += FIX_TPB) {
+                const float4 x4 = xrow[c];
+                const float x[4] = {x4.x, x4.y, x4.z, x4.w};
+                float s4[4];
+                explosion_chunk(x, A[gf], key, c, (uint32_t)row, tn, box, lo ? lo + pb : nullptr,
+                                hi ? hi + pb : nullptr, D, s4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (4 * c + e >= j0 && 4 * c + e < j1) f(4 * c + e, s4[e]);
+            }
+        };
+        if (threadIdx.x == 0) {
+            most = 0;
+            least = 0xffffffffu;
+        }
+        __syncthreads();   // (every thread has read the mark, too)
+        uint32_t m = 0, l = 0xffffffffu;
+        each([&](int, float v) {
+            m = max(m, __float_as_uint(fabsf(v)));
+            l = least_bits(l, v);
+        });
+        atomicMax(&most, m);
+        atomicMin(&least, l);
+        __syncthreads();
+        const RowForm form = row_form(most, least);
+        if (threadIdx.x == 0) {
+            t[0] = form.e;
+            t[1] = form.raw;
+        }
+        const float c = __builtin_ldexpf(1.0f, form.e);
+        each([&](int j, float v) { wide_store(wp, dst, j, v, c, form.raw); });
+        __syncthreads();   // (most and least are read)
     }
 }
 
@@ -380,6 +452,11 @@ hipError_t launch_explode(const Shape &s, const DevState &d, hipStream_t st, con
                           bool write_se)
 {
     const int rows = s.BN * s.lam;
+    const bool planes = wp && wp->kind == WIDE_F16X2;
+    const float *lo = s.map_range ? d.lo : nullptr, *hi = s.map_range ? d.hi : nullptr;
+    if (planes)
+        hipLaunchKernelGGL(k_clear_rows, dim3((rows + TPB - 1) / TPB), dim3(TPB), 0, st, *wp, rows,
+                           d.ctrl);
     if (wp && !write_se) {
         // packed rows only, written in their own order
         const int units = (wp->Kp / 32) * ((wp->hid + XP_ROWS - 1) / XP_ROWS);
@@ -389,24 +466,25 @@ hipError_t launch_explode(const Shape &s, const DevState &d, hipStream_t st, con
         const int rpb = (long)bx * (rows / 8) >= 4096 ? 8 : 1;
         const int ry = (rows + rpb - 1) / rpb;
         const dim3 grid((unsigned)bx, ry < MAX_GRID_Y ? ry : MAX_GRID_Y);
-        const float *lo = s.map_range ? d.lo : nullptr, *hi = s.map_range ? d.hi : nullptr;
         auto *k = wp->kind == WIDE_BF16    ? &k_explode_packed<WIDE_BF16>
                   : wp->kind == WIDE_F16X2 ? &k_explode_packed<WIDE_F16X2>
                                            : &k_explode_packed<WIDE_F32>;
         hipLaunchKernelGGL(k, grid, dim3(TPB), 0, st, d.F, d.A, s.lam, rows, s.D, s.Dp, s.key, s.box, d.ctrl,
                            s.N, lo, hi, *wp, units);
-        return hipGetLastError();
+    } else {
+        const WidePack none{};
+        const WidePack &w = wp ? *wp : none;
+        auto *k = !wp                      ? &k_explode<-1>
+                  : wp->kind == WIDE_BF16  ? &k_explode<WIDE_BF16>
+                  : wp->kind == WIDE_F16X2 ? &k_explode<WIDE_F16X2>
+                                           : &k_explode<WIDE_F32>;
+        hipLaunchKernelGGL(k, explode_grid(s), dim3(TPB), 0, st, d.F, d.A,
+                           write_se || !wp ? d.SE : nullptr, s.lam, rows, s.D, s.Dp, s.key, s.box, d.ctrl,
+                           s.N, lo, hi, w);
     }
-    const WidePack none{};
-    const WidePack &w = wp ? *wp : none;
-    auto *k = !wp                      ? &k_explode<-1>
-              : wp->kind == WIDE_BF16  ? &k_explode<WIDE_BF16>
-              : wp->kind == WIDE_F16X2 ? &k_explode<WIDE_F16X2>
-                                       : &k_explode<WIDE_F32>;
-    hipLaunchKernelGGL(k, explode_grid(s), dim3(TPB), 0, st, d.F, d.A,
-                       write_se || !wp ? d.SE : nullptr, s.lam, rows,
-                       s.D, s.Dp, s.key, s.box, d.ctrl, s.N, s.map_range ? d.lo : nullptr,
-                       s.map_range ? d.hi : nullptr, w);
+    if (planes)
+        hipLaunchKernelGGL(k_explode_fix, dim3(rows < MAX_GRID_Y ? rows : MAX_GRID_Y), dim3(FIX_TPB), 0, st,
+                           d.F, d.A, s.lam, rows, s.D, s.Dp, s.key, s.box, d.ctrl, s.N, lo, hi, *wp);
     return hipGetLastError();
 }
 
