@@ -659,14 +659,15 @@ __device__ __forceinline__ float xor_max4(float v)
 }
 
 // e^x for x <= 0: 2^(x log2 e) on the exponential unit, the rounding of the product
-// carried into a correction factor.
+// carried into a correction factor.  The unit takes the product's fraction: it makes no
+// results below 2^-126, where a confident network's losses still tell sparks apart.
 __device__ __forceinline__ float exp_neg(float x)
 {
     constexpr float L2E = 1.44269504088896341f, L2E_LO = 1.925963033500865e-8f, LN2 = 0.693147180559945309f;
-    const float t = x * L2E;
+    const float t = x * L2E, n = __builtin_rintf(t);
     const float lo = __builtin_fmaf(x, L2E_LO, __builtin_fmaf(x, L2E, -t));
-    const float e = __builtin_amdgcn_exp2f(t);
-    return x < -104.0f ? 0.0f : __builtin_fmaf(e, lo * LN2, e);
+    const float e = __builtin_amdgcn_exp2f(t - n);
+    return x < -104.0f ? 0.0f : __builtin_ldexpf(__builtin_fmaf(e, lo * LN2, e), (int)n);
 }
 
 // A wavefront's running loss.  A sample's cross-entropy is d + log1p(q), d the distance
