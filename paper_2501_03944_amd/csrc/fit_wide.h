@@ -54,7 +54,7 @@
 //             (98.4 ms with FP32 instructions; 31.2 ms with the lo parts on the scale of the
 //             hi parts, right over 2^17 only), the fitness' error against binary64 9e-8 ->
 //             3e-8.  512 rows x 8,192 samples 4.5 ms; with one raw row 4.8, one raw sample
-//             5.0, all raw 14.2 (the same with FP32 operands 12.1).
+//             5.1, all raw 14.5 (the same with FP32 operands 12.1).
 //  * swizzle: a 16-byte chunk c of tile row r lives at chunk c ^ s(r), with
 //             s(r) = (r >> 1) & 3 for 64-byte rows (16-bit) and r & 7 for
 //             128-byte rows (FP32).  A 16-byte LDS read serves eight lanes at a time,
@@ -877,41 +877,43 @@ __device__ __forceinline__ floatx4 lds_read4_at(uint32_t addr)
     return v;
 }
 
-// How a tile's operands are staged: FP32 values, or two planes that are the halves of such
-// values (raw) or parts, of W and of X.
-enum Form32 : int { PLAIN = 0, RAW_W = 1, RAW_X = 2, RAW_WX = 3 };
-
-// Powers of two that parts are brought to their values by.
+// How a tile's planes make FP32 values: raw halves, or parts times a power of two.
 struct Scale32 {
     float w, x[8];     // of the row; of this lane's sample in each column block
+    int wraw, xraw;
 };
 
 __device__ __forceinline__ Scale32 scale32(const WideArgs &a, int r, int col, int n, int sh)
 {
     Scale32 s;
-    s.w = __builtin_ldexpf(1.0f, -wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp)[0]);
+    const int32_t *t = wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp);
+    s.w = __builtin_ldexpf(1.0f, -t[0]);
+    s.wraw = t[1];
+    s.xraw = a.Xe[a.S_pad + col];
 #pragma unroll
     for (int cb = 0; cb < 8; ++cb) s.x[cb] = __builtin_ldexpf(1.0f, -a.Xe[col * WT_N + 128 * sh + 16 * cb + n]);
     return s;
 }
 
 // Value E of a fragment from its words (HI: the first two registers are the hi plane's).
-template <bool HI, bool RAW>
-__device__ __forceinline__ float join_word(const floatx4 &f, int E, float c)
+template <bool HI>
+__device__ __forceinline__ float join_word(const floatx4 &f, int E, float c, int raw)
 {
     typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
     const float fh = HI ? f[E >> 1] : f[2 + (E >> 1)], fl = HI ? f[2 + (E >> 1)] : f[E >> 1];
     const uint32_t h = __float_as_uint(fh), l = __float_as_uint(fl);
-    if constexpr (RAW) return __uint_as_float(E & 1 ? (h & 0xffff0000u) | l >> 16 : h << 16 | (l & 0xffffu));
-    return __builtin_fmaf((float)__builtin_bit_cast(halfx2, l)[E & 1], c * SPLIT_LO_DOWN,
-                          (float)__builtin_bit_cast(halfx2, h)[E & 1] * c);
+    const float bits = __uint_as_float(__builtin_amdgcn_perm(h, l, E & 1 ? 0x07060302u : 0x05040100u));
+    // (multiply-adds take FP16 halves as they are)
+    const float parts = __builtin_fmaf((float)__builtin_bit_cast(halfx2, l)[E & 1], c * SPLIT_LO_DOWN,
+                                       __builtin_fmaf((float)__builtin_bit_cast(halfx2, h)[E & 1], c, 0.0f));
+    return raw ? bits : parts;
 }
 
-template <bool HI, bool RAW>
-__device__ __forceinline__ floatx4 join_words(const floatx4 &f, float c)
+template <bool HI>
+__device__ __forceinline__ floatx4 join_words(const floatx4 &f, float c, int raw)
 {
-    return floatx4{join_word<HI, RAW>(f, 0, c), join_word<HI, RAW>(f, 1, c), join_word<HI, RAW>(f, 2, c),
-                   join_word<HI, RAW>(f, 3, c)};
+    return floatx4{join_word<HI>(f, 0, c, raw), join_word<HI>(f, 1, c, raw), join_word<HI>(f, 2, c, raw),
+                   join_word<HI>(f, 3, c, raw)};
 }
 
 // An operand that vector instructions wrote, before multiplies written as inline assembly
@@ -972,12 +974,11 @@ __device__ __forceinline__ void stage_barrier()
 // accumulators live in AGPRs nothing else writes.)
 // Two planes: fragments are joined from their words as they arrive, in the shadow of the
 // multiplies, but for a step's first ones, whose scale is known in their own step only.
-template <int FORM, int KK, int RB, bool FIRST>
+template <bool PL, int KK, int RB, bool FIRST>
 __device__ __forceinline__ void rb32(uint32_t st, uint32_t stn, const char *wsrc, const char *xsrc, size_t plane,
                                      char *fill, const Lane32 &L, const Scale32 &sc, floatx4 (&acc)[8][8],
                                      floatx4 (&fa)[2], floatx4 &aj, floatx4 (&b0)[8], floatx4 (&b1)[8])
 {
-    constexpr bool PL = FORM != PLAIN, WRAW = FORM & RAW_W, XRAW = FORM & RAW_X;
     constexpr int RB1 = RB + 1 < 8 ? RB + 1 : 0;
     constexpr int J = 8 * KK + RB;              // A fragment J of the step lives in fa[J % 2]
     if constexpr (J < 15) fa[(J + 1) % 2] = lds_read4_at<PL, RB1>(st + L.aoff[RB + 1 < 8 ? KK : 1]);
@@ -1002,14 +1003,14 @@ __device__ __forceinline__ void rb32(uint32_t st, uint32_t stn, const char *wsrc
         constexpr bool B1 = KK == 0 && RB >= 4;
         constexpr int c0 = B1 ? 2 * (RB - 4) : 0;
         if constexpr (J == 0) {
-            aj = join_words<false, WRAW>(fa[0], sc.w);
+            aj = join_words<false>(fa[0], sc.w, sc.wraw);
             operand_wait(aj);
         }
         const floatx4 a = aj;
 #pragma unroll
         for (int cb = 0; cb < 8; ++cb) {
             if constexpr (J == 0) {
-                b0[cb] = join_words<true, XRAW>(b0[cb], sc.x[cb]);
+                b0[cb] = join_words<true>(b0[cb], sc.x[cb], sc.xraw);
                 operand_wait(b0[cb]);
             }
             mfma32<FIRST && KK == 0>(acc[RB][cb], a[0], bk[cb][0]);
@@ -1027,9 +1028,9 @@ __device__ __forceinline__ void rb32(uint32_t st, uint32_t stn, const char *wsrc
                 // (a value in the shadow of each multiply)
                 mfma32<false>(acc[RB][cb], a[v], bk[cb][v]);
                 const int i = 8 * (v - 1) + cb;
-                if (J < 15 && i < 4) aj[i] = join_word<false, WRAW>(fa[(J + 1) % 2], i, sc.w);
-                if (B1 && i >= 4 && i < 8) n0[i - 4] = join_word<true, XRAW>(b1[c0], i - 4, sc.x[c0]);
-                if (B1 && i >= 8 && i < 12) n1[i - 8] = join_word<true, XRAW>(b1[c0 + 1], i - 8, sc.x[c0 + 1]);
+                if (J < 15 && i < 4) aj[i] = join_word<false>(fa[(J + 1) % 2], i, sc.w, sc.wraw);
+                if (B1 && i >= 4 && i < 8) n0[i - 4] = join_word<true>(b1[c0], i - 4, sc.x[c0], sc.xraw);
+                if (B1 && i >= 8 && i < 12) n1[i - 8] = join_word<true>(b1[c0 + 1], i - 8, sc.x[c0 + 1], sc.xraw);
                 if (i < 12) __builtin_amdgcn_sched_barrier(0);
             }
         if constexpr (B1) {
@@ -1057,7 +1058,7 @@ __device__ __forceinline__ void rb32(uint32_t st, uint32_t stn, const char *wsrc
         lgkm_wait1(fa[(J + 1) % 2]);
     }
     if constexpr (RB + 1 < 8)
-        rb32<FORM, KK, RB + 1, FIRST>(st, stn, wsrc, xsrc, plane, fill, L, sc, acc, fa, aj, b0, b1);
+        rb32<PL, KK, RB + 1, FIRST>(st, stn, wsrc, xsrc, plane, fill, L, sc, acc, fa, aj, b0, b1);
 }
 
 // K step kt of a tile, global step q of the block (stage q & 1: a tile with an
@@ -1065,13 +1066,13 @@ __device__ __forceinline__ void rb32(uint32_t st, uint32_t stn, const char *wsrc
 // stage is complete for every wavefront and its first fragments are in b0 and
 // fa[0]; on exit the same holds for the next step (the next tile's first step
 // after a tile's last).
-template <int FORM, bool FIRST>
+template <bool PL, bool FIRST>
 __device__ __forceinline__ void step32(const WideArgs &a, char *smem, const Look &lk, int kt, int q,
                                        const Lane32 &L, const Scale32 &sc, floatx4 (&acc)[8][8],
                                        floatx4 (&fa)[2], floatx4 (&b0)[8], floatx4 (&b1)[8])
 {
     using C = Cfg32;
-    constexpr int TILEB = FORM != PLAIN ? PipeCfg::TILEB : C::TILEB;
+    constexpr int TILEB = PL ? PipeCfg::TILEB : C::TILEB;
     const size_t plane = (size_t)a.nk * PipeCfg::TILEB;
     const bool wrap = kt + 1 >= a.nk;
     const char *wsrc = wrap ? lk.wnext : lk.wcur + (size_t)(kt + 1) * TILEB;
@@ -1080,23 +1081,8 @@ __device__ __forceinline__ void step32(const WideArgs &a, char *smem, const Look
     const uint32_t st = (uint32_t)(uintptr_t)(lds_void_t *)(smem + (q & 1) * C::STAGEB);
     const uint32_t stn = (uint32_t)(uintptr_t)(lds_void_t *)fill;
     floatx4 aj = zero4();   // PL: the A fragment being multiplied
-    rb32<FORM, 0, 0, FIRST>(st, stn, wsrc, xsrc, plane, fill, L, sc, acc, fa, aj, b0, b1);
-    rb32<FORM, 1, 0, FIRST>(st, stn, wsrc, xsrc, plane, fill, L, sc, acc, fa, aj, b0, b1);
-}
-
-// The K steps of a tile, and the epilogue's global inputs, fetched meanwhile (after its
-// first step: the next step's wait covers them).
-template <int FORM>
-__device__ __forceinline__ void tile32(const WideArgs &a, char *smem, const Look &lk, int r, int col, int qbase,
-                                       const Lane32 &L, const Scale32 &sc, int wave, int lane,
-                                       floatx4 (&acc)[8][8], floatx4 (&fa)[2], floatx4 (&b0)[8],
-                                       floatx4 (&b1)[8], W2Frag<false> &w2, LaneSample &own)
-{
-    step32<FORM, true>(a, smem, lk, 0, qbase, L, sc, acc, fa, b0, b1);
-    w2_load<WIDE_F32>(a, r, wave & 1, lane & 15, lane >> 4, w2);
-    own = lane_sample<WIDE_F32>(a, r, col, wave, lane);
-    for (int kt = 1; kt < a.nk; ++kt) step32<FORM, false>(a, smem, lk, kt, qbase + kt, L, sc, acc, fa, b0, b1);
-    mfma_acc_sync(acc);
+    rb32<PL, 0, 0, FIRST>(st, stn, wsrc, xsrc, plane, fill, L, sc, acc, fa, aj, b0, b1);
+    rb32<PL, 1, 0, FIRST>(st, stn, wsrc, xsrc, plane, fill, L, sc, acc, fa, aj, b0, b1);
 }
 
 // PL: the tiles of two planes that k_fit_wide leaves out, their values joined from the
@@ -1108,7 +1094,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     __shared__ float red[4];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // uniform
-    const int n = lane & 15, nh = wave & 1, sh = wave >> 1;
+    const int n = lane & 15, g = lane >> 4, nh = wave & 1, sh = wave >> 1;
     const std::conditional_t<PL, SpreadIter, TileIter> it(a);
     const int ntiles = it.count();
     TileScan<PL, true> scan;
@@ -1133,22 +1119,17 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
         it.tile(i, &r, &col);
         if (qbase > 0) look_set<WIDE_F32, PL>(a, it, i, inext, ntiles, lk);
         floatx4 acc[8][8];
+        Scale32 sc{};
+        if constexpr (PL) sc = scale32(a, r, col, n, sh);
+        step32<PL, true>(a, smem, lk, 0, qbase, L, sc, acc, fa, b0, b1);
+        // the epilogue's global inputs, fetched while the tile's K loop runs
+        // (after its first step: the next step's wait covers them)
         W2Frag<false> w2;
-        LaneSample own;
-        auto run = [&](auto form, const Scale32 &sc) {
-            tile32<decltype(form)::value>(a, smem, lk, r, col, qbase, L, sc, wave, lane, acc, fa, b0, b1, w2, own);
-        };
-        if constexpr (PL) {
-            const Scale32 sc = scale32(a, r, col, n, sh);
-            if (wide_row_exp(a.Wp + (size_t)r * a.pr, a.Kp)[1] == 0)
-                run(std::integral_constant<int, RAW_X>{}, sc);
-            else if (a.Xe[a.S_pad + col] == 0)
-                run(std::integral_constant<int, RAW_W>{}, sc);
-            else
-                run(std::integral_constant<int, RAW_WX>{}, sc);
-        } else {
-            run(std::integral_constant<int, PLAIN>{}, Scale32{});
-        }
+        w2_load<WIDE_F32>(a, r, nh, n, g, w2);
+        const LaneSample own = lane_sample<WIDE_F32>(a, r, col, wave, lane);
+        for (int kt = 1; kt < a.nk; ++kt)
+            step32<PL, false>(a, smem, lk, kt, qbase + kt, L, sc, acc, fa, b0, b1);
+        mfma_acc_sync(acc);
         wide_epilogue<WIDE_F32, ACT, PL>(a, smem, r, col, wave, lane, acc, w2, red, own);
         if (inext >= ntiles) break;
         i = inext;
