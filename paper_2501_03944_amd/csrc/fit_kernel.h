@@ -70,7 +70,10 @@ __device__ __forceinline__ void mfma_acc_sync(floatx4 (&acc)[RB][CB])
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) asm volatile("" : "+a"(acc[rb][cb]));
+    // (no read of an accumulator is scheduled ahead of the wait states)
+    __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
