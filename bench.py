@@ -283,7 +283,8 @@ def kernel_roofline(wl, precision, fit_ms, workload_name):
     rows = wl.n_fireworks * wl.n_sparks
     flops = wl.flops_per_eval() * rows
     achieved = flops / (fit_ms / 1e3) / 1e12
-    # wide FP32 networks and register chains from 48 units on run in two FP16 parts
+    # wide FP32 networks and register chains from 48 units on run in two FP16 parts (the
+    # library's own rule: chain_split in fitness.hip)
     testbed = getattr(wl, "net", None) is not None
     split = (precision == "fp32" and not testbed and max(wl.widths[1:-1], default=0) >= 48 and
              min(wl.widths[:-1]) >= 20 and wl.widths[-1] >= 8)

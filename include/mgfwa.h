@@ -120,7 +120,10 @@ typedef struct {
  *   max_generations   T, the budget the loser-out prediction uses (>= 1)
  *   loser_out 1 enables the loser-out tournament
  *   precision fitness GEMMs in FP32, or BF16 operands with FP32 accumulation.
- *             With BF16 the candidates are ranked on their BF16 fitness (guiding
+ *             FP32 GEMMs of the larger networks run as products of FP16 parts that
+ *             hold every operand to 2^-23 of itself; what the parts cannot hold
+ *             (values 2^29 below the largest of their layer, sample or spark,
+ *             infinities, NaNs) goes through FP32 instructions.  With BF16 the candidates are ranked on their BF16 fitness (guiding
  *             groups, each firework's best candidate), and that best candidate is
  *             re-evaluated in FP32 before the selection compares it with its
  *             firework (Alg. 1, selection step), so the firework, initial and
@@ -319,7 +322,8 @@ MGFWA_API mgfwa_status mgfwa_evaluate(mgfwa_ctx *ctx, const float *w_dev, int ro
  * hip_stream  a stream created by the caller (NULL -> EINVAL).
  * Scratch: the packed samples, targets and per-row partial sums live in a
  * library-held device array of MGFWA_NOALLOC_SCRATCH_BYTES (one per device, held
- * until the process ends); rows are taken in chunks that fit it.  EINVAL when
+ * until the process ends, with a sixteenth as much again behind it for exponents of
+ * the samples); rows are taken in chunks that fit it.  EINVAL when
  * the packed problem plus one row does not fit.  The call allocates nothing
  * (no hipMalloc/hipFree, no library allocation) and does not wait for the device.
  * Every call on one device shares that device's array: calls that may overlap

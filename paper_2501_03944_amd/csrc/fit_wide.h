@@ -50,8 +50,8 @@
 //             the box's exponent, are looked at again when that fails (k_explode_fix).
 //             Of uniform weights in the box about one spark of 784-256-10 in two thousand
 //             is raw.
-//             Measured at 784-256-10: a generation of 4,096 sparks x 8,192 samples 31.9 ms
-//             (98.4 ms with FP32 instructions; 31.2 ms with the lo parts on the scale of the
+//             Measured at 784-256-10: a generation of 4,096 sparks x 8,192 samples 32.0 ms
+//             (98.4 ms with FP32 instructions; 31.3 ms with the lo parts on the scale of the
 //             hi parts, right over 2^17 only), the fitness' error against binary64 9e-8 ->
 //             3e-8.  512 rows x 8,192 samples 4.5 ms; with one raw row 4.8, one raw sample
 //             5.1, all raw 14.5 (the same with FP32 operands 12.1).

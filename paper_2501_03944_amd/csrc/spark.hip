@@ -340,7 +340,7 @@ __global__ __launch_bounds__(TPB) void k_explode_packed(const float *__restrict_
 
 // ... then W1 and b1 are written again: as parts on the row's own exponent, or where that
 // does not hold them either, raw.  A block per row; ordinary rows (of weights uniform in
-// the box, one in a thousand of 784-256-10 has a value below 2^-28 of it) leave at once.
+// the box, one in two thousand of 784-256-10 has a value that far below it) leave at once.
 constexpr int FIX_TPB = 1024;
 __global__ __launch_bounds__(FIX_TPB) void k_explode_fix(const float *__restrict__ F,
                                                          const float *__restrict__ A, int lam, int rows,
