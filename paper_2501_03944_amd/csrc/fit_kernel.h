@@ -662,25 +662,30 @@ __device__ __forceinline__ float xor_max4(float v)
 }
 
 // e^x for x <= 0: 2^(x log2 e) on the exponential unit, the rounding of the product
-// carried into a correction factor.  The unit takes the product's fraction: it makes no
-// results below 2^-126, where a confident network's losses still tell sparks apart.
+// carried into a correction factor.  The unit makes no results below 2^-126, where a
+// confident network's losses still tell sparks apart: those are taken 2^64 up.
 __device__ __forceinline__ float exp_neg(float x)
 {
     constexpr float L2E = 1.44269504088896341f, L2E_LO = 1.925963033500865e-8f, LN2 = 0.693147180559945309f;
-    const float t = x * L2E, n = __builtin_rintf(t);
+    const float t = x * L2E;
     const float lo = __builtin_fmaf(x, L2E_LO, __builtin_fmaf(x, L2E, -t));
-    const float e = __builtin_amdgcn_exp2f(t - n);
-    return x < -104.0f ? 0.0f : __builtin_ldexpf(__builtin_fmaf(e, lo * LN2, e), (int)n);
+    const float up = x < -80.0f ? 64.0f : 0.0f;
+    const float e = __builtin_amdgcn_exp2f(t + up);
+    const float y = __builtin_fmaf(e, lo * LN2, e) * (x < -80.0f ? 0x1p-64f : 1.0f);
+    return x < -104.0f ? 0.0f : y;
 }
 
 // A wavefront's running loss.  A sample's cross-entropy is d + log1p(q), d the distance
 // of the label's logit from the largest one and q the sum of the other classes'
 // exponentials; its four lanes (g = 0..3) hold the same d and q, so the logarithms of
 // four slabs are taken together, lane group g keeping slab g's pair until then (a
-// logarithm per slab was a third of the vector work of a narrow BF16 network).  The sum is
-// in binary64: in FP32 its rounding was most of an FP32 fitness' error.
+// logarithm per slab was a third of the vector work of a narrow BF16 network).  FP32
+// kernels add in binary64: in FP32 the sum's rounding was most of their fitness' error;
+// BF16 kernels, whose error is far above it, in FP32.
+template <bool BF>
 struct LossSum {
-    double total = 0.0;
+    using Sum = std::conditional_t<BF, float, double>;
+    Sum total = 0;
     float d = 0.0f, q = 0.0f;
     int slot = 0;
     __device__ __forceinline__ void flush()
@@ -699,9 +704,9 @@ __device__ __forceinline__ void load_labels(const FitArgs &a, int s0, int n, int
 }
 
 // Add the losses of this wavefront's P slabs (logits z).
-template <int P, int R>
+template <int P, int R, bool BF>
 __device__ __forceinline__ void slab_loss(const FitArgs &a, int l, int s0, int n, int g,
-                                          const floatx4 (&z)[P][R], const int (&lab)[P], LossSum &ls)
+                                          const floatx4 (&z)[P][R], const int (&lab)[P], LossSum<BF> &ls)
 {
     const int fo = a.fo[l];
 #pragma unroll
@@ -769,19 +774,20 @@ __device__ __forceinline__ void store_loss(const FitArgs &a, int r, int c, float
 
 // A block's wavefronts' losses, added in a fixed order: the wavefront's butterfly, then
 // the wavefronts in order.
-template <int NW>
-__device__ __forceinline__ void block_loss(const FitArgs &a, int r, int c, LossSum &loss)
+template <int NW, bool BF>
+__device__ __forceinline__ void block_loss(const FitArgs &a, int r, int c, LossSum<BF> &loss)
 {
-    __shared__ double red[NW];
+    using Sum = typename LossSum<BF>::Sum;
+    __shared__ Sum red[NW];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     if (a.loss == 1) loss.flush();
-    double lsum = loss.total;
+    Sum lsum = loss.total;
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) lsum += __shfl_xor(lsum, off);
     if (lane == 0) red[wave] = lsum;
     __syncthreads();
     if (threadIdx.x == 0) {
-        double t = red[0];
+        Sum t = red[0];
 #pragma unroll
         for (int i = 1; i < NW; ++i) t += red[i];
         store_loss(a, r, c, (float)t);
@@ -794,7 +800,7 @@ template <bool BF, bool WL, int P, int ACT, int R1, int R2, int R3, int R4, int 
 __device__ __forceinline__ void slab_group(const FitArgs &a, const LdsLayout &y, const float *w,
                                            const char *smem, const WView<BF, WL> &w0,
                                            const WView<BF, WL> &w1, const WView<BF, WL> &w2,
-                                           const WView<BF, WL> &w3, int s0, int n, int g, LossSum &loss)
+                                           const WView<BF, WL> &w3, int s0, int n, int g, LossSum<BF> &loss)
 {
     // The staged weights are re-read from LDS for every slab: without this
     // fence the compiler hoists those reads out of the loop and, short of
@@ -860,7 +866,7 @@ __device__ __forceinline__ void fit_body(const FitArgs &a, int bid)
     const WView<BF, WL> w2(a, a.lay, w, smem, 2, n, g), w3(a, a.lay, w, smem, 3, n, g);
     const int s_begin = c * a.spb;
     const int s_end = min(s_begin + a.spb, a.S_pad);
-    LossSum loss;
+    LossSum<BF> loss;
     for (int s0 = s_begin + wave * 16 * P; s0 < s_end; s0 += NW * 16 * P)
         slab_group<BF, WL, P, ACT, R1, R2, R3, R4, SCHED>(a, a.lay, w, smem, w0, w1, w2, w3, s0, n, g, loss);
     block_loss<NW>(a, r, c, loss);

@@ -473,7 +473,7 @@ __device__ __forceinline__ void split_layer(const SplitView<R> &wv, const floatx
 template <int NW, int ACT, int P, int R, int RN, int... RR>
 __device__ __forceinline__ bool split_chain(const FitArgs &a, const char *smem, int l, int s0, int n, int g,
                                             const int (&wexp)[MAXL], floatx4 (&h)[P][R],
-                                            const int (&lab)[P], LossSum &loss, bool ok)
+                                            const int (&lab)[P], LossSum<false> &loss, bool ok)
 {
     if constexpr (RN == 0) {
         if (!__all(ok)) return false;
@@ -496,7 +496,7 @@ __device__ __forceinline__ bool split_chain(const FitArgs &a, const char *smem, 
 template <int NW, int P, int ACT, int R1, int R2, int R3, int R4>
 __device__ __forceinline__ bool split_group(const FitArgs &a, const char *smem, const SplitView<0> &w0, int s0,
                                             int n, int g, const int (&wexp)[MAXL],
-                                            LossSum &loss)
+                                            LossSum<false> &loss)
 {
     // re-read the staged weights for every slab (a hoisted fragment set spills)
     asm volatile("" ::: "memory");
@@ -535,7 +535,7 @@ struct Redo {
 // weights.
 template <int NW, int P, int ACT, int R1, int R2, int R3, int R4>
 __device__ __forceinline__ void redo_groups(ArgsInMemory k, char *smem, int r, int s0, int s_end,
-                                            const Redo &redo, LossSum &loss)
+                                            const Redo &redo, LossSum<false> &loss)
 {
     asm volatile("" : "+s"(k));
     const FitArgs &a = *(const FitArgs *)k;
@@ -574,7 +574,7 @@ __device__ __forceinline__ void split_body(const FitArgs &a, ArgsInMemory k, int
     const SplitView<0> w0(a, smem, 0, n, g);
     const int s_begin = c * a.spb + wave * 16 * P;
     const int s_end = min(c * a.spb + a.spb, a.S_pad);
-    LossSum loss;
+    LossSum<false> loss;
     Redo redo;
     if (!held) redo.rest = 0;
     for (int s0 = s_begin, i = 0; s0 < s_end && i < redo.rest; s0 += NW * 16 * P, ++i)
