@@ -296,7 +296,8 @@ __device__ __forceinline__ void stage_weights(const FitArgs &a, const LdsLayout 
 // block's MFMAs (else right before use); bit 1: the first K block multiplies
 // with a zero addend instead of clearing the accumulators first (fewer
 // instructions, but more registers in most instances: enabled only where it
-// measured faster).
+// measured faster); bit 2: zero_pads (instances that give a layer more row blocks
+// than it needs).
 template <bool BF, bool WL, int P, int RO, int SCHED = 1, bool FOLD = false>
 __device__ __forceinline__ void layer_x(const FitArgs &a, const WView<BF, WL> &wv, int s0, int n,
                                         int g, floatx4 (&out)[P][RO], const floatx4 *c0 = nullptr)
@@ -587,10 +588,25 @@ __device__ __forceinline__ void load_bias(const FitArgs &a, const LdsLayout &y, 
     }
 }
 
+// Units past the width of hidden layer l are zero whatever its inputs are: an infinity
+// times their zero weights is a NaN, and a NaN times the next layer's zero weights too.
+// (17-40-33-20-3, 2,500 rows x 1,029 samples: 793 -> 829 us; looking only at the row blocks
+// that are not full, by scalar branches, 835.)
+template <int P, int R>
+__device__ __forceinline__ void zero_pads(const FitArgs &a, int l, int g, floatx4 (&h)[P][R])
+{
+    const int left = a.fo[l] - 4 * g;
+#pragma unroll
+    for (int rb = 0; rb < R; ++rb)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int p = 0; p < P; ++p) h[p][rb][v] = 16 * rb + v < left ? h[p][rb][v] : 0.0f;
+}
+
 // Bias then activation of layer l.  ACT >= 0 fixes the hidden activation at
 // compile time; ACT < 0 dispatches once per call on the runtime code.
-// MASK: units past the layer's width are zero whatever the inputs are (an infinite input
-// times their zero weights would be a NaN).
+// MASK: with zero_pads.
 template <int ACT, bool WL, bool MASK, int P, int R>
 __device__ __forceinline__ void bias_act(const FitArgs &a, const LdsLayout &y, const float *w,
                                          const char *smem, int l, int g, bool apply_act,
@@ -598,20 +614,11 @@ __device__ __forceinline__ void bias_act(const FitArgs &a, const LdsLayout &y, c
 {
     floatx4 bb[R];
     load_bias<WL, R>(a, y, w, smem, l, g, bb);
-    if constexpr (MASK) {
-#pragma unroll
-        for (int rb = 0; rb < R; ++rb)
-#pragma unroll
-            for (int v = 0; v < 4; ++v)
-                if (16 * rb + 4 * g + v >= a.fo[l]) {
-#pragma unroll
-                    for (int p = 0; p < P; ++p) h[p][rb][v] = 0.0f;
-                }
-    }
     if (!apply_act) {
         add_act<0, P, R>(h, bb);
         return;
     }
+    if constexpr (MASK) zero_pads(a, l, g, h);
     if constexpr (ACT >= 0) {
         add_act<ACT, P, R>(h, bb);
     } else {
@@ -796,7 +803,7 @@ __device__ __forceinline__ void block_loss(const FitArgs &a, int r, int c, LossS
 
 // The losses of one slab group: samples s0 .. s0 + 16 P - 1 of the spark whose weights
 // the views read (layout y).
-template <bool BF, bool WL, int P, int ACT, int R1, int R2, int R3, int R4, int SCHED, bool MASK = false>
+template <bool BF, bool WL, int P, int ACT, int R1, int R2, int R3, int R4, int SCHED>
 __device__ __forceinline__ void slab_group(const FitArgs &a, const LdsLayout &y, const float *w,
                                            const char *smem, const WView<BF, WL> &w0,
                                            const WView<BF, WL> &w1, const WView<BF, WL> &w2,
@@ -813,7 +820,7 @@ __device__ __forceinline__ void slab_group(const FitArgs &a, const LdsLayout &y,
     // addend of its first K block and the ReLU of a hidden layer is applied
     // to its BF16-rounded values as the next layer converts them, so no
     // per-value bias or activation pass runs.
-    constexpr bool FOLD = BF && (SCHED & 2) != 0 && ACT == 1;
+    constexpr bool FOLD = BF && (SCHED & 2) != 0 && ACT == 1, MASK = (SCHED & 4) != 0;
     floatx4 h1[P][R1], c1[R1];
     if constexpr (FOLD) load_bias<WL, R1>(a, y, w, smem, 0, g, c1);
     layer_x<BF, WL, P, R1, SCHED, FOLD>(a, w0, s0, n, g, h1, c1);
@@ -823,6 +830,7 @@ __device__ __forceinline__ void slab_group(const FitArgs &a, const LdsLayout &y,
         slab_loss<P, R1>(a, 0, s0, n, g, h1, lab, loss);
     } else {
         if constexpr (!FOLD) bias_act<ACT, WL, MASK, P, R1>(a, y, w, smem, 0, g, true, h1);
+        else if constexpr (MASK) zero_pads(a, 0, g, h1);
         floatx4 h2[P][R2], c2[R2];
         if constexpr (FOLD) load_bias<WL, R2>(a, y, w, smem, 1, g, c2);
         layer_h<BF, WL, P, R1, R2, SCHED, FOLD>(w1, h1, h2, c2);
@@ -832,6 +840,7 @@ __device__ __forceinline__ void slab_group(const FitArgs &a, const LdsLayout &y,
             slab_loss<P, R2>(a, 1, s0, n, g, h2, lab, loss);
         } else {
             if constexpr (!FOLD) bias_act<ACT, WL, MASK, P, R2>(a, y, w, smem, 1, g, true, h2);
+            else if constexpr (MASK) zero_pads(a, 1, g, h2);
             floatx4 h3[P][R3], c3[R3];
             if constexpr (FOLD) load_bias<WL, R3>(a, y, w, smem, 2, g, c3);
             layer_h<BF, WL, P, R2, R3, SCHED, FOLD>(w2, h2, h3, c3);
@@ -841,6 +850,7 @@ __device__ __forceinline__ void slab_group(const FitArgs &a, const LdsLayout &y,
                 slab_loss<P, R3>(a, 2, s0, n, g, h3, lab, loss);
             } else {
                 if constexpr (!FOLD) bias_act<ACT, WL, MASK, P, R3>(a, y, w, smem, 2, g, true, h3);
+                else if constexpr (MASK) zero_pads(a, 2, g, h3);
                 floatx4 h4[P][R4], c4[R4];
                 if constexpr (FOLD) load_bias<WL, R4>(a, y, w, smem, 3, g, c4);
                 layer_h<BF, WL, P, R3, R4, SCHED, FOLD>(w3, h3, h4, c4);

@@ -546,7 +546,7 @@ __device__ __forceinline__ void redo_groups(ArgsInMemory k, char *smem, int r, i
     const WView<false, true> v2(a, a.lay32, w, smem, 2, n, g), v3(a, a.lay32, w, smem, 3, n, g);
     for (int i = 0; s0 < s_end; s0 += NW * 16 * P, ++i)
         if (i >= redo.rest || (i < 64 && redo.marks >> i & 1))
-            slab_group<false, true, P, ACT, R1, R2, R3, R4, 1, true>(a, a.lay32, w, smem, v0, v1, v2, v3, s0,
+            slab_group<false, true, P, ACT, R1, R2, R3, R4, 5>(a, a.lay32, w, smem, v0, v1, v2, v3, s0,
                                                                      n, g, loss);
 }
 
